@@ -135,9 +135,7 @@ typedef struct {
                                    cached per kernel/precision/padded size in
                                    the file named by BEMFFT_TUNE_CACHE, if
                                    set),
-                                   2 + s schedule s: 0 and 1 (16 or 32 lanes
-                                   per pencil, by length) always exist; 2,
-                                   the wide one with 64 lanes per pencil,
+                                   2 + s schedule s: 0 and 1 always exist; 2
                                    only for Navier plans with padded z length
                                    256, 384 or 512 (else the default is
                                    kept).  Other values: EINVAL.            */

@@ -105,11 +105,13 @@ std::vector<cx<R>> twiddle_table(int64_t p) {
     return t;
 }
 
-int64_t auto_pad(int64_t n) {
+// Smallest supported length of at least len.
+int64_t auto_pad_len(int64_t len) {
     for (int64_t s : kSizes)
-        if (s >= 2 * n) return s;
+        if (s >= len) return s;
     return -1;
 }
+int64_t auto_pad(int64_t n) { return auto_pad_len(2 * n); }
 
 }  // namespace
 
@@ -143,10 +145,23 @@ int upload_twiddles(Engine *e, const bemfft_plan *p) {
     return e->precision == BEMFFT_FP64 ? upload_tw<double>(e, p) : upload_tw<float>(e, p);
 }
 
+// Schedule of the z pass without autotuning, from z-pass times measured on
+// MI355X (us, Navier bodies; schedules 0, 1, 2): P = 192 FP32 68, 73, 68,
+// FP64 170, 150, 170; P = 256 FP32 170, 173, 168, FP64 336, 336, 337; P = 384
+// FP32 612, 571, 571, FP64 1432, 1450, 1387.  Laplace: schedule 0 at every
+// length (P = 256 FP32 43, 49; P = 192 FP32 26, 29).
+static int default_zsched(int kernel, int precision, int64_t pz) {
+    if (kernel != BEMFFT_NAVIER3D) return 0;
+    const bool fp64 = precision == BEMFFT_FP64;
+    if (pz >= 320) return fp64 ? 2 : 1;
+    return fp64 ? 1 : 0;
+}
+
 int alloc_workspace(bemfft_plan *p, Engine *e) {
     BF_CHECK(alloc_intermediates(p, e->precision, e));
+    e->zsched = default_zsched(p->kernel, e->precision, p->P[2]);
     // 16-bit spectra: kz rows padded to a multiple of 8 values (16-byte runs)
-    e->hzs = e->precision == BEMFFT_BF16_MFMA ? (p->H[2] + 7) / 8 * 8 : p->H[2];
+    e->hzs = e->precision == BEMFFT_BF16_MFMA ? (p->H[2] + 7) / 8 * 8 : spec_row(z_split(p->kernel, e->precision == BEMFFT_FP64, p->P[2]), (int)p->H[2]);
     const size_t spec = (size_t)p->K * p->H[0] * p->H[1] * e->hzs * e->sreal;
     if (hipMalloc(&e->spec, spec) != hipSuccess) {
         set_error("hipMalloc of the spectra failed");
@@ -193,7 +208,7 @@ void fill_apply_args(const bemfft_plan *p, const Engine &e, const Engine &ws, Ap
     a.nd = (int)p->nd;
     a.row_inv = p->row_inv;
     a.fwd_xg = p->fwd_xg;
-    a.zsched = p->zsched;
+    a.zsched = e.zsched;
     a.off = 0;
     a.gid = 0;
     *out = a;
@@ -301,7 +316,6 @@ int implicit_free_term(bemfft_plan *p, const Engine &e64, hipStream_t st, std::v
 
 int autotune_zsched(bemfft_plan *p, hipStream_t st);
 int num_zsched(const bemfft_plan *p);
-int default_zsched(const bemfft_plan *p);
 
 int plan_create_impl(bemfft_plan *p, const bemfft_grid *grid, int64_t m, const double *nodes,
                      const double *normals, const double *weights, int kernel, double nu, double mu,
@@ -368,10 +382,10 @@ int plan_create_impl(bemfft_plan *p, const bemfft_grid *grid, int64_t m, const d
                           " is unsupported or shorter than 2n-1");
                 return BEMFFT_EUNSUPPORTED;
             }
-            p->P[a] = pad;
+            p->pad[a] = p->P[a] = pad;
             p->H[a] = pad / 2 + 1;
         } else {
-            p->P[a] = 1;
+            p->pad[a] = p->P[a] = 1;
             p->H[a] = 1;
         }
     }
@@ -407,6 +421,21 @@ int plan_create_impl(bemfft_plan *p, const bemfft_grid *grid, int64_t m, const d
     const int zlo = g[perm[0] * 3 + 2], zhi = g[perm[m - 1] * 3 + 2];
     p->z0 = zlo;
     p->nzo = zhi - zlo + 1;
+    if (d == 3 && grid->pad[2] == 0 && prec != BEMFFT_BF16_MFMA) {
+        // Only offsets between occupied planes occur along z, in the apply and
+        // in the grid evaluation alike, so a padded length of 2 nzo - 1 carries
+        // the same sums; a body that does not fill its box then takes a shorter
+        // transform (a length that the caller asked for is kept, and the 16-bit
+        // form, bound by other loads, keeps the grid's: 33 us against 35).
+        // Navier takes 384 rather than 320, whose half transform has no schedule
+        // of few exchanges (192^3 star-like body, FP32: 569 us against 597).
+        int64_t pz = auto_pad_len(2 * p->nzo - 1);
+        if (pz == 320 && kernel == BEMFFT_NAVIER3D) pz = 384;
+        if (pz < p->P[2]) {
+            p->P[2] = pz;
+            p->H[2] = pz / 2 + 1;
+        }
+    }
     const int64_t ny = p->n[1];
     std::vector<int> rowptr((size_t)p->nzo * ny + 1, 0);
     std::vector<int> sgx(m), sgy(m), sgz(m);
@@ -478,7 +507,7 @@ int plan_create_impl(bemfft_plan *p, const bemfft_grid *grid, int64_t m, const d
     e64.sreal = 8;
     int status = alloc_workspace(p, &e64);
     if (!status) status = upload_twiddles(&e64, p);
-    if (!status) status = build_spectra(p, &e64, nullptr, st);
+    if (!status) status = build_spectra(p, &e64, st);
     if (status) { free_engine(&e64); return status; }
     // free term
     std::vector<double> Cs;
@@ -522,8 +551,7 @@ int plan_create_impl(bemfft_plan *p, const bemfft_grid *grid, int64_t m, const d
         if (!status) status = upload_twiddles(&e32, p);
         if (!status) {
             // the FP64 spectra rounded once to the stored precision, on the device
-            const int64_t hz = p->H[2], rows = (int64_t)p->K * p->H[0] * p->H[1];
-            status = convert_spectra(static_cast<const double *>(e64.spec), &e32, rows, hz, st);
+            status = convert_spectra(p, e64, &e32, st);
             if (!status && hipStreamSynchronize(st) != hipSuccess) {
                 set_error("spectrum conversion failed");
                 status = BEMFFT_EDEVICE;
@@ -542,46 +570,26 @@ int plan_create_impl(bemfft_plan *p, const bemfft_grid *grid, int64_t m, const d
     const int tune = opts ? opts->autotune : 0;
     // the 16-bit z pass has one schedule (its transforms are matrix products)
     if (p->dim == 3 && prec != BEMFFT_BF16_MFMA) {
-        p->zsched = default_zsched(p);
-        if (tune >= 2 && tune - 2 < num_zsched(p)) p->zsched = tune - 2;
+        p->zsched = p->eng.zsched;
+        if (tune >= 2 && tune - 2 < num_zsched(p)) p->eng.zsched = p->zsched = tune - 2;
         else if (tune == 1) BF_CHECK(autotune_zsched(p, st));
     }
     p->plan_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     return 0;
 }
 
-// Cache entries hold zsched + 4 (fwd_xg - 1); the "2:" prefix keeps entries
-// written before the forward width was tuned (z schedule only) from being read.
+// Cache entries hold zsched + 4 (fwd_xg - 1); the "3:" prefix keeps entries
+// written for other sets of schedules from being read.
 std::string tune_key(const bemfft_plan *p) {
-    return "2:" + std::to_string(p->kernel) + ":" + std::to_string(p->eng.precision) + ":" + std::to_string(p->P[0]) +
-           "x" + std::to_string(p->P[1]) + "x" + std::to_string(p->P[2]);
+    return "3:" + std::to_string(p->kernel) + ":" + std::to_string(p->eng.precision) + ":" + std::to_string(p->P[0]) +
+           "x" + std::to_string(p->P[1]) + "x" + std::to_string(p->P[2]) + "/" + std::to_string(num_zsched(p));
 }
 
-// Compiled z schedules of a plan: the default and the alternative one, and
-// for the Navier family the wide one where the length has it.
+// Compiled z schedules of a plan: the default and the alternative one, and a
+// third for the Navier family where the padded z length is 256, 384 or 512.
 int num_zsched(const bemfft_plan *p) {
-    return (p->kernel == BEMFFT_NAVIER3D && has_wide_sched((int)p->P[2])) ? 3 : 2;
-}
-
-// Schedule used without autotuning, from z-pass times measured on MI355X
-// (Navier spheres and stars, median of single applies).  Navier keeps three
-// output transforms live per pencil, so its fastest schedule depends on the
-// precision and the length:
-//   P = 256: FP32 16-lane 196 us (wide 240, 32-lane 347), FP64 32-lane 343 us
-//            (wide 499, 16-lane 933);
-//   P = 384: FP32 32-lane 0.76 ms (wide 1.06, 16-lane 2.64),
-//            FP64 wide 1.86 ms (32-lane 3.67, 16-lane 3.69);
-//   P = 512: FP32 32-lane 1.50 ms (wide 2.57), FP64 wide 2.87 ms (32-lane 10.55).
-// Other Navier lengths take the 32-lane schedule; Laplace keeps schedule 0.
-int default_zsched(const bemfft_plan *p) {
-    if (p->kernel != BEMFFT_NAVIER3D) return 0;
-    const bool fp64 = p->eng.precision == BEMFFT_FP64;
-    switch (p->P[2]) {
-        case 256: return fp64 ? 1 : 0;
-        case 384:
-        case 512: return fp64 ? 2 : 1;
-        default: return 1;
-    }
+    const int64_t pad = p->pad[2];
+    return (p->kernel == BEMFFT_NAVIER3D && (pad == 256 || pad == 384 || pad == 512)) ? 3 : 2;
 }
 
 int tune_cache_lookup(const std::string &key) {
@@ -614,7 +622,7 @@ int autotune_zsched(bemfft_plan *p, hipStream_t st) {
     const int nsched = num_zsched(p);
     const int cached = tune_cache_lookup(key);
     if (cached >= 0 && cached % 4 < nsched && cached / 4 < 2) {
-        p->zsched = cached % 4;
+        p->eng.zsched = p->zsched = cached % 4;
         p->fwd_xg = cached / 4 + 1;
         return 0;
     }
@@ -648,13 +656,14 @@ int autotune_zsched(bemfft_plan *p, hipStream_t st) {
         *us = 1e3 * ms / reps;
     };
     for (int sched = 0; sched < nsched && status == 0; ++sched) {
-        p->zsched = sched;
+        p->eng.zsched = sched;
         time_apply(&p->tune_us[sched]);
     }
     if (status == 0) {
         p->zsched = 0;
         for (int sched = 1; sched < nsched; ++sched)
             if (p->tune_us[sched] < p->tune_us[p->zsched]) p->zsched = sched;
+        p->eng.zsched = p->zsched;
     }
     // the width in use was timed with every schedule above; only the other one
     // needs applies of its own
@@ -775,7 +784,7 @@ int bemfft_plan_get_info(const bemfft_plan *p, bemfft_plan_info *info) {
     info->ncomp = p->ncomp;
     for (int a = 0; a < 3; ++a) {
         info->n[a] = p->n[a];
-        info->pad[a] = p->P[a];
+        info->pad[a] = p->pad[a];
     }
     info->z_lo = p->z0;
     info->z_count = p->nzo;

@@ -8,7 +8,7 @@
 //   k_zpass    per (kx, tile of ky): forward z-FFT of every field (input zero
 //              outside the occupied planes), products with the compact kernel
 //              spectra summed into each output (eqs. 15-16), inverse z-FFT,
-//              keep the occupied planes.              -> Z[o][kx][z][ky]
+//              keep the occupied planes (zsched.hpp).  -> Z[o][kx][z][ky]
 //   k_inv_y    per occupied z-plane and chunk of kx: inverse y-FFT in
 //              registers/LDS, rows y < ny stored with kx contiguous
 //                                                      -> W[o][z][y][kx] (in Y)
@@ -20,8 +20,10 @@
 //              k_rows_inv, instead)
 //
 // Layout: complex intermediates are interleaved (re, im) in the working
-// precision R with ky contiguous, so every global access is a run of whole
-// rows; kernel spectra are [c][kx][ky][kz] reals over one octant.
+// precision R.  Y is tiled for the z pass, [f][kx][ky / KT][z][KT] (the 16-bit
+// form and 2D plans: [f][kx][z][ky]); Z is [o][kx][z][ky].  Kernel spectra
+// are reals over one octant in the order of spec_index (16-bit form:
+// [c][kx][ky][kz]).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -31,6 +33,7 @@
 #include "fft_device.hpp"
 #include "internal.hpp"
 #include "kinds.hpp"
+#include "zsched.hpp"
 
 namespace bemfft {
 
@@ -41,7 +44,7 @@ struct ApplyArgs {
     int hzs;          // stored kz row length of the spectra (hz, or padded)
     int z0, nzo;
     int m;
-    int zsched;       // radix schedule of the z pass (0, 1, or 2 where a wide one exists)
+    int zsched;       // radix schedule of the z pass (0, 1, or 2 for Navier)
     int64_t off;      // batched apply: offset of this member's q, u, r
     int gid;          // batched apply: member index in the whole batch
     const int *gx, *gy, *gz, *rowptr, *perm;
@@ -76,8 +79,8 @@ struct BatchIO {
     const int *active;  // null: all members
 };
 
-constexpr int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
-constexpr int mini(int a, int b) { return a < b ? a : b; }
+__host__ __device__ constexpr int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
+__host__ __device__ constexpr int mini(int a, int b) { return a < b ? a : b; }
 constexpr int kMaxPx = 1024;         // largest padded length along x (2D plans; 3D stop at 512)
 
 // Complex value stored in 16 bits per part (the intermediates Y and Z of the
@@ -279,6 +282,15 @@ __global__ __launch_bounds__(256) void kb_rows_fft(const ApplyArgs *members, con
     rows_fft_body<R, PX, KIND>(a, blockIdx.x, blockIdx.y, blockIdx.z % zdiv);
 }
 
+// Blocks go to the 8 XCDs round-robin, so block b runs on XCD b % 8; item(b)
+// gives each XCD one contiguous run of the total work items (-1: none), so
+// that neighbouring items share its L2.  Grid: 8 * ceil(total / 8) blocks.
+__device__ __forceinline__ int xcd_item(int b, int total) {
+    const int per = (total + 7) / 8;
+    const int lam = (b % 8) * per + b / 8;
+    return b / 8 < per && lam < total ? lam : -1;
+}
+
 // ------------------------------------------------------------------ k_fwd_xy
 template <typename R, int PY, int KIND>
 struct FwdCfg {
@@ -296,15 +308,13 @@ struct FwdCfg {
 // XG: kx per thread in the direct DFT (1, or 2 on plans whose short rows
 // hold few nodes, where one node load then serves two kx).
 template <typename R, int PY, int KIND, int XG_, typename YS = cx<R>>
-__device__ __forceinline__ void fwd_xy_body(const ApplyArgs &a, const int bx, const int by, const int bz) {
-    if (by >= a.nzo) return;  // batched: a member with fewer occupied planes
+__device__ __forceinline__ void fwd_xy_body(const ApplyArgs &a, const int bx, const int zz) {
     using Cfg = FwdCfg<R, PY, KIND>;
     constexpr int F = Cfg::F, KXC = Cfg::KXC, NT = Cfg::NT, TPP = Cfg::TPP, PS = Cfg::PS, E = PY / TPP;
     __shared__ cx<R> buf[F * KXC * PS];
     __shared__ cx<R> tw[PY];
     const int tid = threadIdx.x;
     const int kx0 = bx * KXC;
-    const int zz = by;
     const cx<R> *gtwx = static_cast<const cx<R> *>(a.twx);
     const cx<R> *gtwy = static_cast<const cx<R> *>(a.twy);
     const R *vf = static_cast<const R *>(a.vf);
@@ -382,60 +392,119 @@ __device__ __forceinline__ void fwd_xy_body(const ApplyArgs &a, const int bx, co
     }
     fft_regs<R, PY, -1>(x, pb, tw, t);
     if (kx < a.hx) {
-        YS *Y = static_cast<YS *>(a.Y) + ((size_t)(f * a.hx + kx) * a.nzo + zz) * PY;
+        YS *Y = static_cast<YS *>(a.Y) + (size_t)(f * a.hx + kx) * a.nzo * PY;
+        if constexpr (std::is_same<YS, cbf16>::value) {
+            Y += (size_t)zz * PY;
 #pragma unroll
-        for (int e = 0; e < E; ++e) Y[t + e * TPP] = to_store<YS>(x[e]);
+            for (int e = 0; e < E; ++e) Y[t + e * TPP] = to_store<YS>(x[e]);
+        } else {
+            const int l = z_tile_log2(KIND, sizeof(R) == 8, a.pz);
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const int ky = t + e * TPP;
+                Y[((((ky >> l) * a.nzo) + zz) << l) + (ky & ((1 << l) - 1))] = x[e];
+            }
+        }
     }
 }
 
-template <typename R, int PY, int KIND, int XG, typename YS = cx<R>>
-// Grid (nzo, kx groups): consecutive blocks take consecutive planes of the
-// same kx group, so blocks in flight write neighbouring rows of Y.
-__global__ __launch_bounds__((FwdCfg<R, PY, KIND>::NT)) void k_fwd_xy(ApplyArgs a) {
-    fwd_xy_body<R, PY, KIND, XG, YS>(a, blockIdx.y, blockIdx.x, blockIdx.z);
+// Items (kx group, plane), planes fastest: the blocks in flight on one XCD
+// write neighbouring planes of the same tiles of Y, so its L2 joins their
+// parts of a cache line.
+template <typename R, int PY, int KIND, int XG, typename YS>
+__device__ __forceinline__ void fwd_xy_item(const ApplyArgs &a, const int b) {
+    constexpr int KXC = FwdCfg<R, PY, KIND>::KXC;
+    const int total = (a.hx + KXC - 1) / KXC * a.nzo;
+    // the 16-bit form and 2D plans write whole lines: any order will do
+    constexpr bool WHOLE = KIND == 0 || KIND == 3 || std::is_same<YS, cbf16>::value;
+    const int lam = WHOLE ? (b < total ? b : -1) : xcd_item(b, total);
+    if (lam < 0) return;
+    fwd_xy_body<R, PY, KIND, XG, YS>(a, lam / a.nzo, lam % a.nzo);
 }
 
-// Batched form: blockIdx.z = member * zdiv + the kernel's own z index.
+template <typename R, int PY, int KIND, int XG, typename YS = cx<R>>
+__global__ __launch_bounds__((FwdCfg<R, PY, KIND>::NT)) void k_fwd_xy(ApplyArgs a) {
+    fwd_xy_item<R, PY, KIND, XG, YS>(a, blockIdx.x);
+}
+
+// Batched form: blockIdx.z = member.
 template <typename R, int PY, int KIND>
-__global__ __launch_bounds__((FwdCfg<R, PY, KIND>::NT)) void kb_fwd_xy(const ApplyArgs *members, const BatchIO *io, int zdiv) {
-    ApplyArgs a = members[blockIdx.z / zdiv];
+__global__ __launch_bounds__((FwdCfg<R, PY, KIND>::NT)) void kb_fwd_xy(const ApplyArgs *members, const BatchIO *io) {
+    const ApplyArgs &a = members[blockIdx.z];
     if (io->active && !io->active[a.gid]) return;
-    a.q = io->q + a.off;
-    a.u = io->u + a.off;
-    a.r = io->r + a.off;
-    fwd_xy_body<R, PY, KIND, 1>(a, blockIdx.x, blockIdx.y, blockIdx.z % zdiv);
+    fwd_xy_item<R, PY, KIND, 1, cx<R>>(a, blockIdx.x);
 }
 
 // ------------------------------------------------------------------ k_zpass
-// One wavefront owns PPW = 64/TPP pencils (consecutive ky at one kx) from
-// load to store; waves never wait for each other, so the loads of one wave
-// overlap the transforms of the others.  Lane t of a pencil loads the rows
-// its first FFT stage needs straight into registers, multiplies the
-// transformed values in registers, and stores the inverse transform's rows
-// from registers: LDS only carries the exchange between FFT stages.
+// A wavefront owns PPW = 64/TPP pencils (consecutive ky at one kx) from load
+// to store; with D = 2 (Navier) two wavefronts share them, one with the even
+// frequencies and one with the odd ones, and add their halves at the end,
+// each storing half of the planes.  Lane t of a pencil loads the rows its
+// first FFT stage needs straight into registers (the next field's while the
+// current one is transformed), multiplies the transformed values in registers
+// and stores the inverse transform's rows from registers.  LDS carries the
+// exchanges between FFT stages and, in FP32, the spectrum rows: read straight
+// from memory they would be 4-byte loads over many rows per instruction, each
+// value four times (the two reflections); so a field's rows come in as one
+// run of 16-byte direct-to-LDS loads, in flight during the transform.
 template <typename R, typename SH, int KIND>
 struct ZCfg {
-    static constexpr int PZ = SH::P;
+    static constexpr int D = SH::D, L = SH::L, PZ = D * L;
+    static_assert(D == z_split(KIND, sizeof(R) == 8, PZ), "the stored spectra's split");
     static constexpr int TPP = SH::TPP;
     static constexpr int PPW = 64 / TPP;
+    static constexpr int KT = 1 << z_tile_log2(KIND, sizeof(R) == 8, PZ);
     static constexpr int CB = (int)sizeof(cx<R>);
-    static constexpr int PS = pstride<PZ>();
-    static constexpr int WAVES = clampi((64 * 1024) / (PPW * PS * CB), 1, 4);
-    static constexpr int TY = PPW * WAVES;
+    static constexpr int PS = SH::PS;
+        static constexpr int WAVES = 4;
+    static constexpr int SETS = WAVES / D;  // groups of PPW pencils per block
+    static constexpr int TY = PPW * SETS;
     static constexpr int NT = 64 * WAVES;
-    static constexpr int E = PZ / TPP;
+    static constexpr int E = SH::E;
+    static constexpr int EI = D == 1 ? E / 2 : E;  // elements that hold planes (n < P/2)
+    static constexpr bool STAGE = sizeof(R) == 4;  // spectrum rows through LDS
+    // The next field's planes are loaded during the current field's transform
+    // while they, the field and the sums take at most 160 registers: beyond,
+    // the overlap costs more occupancy than it hides (FP64 Laplace: 256 points
+    // 84 -> 79 us with it, 384 points 389 -> 532; FP64 Navier: 256 points 342
+    // -> 326, 192 points 150 -> 335; FP32 Navier, 384 points: 619 -> 567).
+    static constexpr bool PREFETCH = ((Terms<KIND>::O + 1) * E + EI) * (CB / 4) <= 160;
+    static constexpr int NC = max_field_ncomp<KIND>();
+    static constexpr int CHUNK = (PPW * spec_len(D, 0, PZ / 2 + 1) * (int)sizeof(R) + 1023) / 1024 * 1024;
+    static_assert(PPW <= KT, "a wavefront's ky share a tile");
+    static_assert(E % 2 == 0, "lower and reflected frequencies are told apart by e");
 };
 
-// Kernel spectrum value for component c at (kx, ky, kz) from the octant
-// store, with the reflection sign of each odd axis.
+// Buffer descriptor of a uniform byte range: loads past its end return zero,
+// stores past its end are dropped.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_range(const void *p, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00027000);
+}
+typedef unsigned uvec2 __attribute__((ext_vector_type(2)));
+typedef unsigned uvec4 __attribute__((ext_vector_type(4)));
+template <typename R>
+__device__ __forceinline__ cx<R> buf_load(__amdgpu_buffer_rsrc_t r, int off) {
+    if constexpr (sizeof(R) == 4) return __builtin_bit_cast(cx<R>, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+    else return __builtin_bit_cast(cx<R>, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
+template <typename R>
+__device__ __forceinline__ R buf_load_real(__amdgpu_buffer_rsrc_t r, int off) {
+    if constexpr (sizeof(R) == 4) return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+    else return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+}
+template <typename R>
+__device__ __forceinline__ void buf_store(cx<R> v, __amdgpu_buffer_rsrc_t r, int off) {
+    if constexpr (sizeof(R) == 4) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uvec2, v), r, off, 0, 0);
+    else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uvec4, v), r, off, 0, 0);
+}
+
+// Kernel spectrum value of a 2D plan for component c at (kx, ky) from the
+// quadrant store, with the reflection sign of an odd y axis.
 template <typename R, int KIND>
-__device__ __forceinline__ R spec_at(const R *spec, const ApplyArgs &a, int c, int kx, int ky, int kz) {
-    const int mask = comp_oddmask(KIND, c);
+__device__ __forceinline__ R spec_at(const R *spec, const ApplyArgs &a, int c, int kx, int ky) {
     const int kyp = ky < a.hy ? ky : a.py - ky;
-    const int kzp = kz < a.hz ? kz : a.pz - kz;
-    R s = spec[(((size_t)c * a.hx + kx) * a.hy + kyp) * a.hz + kzp];
-    const bool flip = ((ky >= a.hy) && (mask & 2)) != ((kz >= a.hz) && (mask & 4));
-    return flip ? -s : s;
+    const R s = spec[((size_t)c * a.hx + kx) * a.hy + kyp];
+    return (ky >= a.hy) && (comp_oddmask(KIND, c) & 2) ? -s : s;
 }
 
 template <typename R>
@@ -450,24 +519,26 @@ __device__ __forceinline__ void mac(cx<R> &acc, cx<R> v, R s, bool imag) {
 }
 
 template <typename R, typename SH, int KIND>
-__device__ __forceinline__ void zpass_body(const ApplyArgs &a, const int bx, const int by, const int bz) {
+__device__ __forceinline__ void zpass_body(const ApplyArgs &a, const int kx, const int by) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the host pass cannot type-check the buffer builtins
     using Cfg = ZCfg<R, SH, KIND>;
-    constexpr int PZ = SH::P;
     using T = Terms<KIND>;
-    constexpr int PPW = Cfg::PPW, TY = Cfg::TY, NT = Cfg::NT, TPP = Cfg::TPP, E = Cfg::E, PS = Cfg::PS;
-    constexpr int F = T::F, O = T::O;
-    __shared__ cx<R> buf[TY * PS];
-    __shared__ cx<R> tw[PZ];
+    constexpr int D = Cfg::D, L = Cfg::L, PZ = Cfg::PZ, PPW = Cfg::PPW, TY = Cfg::TY, NT = Cfg::NT, TPP = Cfg::TPP;
+    constexpr int E = Cfg::E, EI = Cfg::EI, PS = Cfg::PS, KT = Cfg::KT, CB = Cfg::CB, RB = (int)sizeof(R);
+    constexpr int F = T::F, O = T::O, NC = Cfg::NC, CHUNK = Cfg::CHUNK;
+    constexpr bool STAGE = Cfg::STAGE;
+    constexpr bool kPrefetch = Cfg::PREFETCH;
+    __shared__ cx<R> buf[Cfg::WAVES * PPW * PS];
+    __shared__ cx<R> tab[zt_size<SH>()];
+    __shared__ __attribute__((aligned(16))) char sspec[STAGE ? Cfg::WAVES * NC * CHUNK : 16];
     const int tid = threadIdx.x;
-    const int wave = tid / 64, lane = tid % 64;
-    const int kx = bx;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
+    const int r = D == 2 ? wave & 1 : 0;  // frequencies D k + r
     const int b = lane / TPP, t = lane % TPP;
-    const int ky = by * TY + wave * PPW + b;
-    const bool live = ky < a.py;
+    const int ky0 = by * TY + wave / D * PPW;  // the wavefront's first ky
+    const int ky = ky0 + b;
     cx<R> *pb = buf + (wave * PPW + b) * PS;
-    const cx<R> *twz = static_cast<const cx<R> *>(a.twz);
-    const R *spec = static_cast<const R *>(a.spec);
-    for (int i = tid; i < PZ; i += NT) tw[i] = twz[i];
+    zt_fill<R, SH>(tab, static_cast<const cx<R> *>(a.twz), tid, NT);
     __syncthreads();
     cx<R> acc[O][E];
 #pragma unroll
@@ -475,121 +546,176 @@ __device__ __forceinline__ void zpass_body(const ApplyArgs &a, const int bx, con
 #pragma unroll
         for (int e = 0; e < E; ++e) acc[o][e] = {R(0), R(0)};
 
-    // Row and spectrum addressing, hoisted out of the element loops: lane t
-    // holds z = t + e*TPP; elements e < E/2 lie in the lower half (kz < P/2,
-    // read straight from the octant), e >= E/2 in the upper half (kz >= P/2,
-    // read at P - kz with the z-reflection sign; kz = P/2 reads the Nyquist
-    // plane, where every z-odd spectrum is zero, so its sign is immaterial).
-    const int zoff = t - a.z0;
-    const int64_t estride = (int64_t)TPP * a.py;
+    // Lane t holds plane n = t + e TPP of the occupied planes, n < P/2 (a shift
+    // of all planes does not change a convolution, so the first occupied one
+    // is n = 0); planes past the last one lie past the tile's end and read as
+    // zero.
     const size_t fstride = (size_t)a.hx * a.nzo * a.py;
-    const cx<R> *Yl = static_cast<const cx<R> *>(a.Y) + (size_t)kx * a.nzo * a.py + (int64_t)zoff * a.py + ky;
-    const int kyp = ky < a.hy ? ky : a.py - ky;
-    const bool fy = ky >= a.hy;
-    const R *srow = spec + ((size_t)kx * a.hy + kyp) * a.hz;
-    const size_t cstride = (size_t)a.hx * a.hy * a.hz;
-
-    // Field f's rows into registers: occupied planes only (planes z >= P/2 are
-    // padding, the grid spans at most P/2 planes).  With nine fields (Navier)
-    // the next field's loads are issued before this field's transform.  They
-    // are branch-free -- a load from a valid address (Y's first element,
-    // written by the forward pass), times zero where the plane is not occupied
-    // -- so one field's loads sit in one block and the wait before a transform
-    // counts only that field's loads, not the next field's, in flight.  The
-    // four-field kinds, and FP64 below 384 points (registers near the limit),
-    // keep the plain conditional loads: there the extra registers cost more
-    // occupancy than the overlap gains (measured on the 128^3 Navier sphere:
-    // FP64 at 256 points 342 -> 541 us with it; FP32 195 -> 185 us).
-    constexpr bool kPrefetch = KIND == 2 && (sizeof(R) == 4 || PZ >= 384);
-    const cx<R> *Ybase = static_cast<const cx<R> *>(a.Y);
+    const cx<R> *Yt = static_cast<const cx<R> *>(a.Y) + ((size_t)kx * a.py + ky0 / KT * KT) * a.nzo;
+    const int yoff = (t * KT + ky0 % KT + b) * CB;
+    const int ybytes = a.nzo * KT * CB;
     auto load_field = [&](int f, cx<R> *x) {
-        const cx<R> *Yf = Yl + f * fstride;
+        const auto rs = buf_range(Yt + f * fstride, ybytes);
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const int zz = zoff + e * TPP;  // occupied plane index; others are zero
-            if (e >= E / 2) {
-                x[e] = cx<R>{R(0), R(0)};
-            } else if constexpr (kPrefetch) {
-                const bool ok = live && zz >= 0 && zz < a.nzo;
-                const cx<R> v = *(ok ? Yf + e * estride : Ybase);
-                const R mk = ok ? R(1) : R(0);  // a product, not a select: the load stays unconditional
-                x[e] = cx<R>{v.x * mk, v.y * mk};
-            } else {
-                x[e] = (live && zz >= 0 && zz < a.nzo) ? Yf[e * estride] : cx<R>{R(0), R(0)};
-            }
-        }
+        for (int e = 0; e < EI; ++e) x[e] = buf_load<R>(rs, yoff + e * (TPP * KT * CB));
     };
-    [[maybe_unused]] cx<R> xn[kPrefetch ? E : 1];
+    // Spectrum rows of the wavefront: those of ky, or reflected to Py - ky from
+    // Py/2 on (Py/2 itself has both names, and its spectra odd in y are zero,
+    // so its sign is immaterial) -- one run of rows either way, in reverse
+    // order when reflected.  Frequency D k + r of element k = t + e TPP sits
+    // at k for e < E/2 and, reflected to P - kz, at L - r - k above (P/2
+    // itself, k = L/2 of part 0, is read there too: its spectra odd in z are
+    // zero).
+    constexpr int HZ = PZ / 2 + 1, L0 = spec_len(D, 0, HZ), L1 = spec_len(D, 1, HZ);
+    const bool fy = 2 * ky0 >= a.py;
+    const int row0 = fy ? a.py - ky0 - (PPW - 1) : ky0, brow = fy ? PPW - 1 - b : b;
+    const int len = r ? L1 : L0;
+    const int lo = brow * len + t, hi = brow * len + (L - r - t) - (E - 1) * TPP;
+    auto spec_rows = [&](int c) {
+        const R *p = static_cast<const R *>(a.spec) + (size_t)(c * a.hx + kx) * a.hy * spec_row(D, HZ) +
+                     (r ? (size_t)a.hy * L0 : 0) + (size_t)row0 * len;
+        return buf_range(p, PPW * len * RB);
+    };
+    char *sw = sspec + (STAGE ? wave * NC * CHUNK : 0);
+    auto stage_spec = [&](auto fc) {  // the spectrum rows of field f into LDS
+        constexpr int f = decltype(fc)::value;
+        static_for<0, field_ncomp<KIND>(f)>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            const auto rs = spec_rows(field_comp<KIND>(f, i));
+#pragma unroll
+            for (int k = 0; k < CHUNK / 1024; ++k)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    rs, (__attribute__((address_space(3))) void *)(sw + i * CHUNK + k * 1024), 16, lane * 16 + k * 1024,
+                    0, 0, 0);
+        });
+    };
+
+    [[maybe_unused]] cx<R> xn[kPrefetch ? EI : 1];
     if constexpr (kPrefetch) load_field(0, xn);
     static_for<0, F>([&](auto fc) {
         constexpr int f = decltype(fc)::value;
+        // one field per scheduling region: without the barrier the scheduler
+        // starts every field's loads at once and runs out of registers
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (STAGE) {
+            stage_spec(fc);  // the previous field's rows have been used
+            __builtin_amdgcn_sched_barrier(0);  // and before the loads below, for the count of the wait
+        }
         cx<R> x[E];
         if constexpr (kPrefetch) {
 #pragma unroll
-            for (int e = 0; e < E; ++e) x[e] = xn[e];
-            if constexpr (f + 1 < F) load_field(f + 1, xn);  // next field in flight during this one
+            for (int e = 0; e < EI; ++e) x[e] = xn[e];
+            if constexpr (f + 1 < F) load_field(f + 1, xn);  // in flight during this field's transform
         } else {
             load_field(f, x);
         }
-        fft_regs_s<R, SH, -1>(x, pb, tw, t);
-        if (live) {
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const int kz = t + e * TPP;
-                const int kzp = e < E / 2 ? kz : PZ - kz;
-                static_for<0, T::N>([&](auto tc) {
-                    constexpr int term = decltype(tc)::value;
-                    if constexpr (T::f(term) == f) {
-                        constexpr int c = T::c(term);
-                        constexpr int mask = comp_oddmask(KIND, c);
-                        const R sv = srow[c * cstride + kzp];
-                        const bool flip = (fy && (mask & 2)) != ((e >= E / 2) && (mask & 4));
-                        mac<R>(acc[T::o(term)][e], x[e], flip ? -sv : sv, comp_imag(KIND, c));
-                    }
-                });
-            }
+        for (int e = EI; e < E; ++e) x[e] = {R(0), R(0)};
+        if (D == 2 && r) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) x[e] = cmul(x[e], tab[t + e * TPP]);
         }
+        z_fft<R, SH, -1>(x, pb, tab, t);
+        if constexpr (STAGE) {
+            // the staged rows have arrived: only the loads issued after them
+            // (the next field's) may be outstanding
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kPrefetch && f + 1 < F ? EI : 0) : "memory");
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        static_for<0, T::N>([&](auto tc) {
+            constexpr int term = decltype(tc)::value;
+            if constexpr (T::f(term) == f) {
+                constexpr int c = T::c(term), slot = term_slot<KIND>(term);
+                constexpr int mask = comp_oddmask(KIND, c);
+                const R *sp = reinterpret_cast<const R *>(sw + slot * CHUNK);
+                const auto rs = spec_rows(c);
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const int k = e < E / 2 ? lo + e * TPP : hi + (E - 1 - e) * TPP;
+                    const R sv = STAGE ? sp[k] : buf_load_real<R>(rs, k * RB);
+                    const bool flip = (fy && (mask & 2)) != ((e >= E / 2) && (mask & 4));
+                    mac<R>(acc[T::o(term)][e], x[e], flip ? -sv : sv, comp_imag(KIND, c));
+                }
+            }
+        });
+        // the sums are formed here, not sunk past the next field's branch
+        // (which would keep every field's values live)
+#pragma unroll
+        for (int o = 0; o < O; ++o)
+#pragma unroll
+            for (int e = 0; e < E; ++e) asm volatile("" : "+v"(acc[o][e].x), "+v"(acc[o][e].y));
     });
 
+    __builtin_amdgcn_sched_barrier(0);
+    const size_t slab = (size_t)a.nzo * a.py;
+    const int zbytes = (int)(slab * CB);
+    const int zoff = (t * a.py + ky) * CB, zstep = TPP * a.py * CB;
+    auto slot = [](int i) { return i + (i >> SH::SHIFT); };
 #pragma unroll
     for (int o = 0; o < O; ++o) {
-        fft_regs_s<R, SH, 1>(acc[o], pb, tw, t);
-        if (live) {
-            cx<R> *Zl = static_cast<cx<R> *>(a.Z) + (size_t)(o * a.hx + kx) * a.nzo * a.py + (int64_t)zoff * a.py + ky;
+        if (D == 2 && o > 0) __syncthreads();  // the other wavefront has read this one's half
+        z_fft<R, SH, 1>(acc[o], pb, tab, t);
+        const auto rs = buf_range(static_cast<const cx<R> *>(a.Z) + (size_t)(o * a.hx + kx) * slab, zbytes);
+        if constexpr (D == 1) {
 #pragma unroll
-            for (int e = 0; e < E / 2; ++e) {  // outputs z >= P/2 are never needed
-                const int zz = zoff + e * TPP;
-                if (zz >= 0 && zz < a.nzo) Zl[e * estride] = acc[o][e];
+            for (int e = 0; e < E / 2; ++e) buf_store<R>(acc[o][e], rs, zoff + e * zstep);
+        } else {
+            // the even wavefront stores e < E/2, the odd one the rest
+            const cx<R> *pother = buf + ((wave ^ 1) * PPW + b) * PS;
+            if (r) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) acc[o][e] = cmulc(acc[o][e], tab[t + e * TPP]);
+            }
+            wave_lds_sync();
+            if (r) {
+#pragma unroll
+                for (int e = 0; e < E / 2; ++e) pb[slot(t + e * TPP)] = acc[o][e];
+            } else {
+#pragma unroll
+                for (int e = E / 2; e < E; ++e) pb[slot(t + e * TPP)] = acc[o][e];
+            }
+            __syncthreads();
+            if (r) {
+#pragma unroll
+                for (int e = E / 2; e < E; ++e)
+                    buf_store<R>(cadd(pother[slot(t + e * TPP)], acc[o][e]), rs, zoff + e * zstep);
+            } else {
+#pragma unroll
+                for (int e = 0; e < E / 2; ++e)
+                    buf_store<R>(cadd(acc[o][e], pother[slot(t + e * TPP)]), rs, zoff + e * zstep);
             }
         }
     }
+#endif
 }
 
-// One-dimensional grid of 8 * ceil(hx * nby / 8) blocks.  Blocks go to the
-// 8 XCDs round-robin, so block b runs on XCD b % 8; each XCD is given one
-// contiguous run of (kx, ky-block) work items, ordered so that the blocks of
-// one kx and their mirrored ky blocks (which read the same octant rows of
-// the spectra) follow each other on the same L2.
+// (kx, ky-block) items, ordered so that the blocks of one kx and their
+// mirrored ky blocks (which read the same octant rows of the spectra) follow
+// each other on the same L2.
 template <typename R, typename SH, int KIND>
-__global__ __launch_bounds__((ZCfg<R, SH, KIND>::NT)) void k_zpass(ApplyArgs a, int nby) {
-    const int total = a.hx * nby;
-    const int per = (total + 7) / 8;
-    const int lam = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
-    if (lam >= total) return;
+__device__ __forceinline__ void zpass_item(const ApplyArgs &a, const int b, const int nby) {
+    const int lam = xcd_item(b, a.hx * nby);
+    if (lam < 0) return;
     const int kx = lam / nby, j = lam % nby;
     const int by = (j & 1) ? nby - 1 - (j >> 1) : (j >> 1);
-    zpass_body<R, SH, KIND>(a, kx, by, 0);
+    zpass_body<R, SH, KIND>(a, kx, by);
 }
 
-// Batched form: blockIdx.z = member * zdiv + the kernel's own z index.
+// At least two wavefronts per SIMD: FP64 Navier would take a few registers
+// more than the 256 that allow them.
 template <typename R, typename SH, int KIND>
-__global__ __launch_bounds__((ZCfg<R, SH, KIND>::NT)) void kb_zpass(const ApplyArgs *members, const BatchIO *io, int zdiv) {
-    ApplyArgs a = members[blockIdx.z / zdiv];
+__global__ __launch_bounds__((ZCfg<R, SH, KIND>::NT), 2) void k_zpass(ApplyArgs a, int nby) {
+    zpass_item<R, SH, KIND>(a, blockIdx.x, nby);
+}
+
+// Batched form: blockIdx.z = member.
+template <typename R, typename SH, int KIND>
+__global__ __launch_bounds__((ZCfg<R, SH, KIND>::NT), 2) void kb_zpass(const ApplyArgs *members, const BatchIO *io,
+                                                                     int nby) {
+    const ApplyArgs &a = members[blockIdx.z];
     if (io->active && !io->active[a.gid]) return;
-    a.q = io->q + a.off;
-    a.u = io->u + a.off;
-    a.r = io->r + a.off;
-    zpass_body<R, SH, KIND>(a, blockIdx.x, blockIdx.y, blockIdx.z % zdiv);
+    zpass_item<R, SH, KIND>(a, blockIdx.x, nby);
 }
 
 // 2D: the third axis has length 1, so the "z pass" is the spectral product.
@@ -610,7 +736,7 @@ __device__ __forceinline__ void mac2d_body(const ApplyArgs &a, const int bx, con
         constexpr int term = decltype(tc)::value;
         constexpr int c = T::c(term), o = T::o(term), f = T::f(term);
         const cx<R> v = Y[(size_t)(f * a.hx + kx) * a.py + ky];
-        mac<R>(acc[o], v, spec_at<R, KIND>(spec, a, c, kx, ky, 0), comp_imag(KIND, c));
+        mac<R>(acc[o], v, spec_at<R, KIND>(spec, a, c, kx, ky), comp_imag(KIND, c));
     });
 #pragma unroll
     for (int o = 0; o < O; ++o) Z[(size_t)(o * a.hx + kx) * a.py + ky] = acc[o];
@@ -907,7 +1033,7 @@ __global__ __launch_bounds__(256) void kb_gather(const ApplyArgs *members, const
 template <typename R, int PY, int KIND, typename YS = cx<R>>
 int launch_fwd(const ApplyArgs &a, hipStream_t st) {
     using Cfg = FwdCfg<R, PY, KIND>;
-    dim3 grid(a.nzo, (a.hx + Cfg::KXC - 1) / Cfg::KXC);
+    dim3 grid(8 * (((a.hx + Cfg::KXC - 1) / Cfg::KXC * a.nzo + 7) / 8));  // xcd_item
     if (a.fwd_xg == 2) hipLaunchKernelGGL((k_fwd_xy<R, PY, KIND, 2, YS>), grid, dim3(Cfg::NT), 0, st, a);
     else hipLaunchKernelGGL((k_fwd_xy<R, PY, KIND, 1, YS>), grid, dim3(Cfg::NT), 0, st, a);
     BF_HIP(hipGetLastError());
@@ -927,10 +1053,14 @@ int launch_z(const ApplyArgs &a, hipStream_t st) {
         dim3 grid(a.hx, (a.py + 255) / 256);
         hipLaunchKernelGGL((k_mac2d<R, KIND>), grid, dim3(256), 0, st, a);
     } else {
-        using SH = Sched<PZ, SCHED>;
+        using SH = ZSched<R, KIND, PZ, SCHED>;
         using Cfg = ZCfg<R, SH, KIND>;
-        const int nby = (a.py + Cfg::TY - 1) / Cfg::TY;
-        const int per = (a.hx * nby + 7) / 8;
+        if (a.py % Cfg::TY != 0 || 2 * a.nzo > PZ + 1) {
+            set_error("z pass: y length or planes do not fit the schedule");
+            return BEMFFT_EUNSUPPORTED;
+        }
+        const int nby = a.py / Cfg::TY;
+        const int per = (a.hx * nby + 7) / 8;  // xcd_item
         hipLaunchKernelGGL((k_zpass<R, SH, KIND>), dim3(8 * per), dim3(Cfg::NT), 0, st, a, nby);
     }
     BF_HIP(hipGetLastError());
@@ -993,7 +1123,7 @@ struct Launch {
         return launch_inv_y<R, P, KIND>(a, all_rows, st);
     }
     template <int P> static int z(const ApplyArgs &a, hipStream_t st) {
-        if constexpr (KIND == 2 && has_wide_sched(P)) {
+        if constexpr (KIND == 2) {
             if (a.zsched == 2) return launch_z<R, P, KIND, 2>(a, st);
         }
         return a.zsched == 1 ? launch_z<R, P, KIND, 1>(a, st) : launch_z<R, P, KIND, 0>(a, st);
@@ -1006,7 +1136,7 @@ struct Launch {
         if (a.nd > 0) {
             BF_CHECK(dispatch_rows(a, st));  // fields and long-row transforms, one launch
         } else {
-            hipLaunchKernelGGL((k_fields<R, KIND>), dim3((a.m + 255) / 256), dim3(256), 0, st, a);
+            BF_CHECK(fields(a, st));
         }
         BF_CHECK(dispatch_fwd(a, st));
         if (ev) BF_HIP(hipEventRecord(ev[1], st));
@@ -1021,10 +1151,19 @@ struct Launch {
         BF_CHECK(dispatch_inv_y(a, 0, st));
         if (ev) BF_HIP(hipEventRecord(ev[3], st));
         if (a.nd > 0 && a.row_inv) BF_CHECK(dispatch_rows_inv(a, st));
+        BF_CHECK(gather(a, st));
+        if (ev) BF_HIP(hipEventRecord(ev[4], st));
+        return 0;
+    }
+    static int fields(const ApplyArgs &a, hipStream_t st) {
+        hipLaunchKernelGGL((k_fields<R, KIND>), dim3((a.m + 255) / 256), dim3(256), 0, st, a);
+        BF_HIP(hipGetLastError());
+        return 0;
+    }
+    static int gather(const ApplyArgs &a, hipStream_t st) {
         constexpr int NPB = 256 / kGatherLanes;  // nodes per block
         hipLaunchKernelGGL((k_gather<R, KIND>), dim3((a.m + NPB - 1) / NPB), dim3(256), 0, st, a);
         BF_HIP(hipGetLastError());
-        if (ev) BF_HIP(hipEventRecord(ev[4], st));
         return 0;
     }
     static int dispatch_fwd(const ApplyArgs &a, hipStream_t st) {
@@ -1035,8 +1174,8 @@ struct Launch {
     // ---- batched: one launch per stage for all members of a group
     template <int P> static int bfwd(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, hipStream_t st) {
         using Cfg = FwdCfg<R, P, KIND>;
-        dim3 grid((g.hx + Cfg::KXC - 1) / Cfg::KXC, g.max_nzo, g.nmem);
-        hipLaunchKernelGGL((kb_fwd_xy<R, P, KIND>), grid, dim3(Cfg::NT), 0, st, dm, io, 1);
+        dim3 grid(8 * (((g.hx + Cfg::KXC - 1) / Cfg::KXC * g.max_nzo + 7) / 8), 1, g.nmem);
+        hipLaunchKernelGGL((kb_fwd_xy<R, P, KIND>), grid, dim3(Cfg::NT), 0, st, dm, io);
         BF_HIP(hipGetLastError());
         return 0;
     }
@@ -1060,16 +1199,17 @@ struct Launch {
             dim3 grid(g.hx, (g.py + 255) / 256, g.nmem);
             hipLaunchKernelGGL((kb_mac2d<R, KIND>), grid, dim3(256), 0, st, dm, io, 1);
         } else {
-            using SH = Sched<PZ, SCHED>;
+            using SH = ZSched<R, KIND, PZ, SCHED>;
             using Cfg = ZCfg<R, SH, KIND>;
-            dim3 grid(g.hx, (g.py + Cfg::TY - 1) / Cfg::TY, g.nmem);
-            hipLaunchKernelGGL((kb_zpass<R, SH, KIND>), grid, dim3(Cfg::NT), 0, st, dm, io, 1);
+            const int nby = g.py / Cfg::TY;
+            dim3 grid(8 * ((g.hx * nby + 7) / 8), 1, g.nmem);
+            hipLaunchKernelGGL((kb_zpass<R, SH, KIND>), grid, dim3(Cfg::NT), 0, st, dm, io, nby);
         }
         BF_HIP(hipGetLastError());
         return 0;
     }
     template <int P> static int bz(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, hipStream_t st) {
-        if constexpr (KIND == 2 && has_wide_sched(P)) {
+        if constexpr (KIND == 2) {
             if (g.zsched == 2) return bz_s<P, 2>(dm, io, g, st);
         }
         return g.zsched == 1 ? bz_s<P, 1>(dm, io, g, st) : bz_s<P, 0>(dm, io, g, st);
@@ -1203,6 +1343,14 @@ template <int KIND>
 int apply_kind(int precision, const ApplyArgs &a, hipStream_t st, hipEvent_t *ev);
 template <int KIND>
 int apply_batch_kind(int precision, const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, hipStream_t st);
+
+// The same for one precision, each in a source file of its own.
+template <int KIND, int PREC>
+int apply_prec(const ApplyArgs &a, hipStream_t st, hipEvent_t *ev);
+template <int KIND, int PREC>
+int apply_batch_prec(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, hipStream_t st);
+template <int KIND, int PREC>
+int volume_prec(const ApplyArgs &a, double *out, hipStream_t st, hipEvent_t *ev);
 
 // Apply arguments of plan p with the spectra/tables of 'shared' and the
 // intermediate buffers of 'ws' (q, u, r left null).

@@ -173,22 +173,24 @@ struct DFT<4, DIR, R> {
     }
 };
 
-// Prime 5: direct sum with constant twiddles.
+// Prime 5: the conjugate-symmetric pairs share their products (36 operations
+// against 96 for the direct sum; the 320-point z pass is bound by them).
 template <int DIR, typename R>
 struct DFT<5, DIR, R> {
     __device__ static __forceinline__ void run(cx<R> (&v)[5]) {
-        cx<R> out[5];
-        static_for<0, 5>([&](auto kk) {
-            constexpr int k = decltype(kk)::value;
-            cx<R> acc = v[0];
-            static_for<1, 5>([&](auto ss) {
-                constexpr int s = decltype(ss)::value;
-                acc = cadd(acc, twc<(long)s * k, 5, DIR, R>(v[s]));
-            });
-            out[k] = acc;
-        });
-#pragma unroll
-        for (int k = 0; k < 5; ++k) v[k] = out[k];
+        constexpr ctrig::CS w1 = ctrig::cs2pi(1, 5), w2 = ctrig::cs2pi(2, 5);
+        constexpr R c1 = R(w1.c), c2 = R(w2.c), s1 = R(DIR * w1.s), s2 = R(DIR * w2.s);
+        const cx<R> t1 = cadd(v[1], v[4]), t2 = cadd(v[2], v[3]);
+        const cx<R> d1 = csub(v[1], v[4]), d2 = csub(v[2], v[3]);
+        const cx<R> m1 = {v[0].x + c1 * t1.x + c2 * t2.x, v[0].y + c1 * t1.y + c2 * t2.y};
+        const cx<R> m2 = {v[0].x + c2 * t1.x + c1 * t2.x, v[0].y + c2 * t1.y + c1 * t2.y};
+        const cx<R> n1 = {s1 * d1.x + s2 * d2.x, s1 * d1.y + s2 * d2.y};
+        const cx<R> n2 = {s2 * d1.x - s1 * d2.x, s2 * d1.y - s1 * d2.y};
+        v[0] = {v[0].x + t1.x + t2.x, v[0].y + t1.y + t2.y};
+        v[1] = {m1.x - n1.y, m1.y + n1.x};  // m1 + i n1
+        v[4] = {m1.x + n1.y, m1.y - n1.x};
+        v[2] = {m2.x - n2.y, m2.y + n2.x};
+        v[3] = {m2.x + n2.y, m2.y - n2.x};
     }
 };
 
@@ -223,8 +225,10 @@ struct DFTSplit {
 
 template <int DIR, typename R> struct DFT<6, DIR, R> : DFTSplit<6, 2, 3, DIR, R> {};
 template <int DIR, typename R> struct DFT<8, DIR, R> : DFTSplit<8, 2, 4, DIR, R> {};
+template <int DIR, typename R> struct DFT<10, DIR, R> : DFTSplit<10, 2, 5, DIR, R> {};
 template <int DIR, typename R> struct DFT<12, DIR, R> : DFTSplit<12, 3, 4, DIR, R> {};
 template <int DIR, typename R> struct DFT<16, DIR, R> : DFTSplit<16, 4, 4, DIR, R> {};
+template <int DIR, typename R> struct DFT<24, DIR, R> : DFTSplit<24, 4, 6, DIR, R> {};
 template <int DIR, typename R> struct DFT<20, DIR, R> : DFTSplit<20, 4, 5, DIR, R> {};
 
 // ------------------------------------------------------------ pencil plans
@@ -242,44 +246,24 @@ struct FFTShape {
     using rad = Radices<Rs...>;
 };
 
-// Two compiled schedules per length (S = 0 default, S = 1 alternative), and
-// for three lengths a wide one (S = 2: one pencil per wavefront, 64 lanes,
-// so a lane holds P/64 values -- for the z pass of the Navier family, whose
-// three FP64 output accumulators do not fit in registers at 16 or 32 lanes
-// per pencil); the plan's autotuner picks one for the z pass by timing them.
-template <int P, int S>
+// Schedule of the x, y and plan-time transforms of length P.
+template <int P>
 struct Sched;
-template <> struct Sched<1, 0> : FFTShape<1, 1> {};
-template <> struct Sched<32, 0> : FFTShape<32, 4, 4, 8> {};
-template <> struct Sched<32, 1> : FFTShape<32, 4, 8, 4> {};
-template <> struct Sched<64, 0> : FFTShape<64, 8, 8, 8> {};
-template <> struct Sched<64, 1> : FFTShape<64, 4, 16, 4> {};
-template <> struct Sched<96, 0> : FFTShape<96, 8, 4, 4, 6> {};
-template <> struct Sched<96, 1> : FFTShape<96, 8, 6, 4, 4> {};
-template <> struct Sched<128, 0> : FFTShape<128, 8, 16, 8> {};
-template <> struct Sched<128, 1> : FFTShape<128, 16, 8, 4, 4> {};
-template <> struct Sched<192, 0> : FFTShape<192, 16, 4, 4, 12> {};
-template <> struct Sched<192, 1> : FFTShape<192, 16, 12, 4, 4> {};
-template <> struct Sched<256, 0> : FFTShape<256, 16, 16, 16> {};
-template <> struct Sched<256, 1> : FFTShape<256, 32, 8, 8, 4> {};
-template <> struct Sched<320, 0> : FFTShape<320, 16, 4, 4, 20> {};
-template <> struct Sched<320, 1> : FFTShape<320, 16, 20, 4, 4> {};
-template <> struct Sched<384, 0> : FFTShape<384, 16, 8, 6, 8> {};
-template <> struct Sched<384, 1> : FFTShape<384, 32, 4, 4, 4, 6> {};
-template <> struct Sched<512, 0> : FFTShape<512, 32, 8, 8, 8> {};
-template <> struct Sched<512, 1> : FFTShape<512, 32, 16, 4, 8> {};
+template <> struct Sched<1> : FFTShape<1, 1> {};
+template <> struct Sched<32> : FFTShape<32, 4, 4, 8> {};
+template <> struct Sched<64> : FFTShape<64, 8, 8, 8> {};
+template <> struct Sched<96> : FFTShape<96, 8, 4, 4, 6> {};
+template <> struct Sched<128> : FFTShape<128, 8, 16, 8> {};
+template <> struct Sched<192> : FFTShape<192, 16, 4, 4, 12> {};
+template <> struct Sched<256> : FFTShape<256, 16, 16, 16> {};
+template <> struct Sched<320> : FFTShape<320, 16, 4, 4, 20> {};
+template <> struct Sched<384> : FFTShape<384, 16, 8, 6, 8> {};
+template <> struct Sched<512> : FFTShape<512, 32, 8, 8, 8> {};
 // 1024 points: 2D plans only (grids of up to 512 points per axis)
-template <> struct Sched<1024, 0> : FFTShape<1024, 64, 16, 16, 4> {};
-template <> struct Sched<1024, 1> : FFTShape<1024, 64, 4, 16, 16> {};
-template <> struct Sched<256, 2> : FFTShape<256, 64, 4, 4, 4, 4> {};
-template <> struct Sched<384, 2> : FFTShape<384, 64, 6, 2, 2, 2, 2, 2, 2> {};
-template <> struct Sched<512, 2> : FFTShape<512, 64, 8, 8, 8> {};
-
-// Lengths with a wide schedule.
-__host__ __device__ constexpr bool has_wide_sched(int p) { return p == 256 || p == 384 || p == 512; }
+template <> struct Sched<1024> : FFTShape<1024, 64, 16, 16, 4> {};
 
 template <int P>
-using PencilShape = Sched<P, 0>;
+using PencilShape = Sched<P>;
 
 // Lanes of one pencil always sit in one wavefront, so the exchanges inside a
 // transform only need the wave's LDS accesses to stay in program order (LDS

@@ -54,8 +54,9 @@ struct Engine {
     int precision = BEMFFT_FP64;  // BEMFFT_FP64, BEMFFT_FP32 or BEMFFT_BF16_MFMA
     size_t creal = 8;             // bytes per real of the arithmetic (twiddles, fields, rows)
     size_t sreal = 8;             // bytes per real of the stored Y, Z and spectra
-    int64_t hzs = 1;              // stored length of a spectrum's kz row (>= Hz)
-    void *spec = nullptr;         // [K][Hx][Hy][hzs] reals (sreal bytes each)
+    int64_t hzs = 1;              // stored values per (c, kx, ky) spectrum row (>= Hz)
+    int zsched = 0;               // radix schedule of the z pass at this precision
+    void *spec = nullptr;         // K Hx Hy hzs reals (sreal bytes each), order of spec_index
     void *twx = nullptr;          // [Px] complex, exp(-2 pi i t / Px)
     void *twy = nullptr;          // [Py]
     void *twz = nullptr;          // [Pz]
@@ -73,7 +74,8 @@ struct bemfft_plan {
     int ncomp = 1, F = 0, K = 0, O = 0;
     int64_t m = 0;
     int64_t n[3] = {1, 1, 1};
-    int64_t P[3] = {1, 1, 1};
+    int64_t pad[3] = {1, 1, 1};   // padded lengths asked for (or picked for the grid)
+    int64_t P[3] = {1, 1, 1};     // lengths in use: pad, or shorter along z (occupied planes only)
     int64_t H[3] = {1, 1, 1};
     int64_t z0 = 0, nzo = 1;
     int *d_row_dense = nullptr;   // [nzo * ny] long-row index or -1
@@ -98,7 +100,7 @@ struct bemfft_plan {
     std::vector<double> h_diag_dir, h_diag_neu;  // Jacobi entries per slot
     std::vector<double> h_self;  // exact single-layer self blocks, caller order (m or 9 m)
     double parity_resid = 0.0;
-    int zsched = 0;               // radix schedule of the z transform
+    int zsched = 0;               // radix schedule of the working engine's z transform
     int cell_quad = 0;            // kernel values at m != 0: 0 point, q >= 2 cell mean (q^dim points)
     double tune_us[3] = {0, 0, 0};
     double fwd_tune_us[2] = {0, 0};  // autotune: apply time with 1 and 2 kx per forward thread, us
@@ -118,10 +120,10 @@ namespace bemfft {
 // Apply-stage launchers (apply.hip).
 int launch_apply(bemfft_plan *p, const Engine &e, const double *q, const double *u, double *r,
                  hipStream_t st, hipEvent_t *ev = nullptr);
-// Spectrum precompute (spectra.hip): fills e64 (FP64) and, if e32 is
-// non-null, its rounded FP32 copy.
-int build_spectra(bemfft_plan *p, Engine *e64, Engine *e32, hipStream_t st);
-int convert_spectra(const double *in, Engine *e, int64_t rows, int64_t hz, hipStream_t st);
+// Spectrum precompute (spectra.hip): fills e64 (FP64); convert_spectra
+// rounds it into the working engine.
+int build_spectra(bemfft_plan *p, Engine *e64, hipStream_t st);
+int convert_spectra(const bemfft_plan *p, const Engine &e64, Engine *e, hipStream_t st);
 int fft3d_c2c_f64(double *data, int64_t px, int64_t py, int64_t pz, int dir, hipStream_t st);
 bool fft_size_supported(int64_t n);
 int upload_twiddles(Engine *e, const bemfft_plan *p);

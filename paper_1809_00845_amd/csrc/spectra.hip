@@ -21,6 +21,7 @@
 #include "fft_device.hpp"
 #include "internal.hpp"
 #include "kinds.hpp"
+#include "zsched.hpp"
 
 namespace bemfft {
 
@@ -253,13 +254,13 @@ __device__ void atomic_max_pos(unsigned long long *dst, double v) {
     atomicMax(dst, (unsigned long long)__double_as_longlong(v));
 }
 
-// One octant of the real (or imaginary) part: out[kx][ky][kz] from
-// full[kz][ky][kx], through a 32 x 32 (kz, kx) LDS tile per block so that the
+// One octant of the real (or imaginary) part, in the order of spec_index (out:
+// this component's values) from full[kz][ky][kx], through a 32 x 32 (kz, kx) LDS tile per block so that the
 // reads run along kx and the writes along kz.  The largest kept and
 // discarded magnitudes are reduced in the block and merged with one atomic
 // per block.  Grid: (ceil(hx/32), ceil(hz/32), hy), 256 threads.
 __global__ __launch_bounds__(256) void k_extract(const cx<double> *full, double *out, int64_t px, int64_t py,
-                                                 int64_t hx, int64_t hy, int64_t hz, int imag,
+                                                 int64_t hx, int64_t hy, int64_t hz, int imag, int split,
                                                  unsigned long long *stats) {
     __shared__ double tile[32][33];
     __shared__ double red[2][4];
@@ -282,7 +283,7 @@ __global__ __launch_bounds__(256) void k_extract(const cx<double> *full, double 
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int64_t kx = kx0 + ty + 8 * i, kz = kz0 + tx;
-        if (kx < hx && kz < hz) out[(kx * hy + ky) * hz + kz] = tile[tx][ty + 8 * i];
+        if (kx < hx && kz < hz) out[spec_index(split, 0, (int)hx, (int)hy, (int)hz, (int)kx, (int)ky, (int)kz)] = tile[tx][ty + 8 * i];
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
@@ -300,21 +301,34 @@ __global__ __launch_bounds__(256) void k_extract(const cx<double> *full, double 
     }
 }
 
-__global__ void k_to_f32(const double *in, float *out, int64_t n) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        out[i] = (float)in[i];
+// FP64 spectra in the order of spec_index with split din -> FP32 with split
+// dout (the same element for element when they are equal).
+__global__ void k_to_f32(const double *in, float *out, int64_t rows, int hx, int hy, int hz, int din, int dout) {
+    const int64_t n = rows * (din == dout ? spec_row(dout, hz) : hz);
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        if (din == dout) {
+            out[i] = (float)in[i];
+        } else {
+            const int64_t r = i / hz;
+            const int kz = (int)(i % hz), ky = (int)(r % hy), kx = (int)((r / hy) % hx), c = (int)(r / hy / hx);
+            out[spec_index(dout, c, hx, hy, hz, kx, ky, kz)] = (float)in[spec_index(din, c, hx, hy, hz, kx, ky, kz)];
+        }
+    }
 }
 
 // BF16 bit pattern of v: rounded to FP32, then to 8 significant bits, round
-// to nearest, ties to even (v finite).  Rows of hz values are stored at a
-// stride of hzs (>= hz), zero beyond hz.
-__global__ void k_to_bf16_rows(const double *in, uint16_t *out, int64_t rows, int64_t hz, int64_t hzs) {
+// to nearest, ties to even (v finite).  The octant in the order of spec_index
+// becomes rows [c][kx][ky] of hz values at a stride of hzs (>= hz), zero
+// beyond hz.
+__global__ void k_to_bf16_rows(const double *in, uint16_t *out, int64_t rows, int hx, int hy, int hz, int hzs,
+                               int split) {
     const int64_t n = rows * hzs;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = i / hzs, k = i % hzs;
+        const int64_t r = i / hzs;
+        const int k = (int)(i % hzs), ky = (int)(r % hy), kx = (int)((r / hy) % hx), c = (int)(r / hy / hx);
         uint16_t b = 0;
         if (k < hz) {
-            unsigned u = __float_as_uint((float)in[r * hz + k]);
+            unsigned u = __float_as_uint((float)in[spec_index(split, c, hx, hy, hz, kx, ky, k)]);
             u += 0x7fffu + ((u >> 16) & 1u);
             b = (uint16_t)(u >> 16);
         }
@@ -345,16 +359,21 @@ int fft3d_c2c_f64(double *data, int64_t px, int64_t py, int64_t pz, int dir, hip
     return 0;
 }
 
-// The FP64 spectra rounded once to the working engine's stored precision,
-// on the device: FP32 contiguous, or BF16 rows of hz values at stride hzs.
-int convert_spectra(const double *in, Engine *e, int64_t rows, int64_t hz, hipStream_t st) {
-    const int64_t n = rows * (e->precision == BEMFFT_BF16_MFMA ? e->hzs : hz);
+// The FP64 spectra e64 rounded once to the working engine's stored precision,
+// on the device: FP32 in the same order, or BF16 rows at stride hzs.
+int convert_spectra(const bemfft_plan *p, const Engine &e64, Engine *e, hipStream_t st) {
+    const int64_t rows = (int64_t)p->K * p->H[0] * p->H[1];
+    const int64_t n = rows * e->hzs;
     const int blocks = (int)std::min<int64_t>((n + 255) / 256, 65536);
+    const double *in = static_cast<const double *>(e64.spec);
+    const int hx = (int)p->H[0], hy = (int)p->H[1], hz = (int)p->H[2];
+    const int d64 = z_split(p->kernel, true, p->P[2]);
     if (e->precision == BEMFFT_FP32)
-        hipLaunchKernelGGL(k_to_f32, dim3(blocks), dim3(256), 0, st, in, static_cast<float *>(e->spec), n);
+        hipLaunchKernelGGL(k_to_f32, dim3(blocks), dim3(256), 0, st, in, static_cast<float *>(e->spec), rows, hx, hy,
+                           hz, d64, z_split(p->kernel, false, p->P[2]));
     else
         hipLaunchKernelGGL(k_to_bf16_rows, dim3(blocks), dim3(256), 0, st, in, static_cast<uint16_t *>(e->spec), rows,
-                           hz, e->hzs);
+                           hx, hy, hz, (int)e->hzs, d64);
     if (hipGetLastError() != hipSuccess) {
         set_error("spectrum conversion failed");
         return BEMFFT_EDEVICE;
@@ -362,11 +381,11 @@ int convert_spectra(const double *in, Engine *e, int64_t rows, int64_t hz, hipSt
     return 0;
 }
 
-int build_spectra(bemfft_plan *p, Engine *e64, Engine *e32, hipStream_t st) {
+int build_spectra(bemfft_plan *p, Engine *e64, hipStream_t st) {
     const int64_t px = p->P[0], py = p->P[1], pz = p->P[2];
     const int64_t hx = p->H[0], hy = p->H[1], hz = p->H[2];
     const int64_t full_n = px * py * pz;
-    const int64_t oct = hx * hy * hz;
+    const int64_t oct = hx * hy * e64->hzs;
     cx<double> *full = nullptr;
     unsigned long long *stats = nullptr;
     BF_HIP(hipMalloc(&full, full_n * sizeof(cx<double>)));
@@ -391,7 +410,7 @@ int build_spectra(bemfft_plan *p, Engine *e64, Engine *e32, hipStream_t st) {
         double *dst = static_cast<double *>(e64->spec) + (int64_t)c * oct;
         const dim3 eg((unsigned)((hx + 31) / 32), (unsigned)((hz + 31) / 32), (unsigned)hy);
         hipLaunchKernelGGL(k_extract, eg, dim3(256), 0, st, full, dst, px, py, hx, hy, hz,
-                           comp_imag(p->kernel, c) ? 1 : 0, stats);
+                           comp_imag(p->kernel, c) ? 1 : 0, z_split(p->kernel, true, pz), stats);
         unsigned long long hs[2];
         if (hipMemcpyAsync(hs, stats, sizeof(hs), hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipStreamSynchronize(st) != hipSuccess) { status = BEMFFT_EDEVICE; break; }
@@ -399,13 +418,6 @@ int build_spectra(bemfft_plan *p, Engine *e64, Engine *e32, hipStream_t st) {
         std::memcpy(&kept, &hs[0], 8);
         std::memcpy(&disc, &hs[1], 8);
         if (kept > 0.0) worst = std::max(worst, disc / kept);
-    }
-    if (status == 0 && e32) {
-        int64_t n = (int64_t)p->K * oct;
-        int eb = (int)std::min<int64_t>((n + 255) / 256, 65536);
-        hipLaunchKernelGGL(k_to_f32, dim3(eb), dim3(256), 0, st, static_cast<const double *>(e64->spec),
-                           static_cast<float *>(e32->spec), n);
-        if (hipGetLastError() != hipSuccess) status = BEMFFT_EDEVICE;
     }
     if (hipStreamSynchronize(st) != hipSuccess && status == 0) status = BEMFFT_EDEVICE;
     (void)hipFree(full);

@@ -1,0 +1,109 @@
+"""The z pass on every padded length, family, precision and schedule, with the
+occupied planes at their limits, against the CPU oracle (plan lengths: a body
+that does not fill its box is transformed at a shorter length than the grid's
+unless the caller fixed the length).
+
+Bars: those of the apply, 1e-12 (FP64) and 2e-5 (FP32) of the term scale.
+"""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle as O  # noqa: E402
+from paper_1809_00845_amd import binding as B  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+TOL = {B.FP64: 1e-12, B.FP32: 2e-5}
+KIND = {B.LAPLACE3D: O.LAPLACE3D, B.NAVIER3D: O.NAVIER3D}
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    B.load()
+    return torch.device("cuda:0")
+
+
+class _Nodes:
+    """m random nodes of an (nx, ny, nz) grid on the planes [lo, hi], both occupied."""
+
+    def __init__(self, n, lo, hi, m=60, seed=0):
+        rng = np.random.default_rng(seed)
+        z = rng.integers(lo, hi + 1, m)
+        z[0], z[1] = lo, hi
+        gi = np.stack([rng.integers(0, n[0], m), rng.integers(0, n[1], m), z], 1)
+        self.dim, self.n, self.h, self.origin = 3, n, 1.0 / max(n), (0.0, 0.0, 0.0)
+        self.nodes = gi * self.h
+        nv = rng.normal(size=(m, 3))
+        self.normals = nv / np.linalg.norm(nv, axis=1, keepdims=True)
+        self.weights = rng.uniform(0.2, 1.5, m) * self.h ** 2
+
+
+def _check(dev, g, kernel, prec, **kw):
+    nc = 3 if kernel == B.NAVIER3D else 1
+    m = len(g.weights)
+    rng = np.random.default_rng(7)
+    q, u = rng.uniform(-1, 1, (nc, m)), rng.uniform(-1, 1, (nc, m))
+    plan = B.Plan(g, kernel, precision=prec, nu=0.3, mu=1.0, **kw)
+    t = lambda a: torch.tensor(a, device=dev)
+    # a first apply on other data: nothing of it may reach the second one
+    plan.apply(t(1e3 * u), t(1e3 * q))
+    r = plan.apply(t(q), t(u)).cpu().numpy().reshape(nc, m)
+    info = plan.info()
+    plan.close()
+    p = O.problem(g, KIND[kernel], 0.3, 1.0)
+    ref, sc = O.apply(p, q if nc > 1 else q[0], u if nc > 1 else u[0], with_scale=True)
+    err = np.abs(r - np.reshape(ref, (nc, -1))).max() / np.max(sc)
+    assert err < TOL[prec], (kernel, prec, kw, err)
+    return info
+
+
+@pytest.mark.parametrize("pz", [32, 64, 96, 128, 192, 256, 320, 384, 512])
+@pytest.mark.parametrize("kernel", [B.LAPLACE3D, B.NAVIER3D])
+def test_every_length_with_full_pencils(dev, pz, kernel):
+    """All P/2 planes of the grid occupied from first to last (no zero plane
+    inside the half pencil), every schedule, the length fixed by the caller."""
+    nz = pz // 2
+    g = _Nodes((13, 10, nz), 0, nz - 1, seed=pz)
+    for prec in (B.FP64, B.FP32):
+        for sched in (0, 1, 2) if kernel == B.NAVIER3D and pz in (256, 384, 512) else (0, 1):
+            info = _check(dev, g, kernel, prec, pad=(32, 32, pz), autotune=2 + sched)
+            assert info["pad"] == [32, 32, pz] and info["zsched"] == sched
+
+
+@pytest.mark.parametrize("lo,hi,nz", [(0, 0, 40), (39, 39, 40), (7, 7, 128), (3, 18, 100), (99, 115, 128),
+                                      (10, 57, 128), (1, 96, 128), (60, 200, 256), (0, 127, 256)])
+def test_shortened_length(dev, lo, hi, nz):
+    """Planes lo..hi of nz: one plane, 2 nzo - 1 just below, at and just above
+    a supported length, at either end of the grid; the reported pad stays the
+    grid's."""
+    g = _Nodes((20, 9, nz), lo, hi, seed=lo + hi)
+    for kernel in (B.LAPLACE3D, B.NAVIER3D):
+        for prec in (B.FP64, B.FP32):
+            info = _check(dev, g, kernel, prec)
+            want = min(s for s in B.supported_sizes() if s >= 2 * nz)
+            assert info["pad"][2] == want and info["z_lo"] == lo and info["z_count"] == hi - lo + 1
+
+
+def test_shortened_length_grid_field_and_batch(dev):
+    """The grid evaluation (against the plan with the grid's own length) and
+    the batch (bit for bit against the plan) on a shortened plan."""
+    g = _Nodes((24, 20, 100), 30, 72, seed=4)
+    rng = np.random.default_rng(1)
+    q, u = (torch.tensor(rng.uniform(-1, 1, 60), device=dev) for _ in range(2))
+    for prec, tol in ((B.FP64, 1e-13), (B.FP32, 1e-5)):
+        a = B.Plan(g, B.LAPLACE3D, precision=prec)
+        b = B.Plan(g, B.LAPLACE3D, precision=prec, pad=(0, 0, 256))
+        fa, fb = a.eval_grid(q, u), b.eval_grid(q, u)
+        assert fa.shape == fb.shape == (1, 43, 20, 24)
+        assert float((fa - fb).abs().max()) <= tol * float(fb.abs().max())
+        batch = B.Batch([a], nrhs=2)
+        r = torch.empty(120, dtype=torch.float64, device=dev)
+        batch.apply(torch.cat([q, u]), torch.cat([u, q]), r)
+        assert torch.equal(r, torch.cat([a.apply(q, u), a.apply(u, q)]))
+        batch.close()
+        a.close()
+        b.close()
