@@ -171,27 +171,49 @@ __global__ void k_nn_gather(const float *y, const int *gx, const int *gy, const 
 }
 
 // s = 1/rms(u) over the Dirichlet slots (1 if there are none or u = 0):
-// one block, fixed-order reduction
-__global__ __launch_bounds__(256) void k_nn_scale(const double *known, const uint8_t *bc, int64_t m, double *s_out) {
-    __shared__ double ss[256], sc[256];
+// one block, fixed-order reduction; eight values per thread in flight (one at
+// a time the loop waited for each load: 20k nodes 24 -> 5 us).
+__global__ __launch_bounds__(1024) void k_nn_scale(const double *known, const uint8_t *bc, int64_t m, double *s_out) {
+    __shared__ double ss[16], sc[16];
     double a = 0.0, c = 0.0;
-    for (int64_t j = threadIdx.x; j < m; j += 256)
-        if (bc == nullptr || bc[j] == 0) {
-            a += known[j] * known[j];
-            c += 1.0;
+    for (int64_t j0 = threadIdx.x; j0 < m; j0 += 8 * 1024) {
+        double k[8];
+        bool on[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int64_t j = j0 + i * 1024;
+            on[i] = j < m;
+            const int64_t jc = on[i] ? j : 0;
+            k[i] = known[jc];
+            if (bc != nullptr) on[i] = on[i] && bc[jc] == 0;
         }
-    ss[threadIdx.x] = a;
-    sc[threadIdx.x] = c;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (threadIdx.x < o) {
-            ss[threadIdx.x] += ss[threadIdx.x + o];
-            sc[threadIdx.x] += sc[threadIdx.x + o];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            a += on[i] ? k[i] * k[i] : 0.0;
+            c += on[i] ? 1.0 : 0.0;
         }
-        __syncthreads();
     }
-    if (threadIdx.x == 0) *s_out = (ss[0] > 0.0 && sc[0] > 0.0) ? 1.0 / sqrt(ss[0] / sc[0]) : 1.0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        a += __shfl_xor(a, o, 64);
+        c += __shfl_xor(c, o, 64);
+    }
+    if (threadIdx.x % 64 == 0) {
+        ss[threadIdx.x / 64] = a;
+        sc[threadIdx.x / 64] = c;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        a = c = 0.0;
+        for (int w = 0; w < 16; ++w) {
+            a += ss[w];
+            c += sc[w];
+        }
+        *s_out = (a > 0.0 && c > 0.0) ? 1.0 / sqrt(a / c) : 1.0;
+    }
 }
+
+__device__ __forceinline__ int xcd_rank(int b, int nb) { return nb % 8 == 0 ? (b % 8) * (nb / 8) + b / 8 : b; }
 
 // ---------------------------------------------------------------- FP16 inference
 // Implicit-GEMM convolution on the matrix cores: for each tap t, the 16 x 16
@@ -308,6 +330,133 @@ __global__ __launch_bounds__(256) void k_conv16(const _Float16 *__restrict__ in,
     }
 }
 
+// Positions (consecutive voxels) that a block of the k_conv*q kernels takes at
+// once, and the largest dilation they take.
+constexpr int kQPos = 256;
+constexpr int kQMaxD = 16;
+
+// Voxel coordinates by multiplication: q = v / G for v < G^3, G <= 256, with
+// magic = floor(2^32 / G) + 1.
+__device__ __forceinline__ void vox_fast(int v, int G, unsigned magic, int &x, int &y, int &z) {
+    const int r = (int)__umulhi((unsigned)v, magic);
+    x = v - r * G;
+    z = (int)__umulhi((unsigned)r, magic);
+    y = r - z * G;
+}
+
+typedef unsigned u4 __attribute__((ext_vector_type(4)));
+// Descriptor of an array of 'bytes' bytes: loads past it return zero.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t nn_range(const void *p, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00027000);
+}
+constexpr int kOutside = (int)0x80000000u;  // a byte offset past every array
+
+// As k_conv16 for dilations up to kQMaxD, with a third of the loads: the three
+// dx taps of a (dz, dy) row read the same input shifted along x, so the tile's
+// unshifted input u is loaded once per row and multiplied by the three taps
+// into three accumulators, Q_dx[u] = sum_(dy,dz) W_(dx,dy,dz) in[u + rows], and
+//     out[v] = Q_-1[v - d] + Q_0[v] + Q_1[v + d]
+// is put together through LDS.  k_conv16 is bound by its 18 16-byte loads per
+// tile (1.0 GB through the L1 caches per 96^3 layer, 54 us); here five loads
+// per tile (two rows per 16x16x32 product) serve 15 products.  A block takes
+// kQPos positions, of which the outer d on each side only feed their
+// neighbours.  96^3, 16 channels: 54 -> 27 us per layer (25 for
+// the one-channel last one).
+template <bool LAST>
+__global__ __launch_bounds__(256) void k_conv16q(const _Float16 *__restrict__ in, const _Float16 *__restrict__ Wp,
+                                                 const float *__restrict__ bias, _Float16 *__restrict__ out,
+                                                 float *__restrict__ y, int G, unsigned magic, int d, int nrange) {
+    constexpr int T = kQPos / 64;  // tiles of 16 per wavefront
+    typedef typename std::conditional<LAST, float, f4>::type QT;
+    constexpr int QW = LAST ? 1 : 4;  // values per position
+    __shared__ QT qm[kQPos * QW], qp[kQPos * QW];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int j = lane & 15, kq = lane >> 4;
+    const int half = 8 * (kq & 1);  // this lane's eight channels of its row
+    const bool first = kq < 2;      // first row of the pair (else the second)
+    h8 A[3][5];
+    int delta[5];  // byte offset of the lane's row of pair i
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+        const int row = first ? 2 * i : 2 * i + 1;  // (dz + 1) * 3 + dy + 1; row 9 is empty
+        const int rc = row < 9 ? row : 0;
+        delta[i] = (((rc / 3 - 1) * G + rc % 3 - 1) * G * d) * 32;
+#pragma unroll
+        for (int x3 = 0; x3 < 3; ++x3) {
+            A[x3][i] = h8{};
+            if (row < 9) A[x3][i] = *reinterpret_cast<const h8 *>(Wp + ((row * 3 + x3) * 16 + j) * 16 + half);
+        }
+    }
+    float br[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) br[r] = bias[4 * kq + r];
+    const int V = G * G * G, own = kQPos - 2 * d;
+    const auto rs = nn_range(in, V * 32);
+    const int nb = gridDim.x, per = (nrange + nb - 1) / nb;
+    const int r_lo = xcd_rank(blockIdx.x, nb) * per;
+    const int r_hi = r_lo + per < nrange ? r_lo + per : nrange;
+    for (int rg = r_lo; rg < r_hi; ++rg) {
+        f4 q0[T];
+        int xs[T];
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+            const int pos = (wave * T + i) * 16 + j, v = rg * own - d + pos;
+            const bool valid = v >= 0 && v < V;
+            int x, yy, z;
+            vox_fast(valid ? v : 0, G, magic, x, yy, z);
+            xs[i] = x;
+            const bool vy[3] = {yy >= d, true, yy + d < G}, vz[3] = {valid && z >= d, valid, valid && z + d < G};
+            h8 B[5];
+#pragma unroll
+            for (int p = 0; p < 5; ++p) {
+                const int ra = 2 * p, rb = 2 * p + 1;  // constants
+                const bool oka = vz[ra / 3] && vy[ra % 3], okb = rb < 9 && vz[rb / 3 % 3] && vy[rb % 3];
+                const bool ok = first ? oka : okb;
+                B[p] = __builtin_bit_cast(
+                    h8, __builtin_amdgcn_raw_buffer_load_b128(rs, ok ? v * 32 + 2 * half + delta[p] : kOutside, 0, 0));
+            }
+            f4 acc[3];
+#pragma unroll
+            for (int x3 = 0; x3 < 3; ++x3) acc[x3] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int p = 0; p < 5; ++p)
+#pragma unroll
+                for (int x3 = 0; x3 < 3; ++x3)
+                    acc[x3] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[x3][p], B[p], acc[x3], 0, 0, 0);
+            if constexpr (LAST) {
+                if (kq == 0) {
+                    qm[pos] = acc[0][0];
+                    qp[pos] = acc[2][0];
+                }
+            } else {
+                qm[pos * 4 + kq] = acc[0];
+                qp[pos * 4 + kq] = acc[2];
+            }
+            q0[i] = acc[1];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+            const int pos = (wave * T + i) * 16 + j, v = rg * own - d + pos;
+            if (pos < d || pos >= kQPos - d || v >= V) continue;
+            const bool lo = xs[i] >= d, hi = xs[i] + d < G;
+            if constexpr (LAST) {
+                if (kq == 0) y[v] = ((q0[i][0] + (lo ? qm[pos - d] : 0.f)) + (hi ? qp[pos + d] : 0.f)) + br[0];
+            } else {
+                const f4 m = qm[(pos - d) * 4 + kq], p = qp[(pos + d) * 4 + kq];
+                h4 o;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float sm = (q0[i][r] + (lo ? m[r] : 0.f)) + (hi ? p[r] : 0.f);
+                    o[r] = (_Float16)fmaxf(sm + br[r], 0.f);
+                }
+                *reinterpret_cast<h4 *>(out + (int64_t)v * 16 + 4 * kq) = o;
+            }
+        }
+        __syncthreads();  // the next range rewrites qm and qp
+    }
+}
+
 // ---------------------------------------------------------------- FP32 training on the matrix cores
 // Every layer trains as an implicit GEMM on gfx950's FP32 16x16x4 matrix
 // product: FP32 operands, FP32 accumulation.  Activations and their
@@ -325,8 +474,6 @@ __global__ __launch_bounds__(256) void k_conv16(const _Float16 *__restrict__ in,
 typedef float f2 __attribute__((ext_vector_type(2)));
 template <int N>
 using fvec = typename std::conditional<N == 4, f4, typename std::conditional<N == 2, f2, float>::type>::type;
-
-__device__ __forceinline__ int xcd_rank(int b, int nb) { return nb % 8 == 0 ? (b % 8) * (nb / 8) + b / 8 : b; }
 
 __device__ __forceinline__ float lane_elem(float v, int) { return v; }
 template <typename T>
@@ -688,6 +835,9 @@ int mx_blocks(int64_t n, int64_t each, int cap) {
     return (int)b;
 }
 
+// The factor of vox_fast.
+unsigned vox_magic(int G) { return (unsigned)((1ull << 32) / (unsigned)G + 1); }
+
 template <int CIN, int CP, int COUT>
 int conv_fwd(const float *in, const float *W, const float *b, float *pre, float *post, int G, int d, int relu,
              hipStream_t st) {
@@ -829,11 +979,23 @@ int infer(bemfft_net *n, const float *x, hipStream_t st) {
     for (int l = 0; l < n->nl; ++l) {
         const _Float16 *W = n->wp + (int64_t)l * 27 * 256;
         const float *b = n->bp + l * 16;
-        if (l == n->nl - 1)
-            hipLaunchKernelGGL(k_conv16<true>, dim3(blocks), dim3(256), 0, st, in, W, b, out, y, n->G, n->dil[l], ntiles);
-        else
-            hipLaunchKernelGGL(k_conv16<false>, dim3(blocks), dim3(256), 0, st, in, W, b, out, y, n->G, n->dil[l],
-                               ntiles);
+        const int d = n->dil[l];
+        const bool last = l == n->nl - 1;
+        if (d <= kQMaxD) {
+            const int own = kQPos - 2 * d, nrange = (int)((V + own - 1) / own);
+            // as many blocks as stay resident (3 or 4 per CU), one share of ranges each
+            const dim3 grid(mx_blocks(nrange, 1, last ? 1024 : 768));
+            if (last)
+                hipLaunchKernelGGL(k_conv16q<true>, grid, dim3(256), 0, st, in, W, b, out, y, n->G, vox_magic(n->G), d,
+                                   nrange);
+            else
+                hipLaunchKernelGGL(k_conv16q<false>, grid, dim3(256), 0, st, in, W, b, out, y, n->G, vox_magic(n->G), d,
+                                   nrange);
+        } else if (last) {
+            hipLaunchKernelGGL(k_conv16<true>, dim3(blocks), dim3(256), 0, st, in, W, b, out, y, n->G, d, ntiles);
+        } else {
+            hipLaunchKernelGGL(k_conv16<false>, dim3(blocks), dim3(256), 0, st, in, W, b, out, y, n->G, d, ntiles);
+        }
         BF_HIP(hipGetLastError());
         std::swap(in, out);
     }
@@ -998,7 +1160,7 @@ int bemfft_net_guess(bemfft_net *n, bemfft_plan *p, const uint8_t *bc, const dou
                      double *x0, void *stream) {
     if (!n || !p || !known || !xbuf || !x0) return BEMFFT_EINVAL;
     hipStream_t st = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_nn_scale, dim3(1), dim3(256), 0, st, known, bc, p->m, n->sdev);
+    hipLaunchKernelGGL(k_nn_scale, dim3(1), dim3(1024), 0, st, known, bc, p->m, n->sdev);
     BF_HIP(hipGetLastError());
     BF_CHECK(input_impl(n, p, bc, known, 1.0, n->sdev, xbuf, st));
     BF_CHECK(infer(n, xbuf, st));

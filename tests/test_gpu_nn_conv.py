@@ -1,0 +1,48 @@
+"""The network's convolution kernels at the edges of their ranges: grids below,
+at and above a tile of 16 voxels and a block's 256 positions, and dilations up
+to and past the 16 up to which a block's halo is shared (and past the grid's
+half, where most taps leave the grid).  Bars as for the same entry points at
+ordinary sizes: they are per layer and do not depend on grid or dilation."""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import nn_oracle as NN  # noqa: E402
+from paper_1809_00845_amd import binding as B  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+# (grid, dilations): first, hidden and output layers on both sides of 16
+EDGES = [(4, (1, 2, 3, 4)), (6, (6, 5, 1)), (16, (15, 16, 1, 16)), (17, (16, 17, 16, 17)), (20, (17, 16, 18)),
+         (33, (16, 17, 8, 16)), (41, (1, 16))]
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    B.load()
+    return torch.device("cuda:0")
+
+
+def _case(G, dil):
+    rng = np.random.default_rng(1000 + G)
+    net = B.Net(G, dil, seed=4)
+    p = (0.2 * rng.standard_normal(net.nparam)).astype(np.float32)
+    net.set_params(p)
+    x = rng.standard_normal((6, G ** 3)).astype(np.float32)
+    return rng, net, p.astype(np.float64), x
+
+
+@pytest.mark.parametrize("G,dil", EDGES)
+def test_infer_edges(dev, G, dil):
+    _, net, p, x = _case(G, dil)
+    y = torch.empty(G ** 3, dtype=torch.float32, device=dev)
+    net.infer(torch.tensor(x, device=dev), y)
+    ref = NN.forward(p, list(dil), x.astype(np.float64).reshape(6, G, G, G))[0].ravel()
+    got = y.cpu().numpy()
+    assert np.abs(got - ref).max() <= 1e-2 * np.abs(ref).max()
+    assert np.linalg.norm(got - ref) <= 3e-3 * np.linalg.norm(ref)
+    net.close()
