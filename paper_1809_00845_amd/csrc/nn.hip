@@ -33,7 +33,7 @@ struct bemfft_net {
     int64_t nparam = 0;
     float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;  // params, grads, Adam moments
     float *xcl = nullptr;                   // training input, channel-last [V][8]
-    float *pre = nullptr, *post = nullptr;  // per layer [V][co] (post = relu(pre) for hidden layers)
+    float *post = nullptr;                  // activations per layer [V][co] (after the ReLU of hidden layers)
     float *ga = nullptr, *gb = nullptr;     // gradient ping-pong [V][width]
     float *part = nullptr;                  // weight-gradient partial sums
     float *red = nullptr;                   // loss partial sums
@@ -116,8 +116,17 @@ __global__ __launch_bounds__(256) void k_conv_w_reduce(const float *part, int nc
     const int per = (nchunk + 7) / 8, c0 = sl * per, c1 = c0 + per < nchunk ? c0 + per : nchunk;
     const int64_t stride = (int64_t)cout * cin * 28;
     float s = 0.f;
-    if (off >= 0)
-        for (int ch = c0; ch < c1; ++ch) s += part[ch * stride + off];
+    if (off >= 0) {
+        int ch = c0;
+        for (; ch + 16 <= c1; ch += 16) {  // sixteen loads in flight, added in order
+            float v[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = part[(ch + i) * stride + off];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s += v[i];
+        }
+        for (; ch < c1; ++ch) s += part[ch * stride + off];
+    }
     sm[sl][o] = s;
     __syncthreads();
     if (sl == 0 && off >= 0) {
@@ -360,8 +369,8 @@ constexpr int kOutside = (int)0x80000000u;  // a byte offset past every array
 // tile (1.0 GB through the L1 caches per 96^3 layer, 54 us); here five loads
 // per tile (two rows per 16x16x32 product) serve 15 products.  A block takes
 // kQPos positions, of which the outer d on each side only feed their
-// neighbours.  96^3, 16 channels: 54 -> 27 us per layer (25 for
-// the one-channel last one).
+// neighbours.  96^3, 16 channels: 54 -> 27 us per layer (25 for the
+// one-channel last one).
 template <bool LAST>
 __global__ __launch_bounds__(256) void k_conv16q(const _Float16 *__restrict__ in, const _Float16 *__restrict__ Wp,
                                                  const float *__restrict__ bias, _Float16 *__restrict__ out,
@@ -453,7 +462,7 @@ __global__ __launch_bounds__(256) void k_conv16q(const _Float16 *__restrict__ in
                 *reinterpret_cast<h4 *>(out + (int64_t)v * 16 + 4 * kq) = o;
             }
         }
-        __syncthreads();  // the next range rewrites qm and qp
+        __syncthreads();  // the next range rewrites qx
     }
 }
 
@@ -546,8 +555,8 @@ __device__ __forceinline__ void load_plane(const float *__restrict__ src, int x,
 // in(. + d o_t) (CP x 16), NS products of four channels.
 template <int CIN, int CP, int COUT>
 __global__ __launch_bounds__(256) void k_conv_fwd_mx(const float *__restrict__ in, const float *__restrict__ W,
-                                                     const float *__restrict__ bias, float *__restrict__ pre,
-                                                     float *__restrict__ post, int G, int d, int relu, int ntiles) {
+                                                     const float *__restrict__ bias, float *__restrict__ post, int G,
+                                                     int d, int relu, int ntiles) {
     constexpr int NS = CP / 4;
     typedef fvec<NS> VT;
     __shared__ VT sA[27][64];
@@ -607,16 +616,12 @@ __global__ __launch_bounds__(256) void k_conv_fwd_mx(const float *__restrict__ i
         if (valid) {
             const f4 o = ((acc[0] + acc[1]) + acc[2]) + br;
             if constexpr (COUT == 16) {
-                *reinterpret_cast<f4 *>(pre + (int64_t)v * 16 + 4 * kq) = o;
-                if (post) {
-                    f4 p;
+                f4 p;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) p[r] = relu ? fmaxf(o[r], 0.f) : o[r];
-                    *reinterpret_cast<f4 *>(post + (int64_t)v * 16 + 4 * kq) = p;
-                }
+                for (int r = 0; r < 4; ++r) p[r] = relu ? fmaxf(o[r], 0.f) : o[r];
+                *reinterpret_cast<f4 *>(post + (int64_t)v * 16 + 4 * kq) = p;
             } else if (kq == 0) {
-                pre[v] = o[0];
-                if (post) post[v] = relu ? fmaxf(o[0], 0.f) : o[0];
+                post[v] = relu ? fmaxf(o[0], 0.f) : o[0];
             }
         }
         x = xn;
@@ -627,15 +632,15 @@ __global__ __launch_bounds__(256) void k_conv_fwd_mx(const float *__restrict__ i
     }
 }
 
-// Data gradient into a 16-channel layer, gin[v][ci] = (prev_pre[v][ci] > 0)
-// sum_{c, t} W[c][ci][t] g[v - d o_t][c]: per tap t, D (16 input channels x
-// 16 voxels) += W_t^T (16 x COUT) g(. - d o_t) (COUT x 16); the same plane
-// pipeline as the forward.
-template <int COUT>
+// Data gradient between 16-channel layers, gin[v][ci] = (prev[v][ci] > 0)
+// sum_{c, t} W[c][ci][t] g[v - d o_t][c], prev the activations of that layer
+// (positive where its ReLU passes): per tap t, D (16 input channels x 16
+// voxels) += W_t^T (16 x 16) g(. - d o_t) (16 x 16); the same plane pipeline
+// as the forward.
 __global__ __launch_bounds__(256) void k_conv_bwd_data_mx(const float *__restrict__ g, const float *__restrict__ W,
-                                                          const float *__restrict__ prev_pre, float *__restrict__ gin,
+                                                          const float *__restrict__ prev, float *__restrict__ gin,
                                                           int G, int d, int ntiles) {
-    constexpr int NS = COUT == 16 ? 4 : 1;
+    constexpr int COUT = 16, NS = 4;
     typedef fvec<NS> VT;
     __shared__ VT sA[27][64];
     stage_weights<NS, true>(W, 16, COUT, sA);
@@ -690,7 +695,7 @@ __global__ __launch_bounds__(256) void k_conv_bwd_data_mx(const float *__restric
         }
         if (valid) {
             const f4 o = (acc[0] + acc[1]) + acc[2];
-            const f4 pp = *reinterpret_cast<const f4 *>(prev_pre + (int64_t)v * 16 + 4 * kq);
+            const f4 pp = *reinterpret_cast<const f4 *>(prev + (int64_t)v * 16 + 4 * kq);
             f4 w;
 #pragma unroll
             for (int r = 0; r < 4; ++r) w[r] = pp[r] > 0.f ? o[r] : 0.f;
@@ -704,39 +709,312 @@ __global__ __launch_bounds__(256) void k_conv_bwd_data_mx(const float *__restric
     }
 }
 
-// Weight and bias gradients of one layer, gW[c][ci][t] = sum_v g[v][c]
-// in[v + d o_t][ci]: per tap t, D (16 output channels x 16 input channels)
-// += g (16 x 4 voxels) in(. + d o_t)^T (4 x 16), four voxels per product,
-// one accumulator per tap.  blockIdx.y picks the z offset of the taps (9
-// taps per block).  A block walks slabs of kSlab voxels; lane (j, k) of wave
-// w keeps g of voxels 64 k + 16 w + i (i < 16, the K index of product i) in
-// registers for the whole slab.  Tap by tap, the slab's shifted input (zero
-// where the tap leaves the grid) is fetched with coalesced 16-byte loads --
-// the next two taps' into registers while the current one is multiplied --
-// and stored transposed in LDS, [ci][u] with padded rows, so that a lane
-// reads the B values of four products with one 16-byte LDS load (two
-// buffers, one barrier per tap).  The four wavefronts' sums are added
-// through LDS in a fixed order into the partial part[blockIdx.x][c][ci][28]
-// (taps 0..26, bias in slot 27 of ci 0), which k_conv_w_reduce adds up in a
-// fixed order: deterministic.
+// Forward of a layer (SIGN = 1) and data gradient between 16-channel layers
+// (SIGN = -1) for dilations up to kQMaxD, with a third of the loads of the
+// kernels above: as in k_conv16q the input of a (dz, dy) row is loaded once per
+// tile and multiplied by the row's three dx taps into three accumulators,
+//     Q_dx[u] = sum_(dy,dz) W_(dx,dy,dz) in[u + SIGN rows],
+//     out[v] = Q_-1[v - SIGN d] + Q_0[v] + Q_1[v + SIGN d],
+// summed through LDS.  Two tiles share each weight word read from LDS (at one
+// tile per word those reads alone take as long as the products).  A wavefront
+// takes two pairs of tiles; the next plane's loads are in flight during a
+// plane's products.  Forward: out = relu(. + bias) or without ReLU; gradient:
+// out is zero where prev (the layer's activations) is not positive.
+// Bound: the FP32 matrix cores, 12.2 GFLOP at 96^3 and 16 channels = 78 us at
+// 157 TFLOP/s plus the d positions computed twice per side; 168 -> 120 us (six
+// channels 94 -> 68), of which an eighth is blocks with fewer ranges than others.
+template <int CIN, int CP, int SIGN>
+__global__ __launch_bounds__(256) void k_conv_q(const float *__restrict__ in, const float *__restrict__ W,
+                                                const float *__restrict__ bias, const float *__restrict__ prev,
+                                                float *__restrict__ out, int G, unsigned magic, int d, int relu,
+                                                int nrange) {
+    constexpr int NS = CP / 4;
+    typedef fvec<NS> VT;
+    __shared__ VT sA[27][64];
+    __shared__ f4 qm[kQPos * 4], qp[kQPos * 4];
+    stage_weights<NS, (SIGN < 0)>(W, CIN, 16, sA);
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int j = lane & 15, kq = lane >> 4;
+    f4 br = f4{0.f, 0.f, 0.f, 0.f};
+    if (SIGN > 0) br = *reinterpret_cast<const f4 *>(bias + 4 * kq);
+    const int V = G * G * G, own = kQPos - 2 * d;
+    const auto rs = nn_range(in, V * CP * 4);
+    const int nb = gridDim.x, per = (nrange + nb - 1) / nb;
+    const int r_lo = xcd_rank(blockIdx.x, nb) * per;
+    const int r_hi = r_lo + per < nrange ? r_lo + per : nrange;
+    struct Pos {
+        int v, x, y, z;
+        bool valid;
+    };
+    auto position = [&](int rg, int i) {  // tile i of the wavefront's four
+        Pos p;
+        p.v = rg * own - d + (wave * 4 + i) * 16 + j;
+        p.valid = p.v >= 0 && p.v < V;
+        vox_fast(p.valid ? p.v : 0, G, magic, p.x, p.y, p.z);
+        return p;
+    };
+    // the rows of plane dz = q - 1 of tile position p
+    auto load = [&](const Pos &p, int q, VT *B) {
+        const int dz = SIGN * (q - 1) * d;
+        const bool zok = p.valid && p.z + dz >= 0 && p.z + dz < G;
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const int dy = SIGN * (r - 1) * d;
+            const bool ok = zok && p.y + dy >= 0 && p.y + dy < G;
+            const int off = ok ? (p.v + (dz * G + dy) * G) * (CP * 4) + kq * (NS * 4) : kOutside;
+            if constexpr (NS == 4) B[r] = __builtin_bit_cast(VT, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
+            else B[r] = __builtin_bit_cast(VT, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0));
+        }
+    };
+    VT Bc[2][3], Bn[2][3];
+    Pos pc[2];
+    if (r_lo < r_hi) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            pc[i] = position(r_lo, i);
+            load(pc[i], 0, Bc[i]);
+        }
+    }
+    for (int rg = r_lo; rg < r_hi; ++rg) {
+        f4 q0[4];
+        int xs[4];
+#pragma unroll
+        for (int pr = 0; pr < 2; ++pr) {
+            Pos pn[2];
+            f4 acc[2][3];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int x3 = 0; x3 < 3; ++x3) acc[i][x3] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                __builtin_amdgcn_sched_barrier(0);  // one plane's weight words live at a time
+                if (q < 2) {
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) load(pc[i], q + 1, Bn[i]);
+                } else if (pr == 0 || rg + 1 < r_hi) {  // the next pair, or the next range's first
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        pn[i] = position(pr == 0 ? rg : rg + 1, pr == 0 ? 2 + i : i);
+                        load(pn[i], 0, Bn[i]);
+                    }
+                }
+#pragma unroll
+                for (int r = 0; r < 3; ++r)
+#pragma unroll
+                    for (int x3 = 0; x3 < 3; ++x3) {
+                        const VT a = sA[q * 9 + r * 3 + x3][lane];
+#pragma unroll
+                        for (int s = 0; s < NS; ++s)  // alternating accumulators
+#pragma unroll
+                            for (int i = 0; i < 2; ++i)
+                                acc[i][x3] = __builtin_amdgcn_mfma_f32_16x16x4f32(lane_elem(a, s), lane_elem(Bc[i][r], s),
+                                                                                  acc[i][x3], 0, 0, 0);
+                    }
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int r = 0; r < 3; ++r) Bc[i][r] = Bn[i][r];
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int pos = (wave * 4 + 2 * pr + i) * 16 + j;
+                qm[pos * 4 + kq] = acc[i][0];
+                qp[pos * 4 + kq] = acc[i][2];
+                q0[2 * pr + i] = acc[i][1];
+                xs[2 * pr + i] = pc[i].x;
+                pc[i] = pn[i];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int pos = (wave * 4 + i) * 16 + j, v = rg * own - d + pos;
+            if (pos < d || pos >= kQPos - d || v >= V) continue;
+            // the term of tap dx is in range if x + SIGN dx d is
+            const bool lo = xs[i] >= d, hi = xs[i] + d < G;
+            const f4 m = qm[(pos - SIGN * d) * 4 + kq], p = qp[(pos + SIGN * d) * 4 + kq];
+            const bool okm = SIGN > 0 ? lo : hi, okp = SIGN > 0 ? hi : lo;
+            f4 o;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o[r] = ((q0[i][r] + (okm ? m[r] : 0.f)) + (okp ? p[r] : 0.f)) + br[r];
+            f4 *dst = reinterpret_cast<f4 *>(out + (int64_t)v * 16 + 4 * kq);
+            if constexpr (SIGN > 0) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o[r] = relu ? fmaxf(o[r], 0.f) : o[r];
+            } else {
+                const f4 pp = *reinterpret_cast<const f4 *>(prev + (int64_t)v * 16 + 4 * kq);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o[r] = pp[r] > 0.f ? o[r] : 0.f;
+            }
+            *dst = o;
+        }
+        __syncthreads();  // the next range rewrites qm and qp
+    }
+}
+
+// Forward of the one-channel output layer (no ReLU), dilations up to kQMaxD:
+// rows of the product are the three dx taps (three of sixteen) instead of the
+// output channels (one of sixteen), so a tile takes 36 products and 9 loads
+// instead of 108 and 27.  96^3: 146 -> 57 us.
+__global__ __launch_bounds__(256) void k_conv_fwd_q1(const float *__restrict__ in, const float *__restrict__ W,
+                                                     const float *__restrict__ bias, float *__restrict__ y, int G,
+                                                     unsigned magic, int d, int nrange) {
+    constexpr int T = kQPos / 64;
+    __shared__ float qm[kQPos], qp[kQPos];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int j = lane & 15, kq = lane >> 4;
+    f4 A[9];  // lane (dx = j, kq): W[4 kq + s][tap]
+#pragma unroll
+    for (int r = 0; r < 9; ++r)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) A[r][s] = j < 3 ? W[(4 * kq + s) * 27 + r * 3 + j] : 0.f;
+    const float b0 = bias[0];
+    const int V = G * G * G, own = kQPos - 2 * d;
+    const auto rs = nn_range(in, V * 64);
+    const int nb = gridDim.x, per = (nrange + nb - 1) / nb;
+    const int r_lo = xcd_rank(blockIdx.x, nb) * per;
+    const int r_hi = r_lo + per < nrange ? r_lo + per : nrange;
+    for (int rg = r_lo; rg < r_hi; ++rg) {
+        float q0[T];
+        int xs[T];
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+            const int pos = (wave * T + i) * 16 + j, v = rg * own - d + pos;
+            const bool valid = v >= 0 && v < V;
+            int x, yy, z;
+            vox_fast(valid ? v : 0, G, magic, x, yy, z);
+            xs[i] = x;
+            const bool vy[3] = {yy >= d, true, yy + d < G}, vz[3] = {valid && z >= d, valid, valid && z + d < G};
+            f4 acc[3], B[9];  // one sum per dz, alternating
+#pragma unroll
+            for (int r = 0; r < 9; ++r) {
+                const bool ok = vz[r / 3] && vy[r % 3];
+                const int off = ok ? (v + ((r / 3 - 1) * G + r % 3 - 1) * G * d) * 64 + kq * 16 : kOutside;
+                B[r] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
+            }
+#pragma unroll
+            for (int q = 0; q < 3; ++q) acc[q] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+                        acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[3 * q + r][s], B[3 * q + r][s], acc[q], 0, 0, 0);
+            const f4 sm = (acc[0] + acc[1]) + acc[2];
+            if (kq == 0) {
+                qm[pos] = sm[0];
+                qp[pos] = sm[2];
+            }
+            q0[i] = sm[1];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+            const int pos = (wave * T + i) * 16 + j, v = rg * own - d + pos;
+            if (kq != 0 || pos < d || pos >= kQPos - d || v >= V) continue;
+            y[v] = ((q0[i] + (xs[i] >= d ? qm[pos - d] : 0.f)) + (xs[i] + d < G ? qp[pos + d] : 0.f)) + b0;
+        }
+        __syncthreads();
+    }
+}
+
+// Data gradient of the one-channel output layer, gin[v][ci] = (prev[v][ci] > 0)
+// sum_t W[ci][t] g[v - d o_t]: the contraction runs over the 27 taps (seven
+// products of four taps per tile instead of 27 with one used channel each).
+// Bound by the 16-channel array read and written.  96^3: 81 -> 26 us.
+__global__ __launch_bounds__(256) void k_conv_bwd_data1(const float *__restrict__ g, const float *__restrict__ W,
+                                                        const float *__restrict__ prev, float *__restrict__ gin, int G,
+                                                        unsigned magic, int d, int ntiles) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int j = lane & 15, kq = lane >> 4;
+    float A[7];
+    int tx[7], ty[7], tz[7];  // d o_t of the lane's tap 4 s + kq
+#pragma unroll
+    for (int s = 0; s < 7; ++s) {
+        const int t = 4 * s + kq;
+        A[s] = t < 27 ? W[j * 27 + t] : 0.f;
+        tx[s] = d * (t % 3 - 1);
+        ty[s] = d * (t / 3 % 3 - 1);
+        tz[s] = t < 27 ? d * (t / 9 - 1) : 2 * G;  // tap 27 does not exist
+    }
+    const int V = G * G * G;
+    const auto rs = nn_range(g, V * 4);
+    const int nb = gridDim.x, per = (ntiles + nb - 1) / nb;
+    const int t_lo = xcd_rank(blockIdx.x, nb) * per;
+    const int t_hi = t_lo + per < ntiles ? t_lo + per : ntiles;
+    for (int tile = t_lo + wave; tile < t_hi; tile += 4) {
+        const int v = tile * 16 + j;
+        const bool valid = v < V;
+        int x, y, z;
+        vox_fast(valid ? v : 0, G, magic, x, y, z);
+        float B[7];
+#pragma unroll
+        for (int s = 0; s < 7; ++s) {
+            const int xx = x - tx[s], yy = y - ty[s], zz = z - tz[s];
+            const bool ok = valid && xx >= 0 && xx < G && yy >= 0 && yy < G && zz >= 0 && zz < G;
+            B[s] = __builtin_bit_cast(
+                float, __builtin_amdgcn_raw_buffer_load_b32(rs, ok ? ((zz * G + yy) * G + xx) * 4 : kOutside, 0, 0));
+        }
+        f4 acc[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int s = 0; s < 7; ++s) acc[s & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[s], B[s], acc[s & 1], 0, 0, 0);
+        if (valid) {
+            const f4 o = acc[0] + acc[1];
+            const f4 pp = *reinterpret_cast<const f4 *>(prev + (int64_t)v * 16 + 4 * kq);
+            f4 w;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) w[r] = pp[r] > 0.f ? o[r] : 0.f;
+            *reinterpret_cast<f4 *>(gin + (int64_t)v * 16 + 4 * kq) = w;
+        }
+    }
+}
+
+// Weight and bias gradients of one 16-channel-output layer, gW[c][ci][t] =
+// sum_v g[v][c] in[v + d o_t][ci].  With u = v + d dx (the tap's x offset moved
+// to the gradient),
+//     gW[c][ci][dz, dy, dx] = sum_u g[u - d dx][c] in[u + d (dz, dy)][ci],
+// so a (dz, dy) row of the input serves its three dx taps: D (16 output
+// channels x 16 input channels) += g (16 x 4 voxels) in^T (4 x 16), four voxels
+// per product, one accumulator for each of the 27 taps.  A block walks slabs of
+// kSlab voxels u; lane (j, k) of wave w keeps the three shifted g of voxels
+// 64 k + 16 w + i (i < 16, the K index of product i) in registers for the slab.
+// Row by row the slab's input (zero where the row leaves the grid) is fetched
+// with coalesced 16-byte loads, one row ahead, and stored transposed in LDS,
+// [ci][u] with padded rows, so that one 16-byte LDS read feeds twelve products.
+// With the 8-channel input layer two rows share the sixteen columns of a
+// product.  The four wavefronts' sums are added through LDS in a fixed order
+// into the partial part[blockIdx.x][c][ci][28] (taps 0..26, bias in slot 27 of
+// ci 0), which k_conv_w_reduce adds up in a fixed order: deterministic.
+// Bound: the FP32 matrix cores (78 us at 96^3 and 16 channels).  Staging every
+// tap 190 us; nine taps per block, three blocks sharing a slab, 142 us (g
+// loaded three times as often, each time waited for); now
+// 128 (six channels 185 -> 76); the address and LDS work issues in between the
+// products, not beside them.
 constexpr int kSlab = 256;
 
-template <int CIN, int CP, int COUT>
-__global__ __launch_bounds__(256) void k_conv_bwd_w_mx(const float *__restrict__ g, const float *__restrict__ in,
-                                                       float *__restrict__ part, int G, int d, int nslabs) {
-    constexpr int QV = CP / 4;            // 16-byte words per voxel of the input
-    constexpr int NF = kSlab * QV / 256;  // of them staged per thread and tap
-    constexpr int LD = kSlab + 4;         // padded row of the transposed slab
-    __shared__ __align__(16) float sT[2][CP * LD];
-    __shared__ float sR[4][256];
+template <int CIN, int CP>
+__global__ __launch_bounds__(256) void k_conv_bwd_w(const float *__restrict__ g, const float *__restrict__ in,
+                                                    float *__restrict__ part, int G, unsigned magic, int d,
+                                                    int nslabs) {
+    constexpr int QV = CP / 4;                // 16-byte words per voxel of the input
+    constexpr int NF = kSlab * QV / 256;      // of them per thread and row
+    constexpr int RP = 16 / CP;               // rows sharing the columns of a product
+    constexpr int NG = (9 + RP - 1) / RP;     // groups of the nine (dz, dy) rows
+    constexpr int LD = kSlab + 4;             // padded row of the transposed slab
+    __shared__ __align__(16) float sT[2][16 * LD];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int j = lane & 15, kq = lane >> 4;
-    const int qz = blockIdx.y;  // taps 9 qz .. 9 qz + 8 (dz = qz - 1)
-    const int V = G * G * G, GG = G * G;
+    const int V = G * G * G;
     const int ubase = 64 * kq + 16 * wave;  // this lane's product voxels: ubase + i
-    f4 acc[9];
+    const auto rg = nn_range(g, V * 64), ri = nn_range(in, V * CP * 4);
+    f4 acc[NG][3];
 #pragma unroll
-    for (int t = 0; t < 9; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int a = 0; a < NG; ++a)
+#pragma unroll
+        for (int x3 = 0; x3 < 3; ++x3) acc[a][x3] = f4{0.f, 0.f, 0.f, 0.f};
     float accb = 0.f;  // bias of channel j from this lane's voxels
     const int nb = gridDim.x, per = (nslabs + nb - 1) / nb;
     const int s_lo = xcd_rank(blockIdx.x, nb) * per;
@@ -744,85 +1022,178 @@ __global__ __launch_bounds__(256) void k_conv_bwd_w_mx(const float *__restrict__
     for (int slab = s_lo; slab < s_hi; ++slab) {
         const int v0 = slab * kSlab;
         // staged words: f = tid + 256 i is voxel f / QV, channels 4 (f % QV) .. + 3
-        int ux[NF], uy[NF], uz[NF];
+        int uy[NF], uz[NF];
         bool uval[NF];
 #pragma unroll
         for (int i = 0; i < NF; ++i) {
             const int vs = v0 + (tid + 256 * i) / QV;
+            int x;
             uval[i] = vs < V;
-            const int vv = uval[i] ? vs : 0;
-            ux[i] = vv % G;
-            uy[i] = (vv / G) % G;
-            uz[i] = vv / GG;
+            vox_fast(uval[i] ? vs : 0, G, magic, x, uy[i], uz[i]);
         }
-        auto fetch = [&](int t9, f4 *R) {
-            const int dx = d * (t9 % 3 - 1), dy = d * (t9 / 3 - 1), dz = d * (qz - 1);
+        auto fetch = [&](int a, f4 (*R)[NF]) {  // the rows of group a
 #pragma unroll
-            for (int i = 0; i < NF; ++i) {
-                const int f = tid + 256 * i;
-                const int xx = ux[i] + dx, yy = uy[i] + dy, zz = uz[i] + dz;
-                const bool ok = uval[i] && xx >= 0 && xx < G && yy >= 0 && yy < G && zz >= 0 && zz < G;
-                const f4 val =
-                    *reinterpret_cast<const f4 *>(in + (ok ? ((int64_t)(zz * G + yy) * G + xx) * CP + 4 * (f % QV) : 0));
-                R[i] = ok ? val : f4{0.f, 0.f, 0.f, 0.f};
+            for (int h = 0; h < RP; ++h) {
+                const int row = a * RP + h, dz = d * (row / 3 - 1), dy = d * (row % 3 - 1);
+#pragma unroll
+                for (int i = 0; i < NF; ++i) {
+                    const int yy = uy[i] + dy, zz = uz[i] + dz;
+                    const bool ok = row < 9 && uval[i] && yy >= 0 && yy < G && zz >= 0 && zz < G;
+                    const int off = ok ? (v0 + (dz * G + dy) * G) * (CP * 4) + 16 * (tid + 256 * i) : kOutside;
+                    R[h][i] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(ri, off, 0, 0));
+                }
             }
         };
-        f4 R0[NF], R1[NF];  // taps t and t + 1 in flight
-        fetch(0, R0);
-        fetch(1, R1);
-        float a[16];
+        f4 R[RP][NF];
+        fetch(0, R);
+        float ga[3][16];
+        int gx, gy, gz;  // coordinates of the lane's first product voxel
+        vox_fast(v0 + ubase < V ? v0 + ubase : 0, G, magic, gx, gy, gz);
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const int vg = v0 + ubase + i;
-            const bool ok = j < COUT && vg < V;
-            const float val = g[ok ? (int64_t)vg * COUT + (COUT == 16 ? j : 0) : 0];
-            a[i] = ok ? val : 0.f;
-            accb += a[i];
+            const int u = v0 + ubase + i;
+            int ux = gx + i;
+            while (ux >= G) ux -= G;
+#pragma unroll
+            for (int x3 = 0; x3 < 3; ++x3) {
+                const int xv = ux - d * (x3 - 1);  // x of v = u - d dx
+                const bool ok = u < V && xv >= 0 && xv < G;
+                ga[x3][i] = __builtin_bit_cast(
+                    float, __builtin_amdgcn_raw_buffer_load_b32(rg, ok ? (u - d * (x3 - 1)) * 64 + j * 4 : kOutside, 0, 0));
+            }
+            accb += ga[1][i];
         }
         __syncthreads();  // the previous slab's products have read both buffers
 #pragma unroll
-        for (int t = 0; t < 9; ++t) {
-            float *T = sT[t & 1];
-            f4 *R = (t & 1) ? R1 : R0;
+        for (int a = 0; a < NG; ++a) {
+            float *T = sT[a & 1];
 #pragma unroll
-            for (int i = 0; i < NF; ++i) {
-                const int f = tid + 256 * i, u = f / QV, c0 = 4 * (f % QV);
+            for (int h = 0; h < RP; ++h)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) T[(c0 + e) * LD + u] = R[i][e];
-            }
+                for (int i = 0; i < NF; ++i) {
+                    const int f = tid + 256 * i, u = f / QV, c0 = h * CP + 4 * (f % QV);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) T[(c0 + e) * LD + u] = R[h][i][e];
+                }
             __syncthreads();
-            if (t + 2 < 9) fetch(t + 2, R);
+            if (a + 1 < NG) fetch(a + 1, R);
 #pragma unroll
             for (int h = 0; h < 4; ++h) {
-                f4 b = f4{0.f, 0.f, 0.f, 0.f};
-                if (j < CP) b = *reinterpret_cast<const f4 *>(T + j * LD + ubase + 4 * h);
+                const f4 b = *reinterpret_cast<const f4 *>(T + j * LD + ubase + 4 * h);
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[4 * h + e], b[e], acc[t], 0, 0, 0);
+#pragma unroll
+                    for (int x3 = 0; x3 < 3; ++x3)
+                        acc[a][x3] =
+                            __builtin_amdgcn_mfma_f32_16x16x4f32(ga[x3][4 * h + e], b[e], acc[a][x3], 0, 0, 0);
             }
         }
     }
-    // block sums in a fixed order
-    float *pb = part + (int64_t)blockIdx.x * COUT * CIN * 28;
+    // block sums in a fixed order, eight accumulators at a time
+    float *pb = part + (int64_t)blockIdx.x * 16 * CIN * 28;
+    float *sR = &sT[0][0];  // [8][4][256]
+    static_assert(2 * 16 * LD >= 8 * 4 * 256, "the sums fit the slab's buffers");
 #pragma unroll
-    for (int t = 0; t < 9; ++t) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sR[wave][lane * 4 + r] = acc[t][r];
+    for (int b0 = 0; b0 < NG * 3; b0 += 8) {
         __syncthreads();
-        {
-            const int i = tid, ln = i >> 2, c = 4 * (ln >> 4) + (i & 3), ci = ln & 15;
-            const float s = (sR[0][i] + sR[1][i]) + (sR[2][i] + sR[3][i]);
-            if (c < COUT && ci < CIN) pb[(c * CIN + ci) * 28 + 9 * qz + t] = s;
+#pragma unroll
+        for (int b = b0; b < b0 + 8 && b < NG * 3; ++b)
+            *reinterpret_cast<f4 *>(sR + ((b - b0) * 4 + wave) * 256 + lane * 4) = acc[b / 3][b % 3];
+        __syncthreads();
+#pragma unroll
+        for (int b = b0; b < b0 + 8 && b < NG * 3; ++b) {
+            const float *q = sR + (b - b0) * 1024 + tid;
+            const int ln = tid >> 2, c = 4 * (ln >> 4) + (tid & 3), col = ln & 15;
+            const int row = b / 3 * RP + col / CP, ci = col % CP;
+            if (row < 9 && ci < CIN) pb[(c * CIN + ci) * 28 + 3 * row + b % 3] = (q[0] + q[256]) + (q[512] + q[768]);
         }
-        __syncthreads();
     }
-    if (qz == 0) {  // the bias once per chunk
-        accb += __shfl_xor(accb, 16, 64);
-        accb += __shfl_xor(accb, 32, 64);
-        if (kq == 0) sR[wave][j] = accb;
-        __syncthreads();
-        if (tid < COUT) pb[(tid * CIN + 0) * 28 + 27] = (sR[0][tid] + sR[1][tid]) + (sR[2][tid] + sR[3][tid]);
+    accb += __shfl_xor(accb, 16, 64);
+    accb += __shfl_xor(accb, 32, 64);
+    __syncthreads();
+    if (kq == 0) sR[wave * 16 + j] = accb;
+    __syncthreads();
+    if (tid < 16) pb[(tid * CIN + 0) * 28 + 27] = (sR[tid] + sR[16 + tid]) + (sR[32 + tid] + sR[48 + tid]);
+}
+
+// Weight and bias gradients of the one-channel output layer, gW[ci][t] =
+// sum_u g[u - d o_t] in[u][ci]: the rows of a product are taps (27 of two
+// sixteens) instead of output channels (one of sixteen), so the 16-channel
+// array is read once and not once per tap.  Sixteen voxels per step; lane (j,
+// k) takes taps j and 16 + j, channel j, voxels 4 k + s.  Partials and
+// reduction as above.  96^3: 146 -> 38 us.
+__global__ __launch_bounds__(256) void k_conv_bwd_w1(const float *__restrict__ g, const float *__restrict__ in,
+                                                     float *__restrict__ part, int G, unsigned magic, int d,
+                                                     int ntiles) {
+    __shared__ float sR[4][512];
+    __shared__ float sB[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int j = lane & 15, kq = lane >> 4;
+    const int V = G * G * G;
+    const auto rg = nn_range(g, V * 4), ri = nn_range(in, V * 64);
+    int tx[2], ty[2], tz[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int t = 16 * h + j;
+        tx[h] = d * (t % 3 - 1);
+        ty[h] = d * (t / 3 % 3 - 1);
+        tz[h] = t < 27 ? d * (t / 9 - 1) : 2 * G;  // no such tap
     }
+    f4 acc[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};
+    float accb = 0.f;
+    const int nb = gridDim.x, per = (ntiles + nb - 1) / nb;
+    const int t_lo = xcd_rank(blockIdx.x, nb) * per;
+    const int t_hi = t_lo + per < ntiles ? t_lo + per : ntiles;
+    for (int tile = t_lo + wave; tile < t_hi; tile += 4) {
+        const int u0 = tile * 16 + 4 * kq;
+        int x0, y0, z0;
+        vox_fast(u0 < V ? u0 : 0, G, magic, x0, y0, z0);
+        float A[2][4], B[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int u = u0 + s;
+            int x = x0 + s, y = y0, z = z0;
+            if (x >= G) {  // at most one row further: G >= 4
+                x -= G;
+                if (++y == G) {
+                    y = 0;
+                    ++z;
+                }
+            }
+            const bool uok = u < V;
+            B[s] = __builtin_bit_cast(float,
+                                      __builtin_amdgcn_raw_buffer_load_b32(ri, uok ? u * 64 + j * 4 : kOutside, 0, 0));
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int xx = x - tx[h], yy = y - ty[h], zz = z - tz[h];
+                const bool ok = uok && xx >= 0 && xx < G && yy >= 0 && yy < G && zz >= 0 && zz < G;
+                A[h][s] = __builtin_bit_cast(
+                    float, __builtin_amdgcn_raw_buffer_load_b32(rg, ok ? ((zz * G + yy) * G + xx) * 4 : kOutside, 0, 0));
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[h][s], B[s], acc[h], 0, 0, 0);
+            if (j == 13) accb += A[0][s];  // tap 13 is the centre: g itself
+        }
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sR[wave][h * 256 + lane * 4 + r] = acc[h][r];
+    accb += __shfl_xor(accb, 16, 64);
+    accb += __shfl_xor(accb, 32, 64);
+    if (lane == 13) sB[wave] = accb;
+    __syncthreads();
+    float *pb = part + (int64_t)blockIdx.x * 16 * 28;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int i = h * 256 + tid, ln = tid >> 2, t = 16 * h + 4 * (ln >> 4) + (tid & 3), ci = ln & 15;
+        const float s = (sR[0][i] + sR[1][i]) + (sR[2][i] + sR[3][i]);
+        if (t < 27) pb[ci * 28 + t] = s;
+    }
+    if (tid == 0) pb[27] = (sB[0] + sB[1]) + (sB[2] + sB[3]);
 }
 
 int grid1(int64_t n) { return (int)std::min<int64_t>((n + 255) / 256, 65535); }
@@ -838,26 +1209,42 @@ int mx_blocks(int64_t n, int64_t each, int cap) {
 // The factor of vox_fast.
 unsigned vox_magic(int G) { return (unsigned)((1ull << 32) / (unsigned)G + 1); }
 
+// Ranges and blocks of the k_conv*q kernels: as many blocks as stay resident
+// (two per CU for the FP32 ones; with one exchange array and three per CU
+// k_conv_q took 126 instead of 120 us), one share of ranges each.
+int q_ranges(int64_t V, int d) {
+    const int own = kQPos - 2 * d;
+    return (int)((V + own - 1) / own);
+}
+
 template <int CIN, int CP, int COUT>
-int conv_fwd(const float *in, const float *W, const float *b, float *pre, float *post, int G, int d, int relu,
-             hipStream_t st) {
+int conv_fwd(const float *in, const float *W, const float *b, float *post, int G, int d, int relu, hipStream_t st) {
     const int64_t V = (int64_t)G * G * G;
-    const int ntiles = (int)((V + 15) / 16);
-    hipLaunchKernelGGL((k_conv_fwd_mx<CIN, CP, COUT>), dim3(mx_blocks(ntiles, 32, 2048)), dim3(256), 0, st, in, W, b,
-                       pre, post, G, d, relu, ntiles);
+    if (d <= kQMaxD) {
+        const int nr = q_ranges(V, d);
+        if constexpr (COUT == 16)
+            hipLaunchKernelGGL((k_conv_q<CIN, CP, 1>), dim3(mx_blocks(nr, 1, 512)), dim3(256), 0, st, in, W, b, nullptr,
+                               post, G, vox_magic(G), d, relu, nr);
+        else
+            hipLaunchKernelGGL(k_conv_fwd_q1, dim3(mx_blocks(nr, 1, 1024)), dim3(256), 0, st, in, W, b, post, G,
+                               vox_magic(G), d, nr);
+    } else {  // the halo would be too large a part of a range
+        const int ntiles = (int)((V + 15) / 16);
+        hipLaunchKernelGGL((k_conv_fwd_mx<CIN, CP, COUT>), dim3(mx_blocks(ntiles, 32, 2048)), dim3(256), 0, st, in, W, b,
+                           post, G, d, relu, ntiles);
+    }
     BF_HIP(hipGetLastError());
     return 0;
 }
 
 int layer_fwd(bemfft_net *n, int l, const float *in, hipStream_t st) {
     const float *W = n->p + n->woff[l], *b = n->p + n->boff[l];
-    float *pre = n->pre + (int64_t)l * n->width * n->V;
     float *post = n->post + (int64_t)l * n->width * n->V;
     const int relu = l < n->nl - 1;
     const int ci = n->ci[l], co = n->co[l];
-    if (ci == 6 && co == 16) return conv_fwd<6, 8, 16>(in, W, b, pre, post, n->G, n->dil[l], relu, st);
-    if (ci == 16 && co == 16) return conv_fwd<16, 16, 16>(in, W, b, pre, post, n->G, n->dil[l], relu, st);
-    if (ci == 16 && co == 1) return conv_fwd<16, 16, 1>(in, W, b, pre, post, n->G, n->dil[l], relu, st);
+    if (ci == 6 && co == 16) return conv_fwd<6, 8, 16>(in, W, b, post, n->G, n->dil[l], relu, st);
+    if (ci == 16 && co == 16) return conv_fwd<16, 16, 16>(in, W, b, post, n->G, n->dil[l], relu, st);
+    if (ci == 16 && co == 1) return conv_fwd<16, 16, 1>(in, W, b, post, n->G, n->dil[l], relu, st);
     set_error("network: unsupported layer shape");
     return BEMFFT_EUNSUPPORTED;
 }
@@ -874,24 +1261,36 @@ int forward(bemfft_net *n, const float *x, hipStream_t st) {
     return 0;
 }
 
-template <int CIN, int CP, int COUT>
-int bwd_w(const float *g, const float *in, float *part, int G, int d, float *gW, float *gb, hipStream_t st) {
+int bwd_w(const float *g, const float *in, float *part, int cin, int cout, int G, int d, float *gW, float *gb,
+          hipStream_t st) {
     const int64_t V = (int64_t)G * G * G;
-    const int nslabs = (int)((V + kSlab - 1) / kSlab);
-    const int nch = mx_blocks(nslabs, 2, kWgBlocks);
-    hipLaunchKernelGGL((k_conv_bwd_w_mx<CIN, CP, COUT>), dim3(nch, 3), dim3(256), 0, st, g, in, part, G, d, nslabs);
-    const int tot = COUT * CIN * 27 + COUT;
-    hipLaunchKernelGGL(k_conv_w_reduce, dim3((tot + 31) / 32), dim3(256), 0, st, part, nch, CIN, COUT, gW, gb);
+    const int nslabs = (int)((V + kSlab - 1) / kSlab), ntiles = (int)((V + 15) / 16);
+    const int nch = cout == 1 ? mx_blocks(ntiles, 32, kWgBlocks) : mx_blocks(nslabs, 1, kWgBlocks);
+    if (cout == 1)
+        hipLaunchKernelGGL(k_conv_bwd_w1, dim3(nch), dim3(256), 0, st, g, in, part, G, vox_magic(G), d, ntiles);
+    else if (cin == 6)
+        hipLaunchKernelGGL((k_conv_bwd_w<6, 8>), dim3(nch), dim3(256), 0, st, g, in, part, G, vox_magic(G), d, nslabs);
+    else
+        hipLaunchKernelGGL((k_conv_bwd_w<16, 16>), dim3(nch), dim3(256), 0, st, g, in, part, G, vox_magic(G), d,
+                           nslabs);
+    const int tot = cout * cin * 27 + cout;
+    hipLaunchKernelGGL(k_conv_w_reduce, dim3((tot + 31) / 32), dim3(256), 0, st, part, nch, cin, cout, gW, gb);
     BF_HIP(hipGetLastError());
     return 0;
 }
 
-template <int COUT>
-int bwd_d(const float *g, const float *W, const float *prev_pre, float *gin, int G, int d, hipStream_t st) {
+int bwd_d(const float *g, const float *W, const float *prev, float *gin, int cout, int G, int d, hipStream_t st) {
     const int64_t V = (int64_t)G * G * G;
-    const int ntiles = (int)((V + 15) / 16);
-    hipLaunchKernelGGL((k_conv_bwd_data_mx<COUT>), dim3(mx_blocks(ntiles, 32, 2048)), dim3(256), 0, st, g, W, prev_pre,
-                       gin, G, d, ntiles);
+    const int ntiles = (int)((V + 15) / 16), nr = d <= kQMaxD ? q_ranges(V, d) : 0;
+    if (cout == 1)
+        hipLaunchKernelGGL(k_conv_bwd_data1, dim3(mx_blocks(ntiles, 16, 2048)), dim3(256), 0, st, g, W, prev, gin, G,
+                           vox_magic(G), d, ntiles);
+    else if (d <= kQMaxD)
+        hipLaunchKernelGGL((k_conv_q<16, 16, -1>), dim3(mx_blocks(nr, 1, 512)), dim3(256), 0, st, g, W, nullptr, prev,
+                           gin, G, vox_magic(G), d, 0, nr);
+    else
+        hipLaunchKernelGGL(k_conv_bwd_data_mx, dim3(mx_blocks(ntiles, 32, 2048)), dim3(256), 0, st, g, W, prev, gin, G,
+                           d, ntiles);
     BF_HIP(hipGetLastError());
     return 0;
 }
@@ -911,17 +1310,9 @@ int gradients(bemfft_net *n, const float *x, int64_t nt, const int *vox, const f
         const float *in = l == 0 ? n->xcl : n->post + (int64_t)(l - 1) * n->width * n->V;
         float *gW = n->g + n->woff[l], *gb = n->g + n->boff[l];
         const int ci = n->ci[l], co = n->co[l], d = n->dil[l];
-        int s;
-        if (ci == 6 && co == 16) s = bwd_w<6, 8, 16>(gcur, in, n->part, n->G, d, gW, gb, st);
-        else if (ci == 16 && co == 16) s = bwd_w<16, 16, 16>(gcur, in, n->part, n->G, d, gW, gb, st);
-        else s = bwd_w<16, 16, 1>(gcur, in, n->part, n->G, d, gW, gb, st);
-        BF_CHECK(s);
+        BF_CHECK(bwd_w(gcur, in, n->part, ci, co, n->G, d, gW, gb, st));
         if (l > 0) {
-            const float *W = n->p + n->woff[l];
-            const float *prev_pre = n->pre + (int64_t)(l - 1) * n->width * n->V;
-            if (co == 16) s = bwd_d<16>(gcur, W, prev_pre, gnext, n->G, d, st);
-            else s = bwd_d<1>(gcur, W, prev_pre, gnext, n->G, d, st);
-            BF_CHECK(s);
+            BF_CHECK(bwd_d(gcur, n->p + n->woff[l], in, gnext, co, n->G, d, st));
             std::swap(gcur, gnext);
         }
     }
@@ -1051,7 +1442,7 @@ int bemfft_net_create(bemfft_net **out, int grid, int width, int nlayers, const 
     const size_t act = (size_t)nlayers * width * n->V * sizeof(float);
     if (hipMalloc(&n->p, n->nparam * 4) != hipSuccess || hipMalloc(&n->g, n->nparam * 4) != hipSuccess ||
         hipMalloc(&n->m, n->nparam * 4) != hipSuccess || hipMalloc(&n->v, n->nparam * 4) != hipSuccess ||
-        hipMalloc(&n->pre, act) != hipSuccess || hipMalloc(&n->post, act) != hipSuccess ||
+        hipMalloc(&n->post, act) != hipSuccess ||
         hipMalloc(&n->xcl, (size_t)8 * n->V * 4) != hipSuccess ||
         hipMalloc(&n->ga, (size_t)width * n->V * 4) != hipSuccess ||
         hipMalloc(&n->gb, (size_t)width * n->V * 4) != hipSuccess ||
@@ -1078,7 +1469,7 @@ int bemfft_net_create(bemfft_net **out, int grid, int width, int nlayers, const 
 
 int bemfft_net_destroy(bemfft_net *n) {
     if (!n) return 0;
-    for (float *q : {n->p, n->g, n->m, n->v, n->xcl, n->pre, n->post, n->ga, n->gb, n->part, n->red})
+    for (float *q : {n->p, n->g, n->m, n->v, n->xcl, n->post, n->ga, n->gb, n->part, n->red})
         if (q) (void)hipFree(q);
     for (double *q : {n->dq, n->du, n->db, n->sdev})
         if (q) (void)hipFree(q);

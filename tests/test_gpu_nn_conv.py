@@ -46,3 +46,26 @@ def test_infer_edges(dev, G, dil):
     assert np.abs(got - ref).max() <= 1e-2 * np.abs(ref).max()
     assert np.linalg.norm(got - ref) <= 3e-3 * np.linalg.norm(ref)
     net.close()
+
+
+@pytest.mark.parametrize("G,dil", EDGES)
+def test_forward_and_gradients_edges(dev, G, dil):
+    rng, net, p, x = _case(G, dil)
+    xt = torch.tensor(x, device=dev)
+    y = torch.empty(G ** 3, dtype=torch.float32, device=dev)
+    net.forward(xt, y)
+    x3 = x.astype(np.float64).reshape(6, G, G, G)
+    ref = NN.forward(p, list(dil), x3)[0].ravel()
+    assert np.abs(y.cpu().numpy() - ref).max() <= 1e-5 * np.abs(ref).max()
+    nt = G ** 3 // 3
+    vox = rng.choice(G ** 3, size=nt, replace=False).astype(np.int32)
+    tgt = rng.standard_normal(nt).astype(np.float32)
+    wt = (rng.uniform(0.5, 1.5, nt) / nt).astype(np.float32)
+    args = (xt,) + tuple(torch.tensor(a, device=dev) for a in (vox, tgt, wt))
+    L, g = net.gradients(*args)
+    Lr, gr = NN.loss_and_grad(p, list(dil), x3, vox, tgt.astype(np.float64), wt.astype(np.float64))
+    assert abs(L - Lr) <= 1e-5 * abs(Lr)
+    assert np.abs(g - gr).max() <= 2e-4 * np.abs(gr).max()
+    assert np.linalg.norm(g - gr) <= 2e-5 * np.linalg.norm(gr)
+    assert np.array_equal(net.gradients(*args)[1], g)
+    net.close()
