@@ -28,13 +28,15 @@ constexpr int kDenseRow = 24;
 // When no other row holds more than this many nodes, the forward direct DFT
 // takes two kx per thread (each node load serves both; measured on the
 // 128^3 cube: 42 -> 38 us).  Plans with busier short rows keep one kx per
-// thread, whose work per thread is then balanced better (the sphere).
+// thread, whose work per thread is then balanced better (the sphere).  3D plans;
+// a 2D plan's block has one kx.
 constexpr int kFewNodesRow = 4;
 // The long rows' inverse x transform goes through a row FFT (one more launch,
 // a few microseconds) when the per-node sums it replaces exceed this many
 // complex products: the nodes of long rows x Hx x outputs.  Measured: the
 // 128^3 cube (3e6) is faster without it, the 256^2 half-space surface (5e7)
-// 1.4x faster with it.
+// was 1.4x faster with it (2D plans whose nodes all lie in long rows now always
+// take a row FFT, k_rows_gather).
 constexpr double kRowInvWork = 8.0e6;
 
 template <typename T>
@@ -207,6 +209,7 @@ void fill_apply_args(const bemfft_plan *p, const Engine &e, const Engine &ws, Ap
     a.dense_rows = p->d_dense_rows;
     a.nd = (int)p->nd;
     a.row_inv = p->row_inv;
+    a.all_long = p->all_long;
     a.fwd_xg = p->fwd_xg;
     a.zsched = e.zsched;
     a.off = 0;
@@ -222,11 +225,13 @@ int alloc_intermediates(const bemfft_plan *p, int precision, Engine *e) {
     const size_t rows = (size_t)p->H[0] * p->nzo * p->P[1];
     // Y also holds the inverse y pass's rows in the arithmetic precision:
     // O nzo ny Hx complex values, never more than F Hx nzo Py stored ones
-    const size_t ysz = std::max((size_t)p->F * rows * sb, (size_t)p->O * p->nzo * p->n[1] * p->H[0] * cb);
-    const size_t zsz = (size_t)p->O * rows * sb;
+    // (2D plans keep what comes before those in LDS)
+    const bool flat = p->dim == 2;
+    const size_t ysz = std::max(flat ? 0 : (size_t)p->F * rows * sb, (size_t)p->O * p->nzo * p->n[1] * p->H[0] * cb);
+    const size_t zsz = flat ? 0 : (size_t)p->O * rows * sb;
     const size_t vsz = (size_t)p->F * p->m * e->creal;
     const size_t xsz = std::max<size_t>(1, (size_t)p->nd * p->F * p->H[0] * cb);
-    if (hipMalloc(&e->Y, ysz) != hipSuccess || hipMalloc(&e->Z, zsz) != hipSuccess ||
+    if (hipMalloc(&e->Y, ysz) != hipSuccess || (zsz > 0 && hipMalloc(&e->Z, zsz) != hipSuccess) ||
         hipMalloc(&e->vf, vsz) != hipSuccess || hipMalloc(&e->Xd, xsz) != hipSuccess) {
         set_error("hipMalloc of the intermediates failed");
         return BEMFFT_ENOMEM;
@@ -473,6 +478,7 @@ int plan_create_impl(bemfft_plan *p, const bemfft_grid *grid, int64_t m, const d
     {
         int64_t long_nodes = 0;
         for (int r : dense_rows) long_nodes += rowptr[r + 1] - rowptr[r];
+        p->all_long = p->dim == 2 && long_nodes == m;
         p->row_inv = (double)long_nodes * (double)p->H[0] * p->O > kRowInvWork ? 1 : 0;
     }
     // per-node free term and self correction blocks (sorted order)

@@ -19,9 +19,13 @@
 //              (nodes of long rows read their row's inverse FFT, made by
 //              k_rows_inv, instead)
 //
+// 2D plans: k_mid2d takes the place of the first three (one kx per block, no Y
+// and Z), with the fields folded in for few nodes; k_gather_wide or
+// k_rows_gather that of the last where flat_path says so.
+//
 // Layout: complex intermediates are interleaved (re, im) in the working
 // precision R.  Y is tiled for the z pass, [f][kx][ky / KT][z][KT] (the 16-bit
-// form and 2D plans: [f][kx][z][ky]); Z is [o][kx][z][ky].  Kernel spectra
+// form: [f][kx][z][ky]); Z is [o][kx][z][ky].  Kernel spectra
 // are reals over one octant in the order of spec_index (16-bit form:
 // [c][kx][ky][kz]).
 #pragma once
@@ -57,6 +61,7 @@ struct ApplyArgs {
     const int *row_dense;   // [nzo * ny]: index into dense_rows, or -1
     const int *dense_rows;  // [nd]: row index (zz * ny + y) of each long row
     int nd;
+    int all_long;           // 2D: every node lies in a long row
     int row_inv;            // 1: the long rows' inverse x transform is an FFT (k_rows_inv)
     int fwd_xg;             // kx per thread in the forward direct DFT (1 or 2)
     void *Y, *Z;
@@ -69,7 +74,18 @@ struct GroupDims {
     int max_m, max_nd, max_nzo;
     int hx, px, py, pz, zsched;
     int row_inv;  // some member takes the row FFT for its long rows
+    int flat;     // 2D: flat_path of every member
 };
+
+// The 2D kernels that a plan takes, a rule on its nodes (m, nd long rows) so
+// that a batch's members take their own plan's (bit 0: k_mid2d with the fields
+// folded in, bit 1: k_gather_wide, bit 2: k_rows_gather).
+constexpr int kFoldNodes = 4096, kFoldRows = 8, kWideNodes = 8192, kWaveRow = 8;
+constexpr int kFlatFold = 1, kFlatWide = 2, kFlatRows = 4;
+
+inline int flat_path(int64_t m, int64_t nd, int all_long) {
+    return (m <= kFoldNodes && nd <= kFoldRows ? kFlatFold : 0) | (all_long ? kFlatRows : m <= kWideNodes ? kFlatWide : 0);
+}
 
 // Base pointers of a batched apply (device memory, so that a captured graph
 // of the launches serves any call) and the members still iterating.
@@ -109,6 +125,20 @@ __device__ __forceinline__ int mod_small(int kx, int x, int p, float inv_p) {
     if (r >= p) r -= p;
     return r;
 }
+
+// Schedules of the 2D plans' transforms.  Few pencils are in flight and each
+// waits for its own instructions, so more lanes with fewer points each are
+// faster than the bulk schedules (256 points in FP64: 1.8 us at 16 points per
+// lane, 0.9 at 4; 512 in FP32: 1.8 at 16, 1.1 at 8), as far as a pencil stays in one wavefront.
+template <int P> struct FlatShape : PencilShape<P> {};
+template <> struct FlatShape<32> : FFTShape<32, 8, 4, 4, 2> {};
+template <> struct FlatShape<64> : FFTShape<64, 16, 4, 4, 4> {};
+template <> struct FlatShape<128> : FFTShape<128, 32, 4, 4, 4, 2> {};
+template <> struct FlatShape<256> : FFTShape<256, 64, 4, 4, 4, 4> {};
+template <> struct FlatShape<384> : FFTShape<384, 32, 12, 4, 4, 2> {};
+template <> struct FlatShape<512> : FFTShape<512, 64, 8, 8, 8> {};
+template <int P, int KIND>
+using LineShape = std::conditional_t<KIND == 0 || KIND == 3, FlatShape<P>, PencilShape<P>>;
 
 // ------------------------------------------------------------------ k_fields
 // Boundary fields of every node in sorted order (the zero-extended data of
@@ -202,7 +232,8 @@ __device__ __forceinline__ void node_fields(const ApplyArgs &a, const int s, R *
 // transformed; kx < Hx is kept.                          -> Xd[d][f][kx]
 template <typename R, int PX, int KIND>
 struct RowCfg {
-    static constexpr int TPP = PencilShape<PX>::TPP;
+    using SH = LineShape<PX, KIND>;
+    static constexpr int TPP = SH::TPP;
     static constexpr int PPB = 256 / TPP;  // pencils per block
 };
 
@@ -251,7 +282,7 @@ __device__ __forceinline__ void rows_fft_body(const ApplyArgs &a, const int bx, 
         cx<R> xr[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) xr[e] = pb[pslot(t + e * TPP)];
-        fft_regs<R, PX, -1>(xr, pb, tw, t);
+        fft_regs_s<R, typename Cfg::SH, -1>(xr, pb, tw, t);
         if (f < F) {
 #pragma unroll
             for (int e = 0; e < E; ++e) {
@@ -415,8 +446,8 @@ template <typename R, int PY, int KIND, int XG, typename YS>
 __device__ __forceinline__ void fwd_xy_item(const ApplyArgs &a, const int b) {
     constexpr int KXC = FwdCfg<R, PY, KIND>::KXC;
     const int total = (a.hx + KXC - 1) / KXC * a.nzo;
-    // the 16-bit form and 2D plans write whole lines: any order will do
-    constexpr bool WHOLE = KIND == 0 || KIND == 3 || std::is_same<YS, cbf16>::value;
+    // the 16-bit form writes whole lines: any order will do
+    constexpr bool WHOLE = std::is_same<YS, cbf16>::value;
     const int lam = WHOLE ? (b < total ? b : -1) : xcd_item(b, total);
     if (lam < 0) return;
     fwd_xy_body<R, PY, KIND, XG, YS>(a, lam / a.nzo, lam % a.nzo);
@@ -496,15 +527,6 @@ template <typename R>
 __device__ __forceinline__ void buf_store(cx<R> v, __amdgpu_buffer_rsrc_t r, int off) {
     if constexpr (sizeof(R) == 4) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uvec2, v), r, off, 0, 0);
     else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uvec4, v), r, off, 0, 0);
-}
-
-// Kernel spectrum value of a 2D plan for component c at (kx, ky) from the
-// quadrant store, with the reflection sign of an odd y axis.
-template <typename R, int KIND>
-__device__ __forceinline__ R spec_at(const R *spec, const ApplyArgs &a, int c, int kx, int ky) {
-    const int kyp = ky < a.hy ? ky : a.py - ky;
-    const R s = spec[((size_t)c * a.hx + kx) * a.hy + kyp];
-    return (ky >= a.hy) && (comp_oddmask(KIND, c) & 2) ? -s : s;
 }
 
 template <typename R>
@@ -718,44 +740,309 @@ __global__ __launch_bounds__((ZCfg<R, SH, KIND>::NT), 2) void kb_zpass(const App
     zpass_item<R, SH, KIND>(a, blockIdx.x, nby);
 }
 
-// 2D: the third axis has length 1, so the "z pass" is the spectral product.
-template <typename R, int KIND>
-__device__ __forceinline__ void mac2d_body(const ApplyArgs &a, const int bx, const int by, const int bz) {
-    using T = Terms<KIND>;
-    constexpr int O = T::O;
-    const int kx = bx;
-    const int ky = by * 256 + threadIdx.x;
-    if (ky >= a.py) return;
-    const cx<R> *Y = static_cast<const cx<R> *>(a.Y);
-    cx<R> *Z = static_cast<cx<R> *>(a.Z);
+// ------------------------------------------------------------------ k_mid2d
+// 2D plans: everything between the fields and W for one kx, in one block.  The
+// F fields' columns at a kx fit in LDS together, so the y FFT, the spectral
+// product and the inverse y FFT follow each other there (x[e] of lane t is
+// ky = t + e TPP throughout) and only W is written: the forward pass, the
+// product and the inverse y pass as kernels of their own took 18.8 + 8.6 +
+// 12.1 us for the 500-point square in FP64 and 7.8 + 3.6 + 7.7 us for a 256^2
+// half-space surface in FP32, against 21.7 and 8.7 us.  All of them are bound by
+// latency (a few loads that wait for each other, barriers), so the block has
+// more threads than the pencils need -- every row of the direct DFT gets its own
+// as far as possible --, the rows' extents and the spectra are loaded before
+// anything waits, and a row's nodes are fetched four at a time.
+//
+// FOLD: the node data come from q and u directly and rows of more than kWaveRow
+// nodes are summed by their wavefront (one round of loads instead of a chain of
+// them; long rows always, others unless a wavefront has many), which saves the launch before (fields and long-row
+// transforms, 7.9 us on the square).  Each block then reads every node's data,
+// so this is for few nodes and few long rows (flat_path).
+template <typename R, int PY, int KIND>
+struct Mid2dCfg {
+    static constexpr int F = Terms<KIND>::F, O = Terms<KIND>::O;
+    using SH = FlatShape<PY>;
+    static constexpr int TPP = SH::TPP, E = SH::E, PS = pstride<PY>();
+    // threads: one per grid row up to 256, at least one per pencil lane
+    static constexpr int NT = clampi((PY / 2 + 63) / 64 * 64, (F * TPP + 63) / 64 * 64, 256);
+    // 1024 points in FP64: without a twiddle table in LDS three blocks fit on a
+    // CU, and all 513 of them on the chip at once (with it, two: 512)
+    static constexpr bool TWL = PY * sizeof(cx<R>) < 16384;
+    static constexpr int WPE = KIND == 0 && PY == 1024 ? 3 : 1;  // wavefronts per SIMD that the registers must allow
+    static_assert(F * TPP <= NT && O <= F, "a thread for every pencil lane");
+};
+
+// Component of the term (output o, field f): O = 1 has one per field.
+template <int KIND>
+__device__ __forceinline__ int term_comp2d(int o, int f) {
+    if constexpr (Terms<KIND>::O == 1) return f;
+    else {
+        static_assert(KIND != 3 || (Terms<3>::c(0) == 0 && Terms<3>::c(1) == 2 && Terms<3>::c(2) == 4 && Terms<3>::c(3) == 2 &&
+                                    Terms<3>::c(4) == 1 && Terms<3>::c(5) == 5 && Terms<3>::c(6) == 6 && Terms<3>::c(7) == 7 &&
+                                    Terms<3>::c(8) == 3));
+        return (int)((0x376512420ull >> (4 * (3 * o + f))) & 15);  // the table, four bits each
+    }
+}
+
+template <typename R, int PY, int KIND, bool FOLD>
+__device__ __forceinline__ void mid2d_body(const ApplyArgs &a, const int kx, const int all_rows) {
+    using Cfg = Mid2dCfg<R, PY, KIND>;
+    constexpr int F = Cfg::F, O = Cfg::O, TPP = Cfg::TPP, E = Cfg::E, PS = Cfg::PS, NT = Cfg::NT;
+    using SH = typename Cfg::SH;
+    constexpr int NS = O == 1 ? 1 : F;              // spectra per thread
+    constexpr int NR = (PY / 2 + NT - 1) / NT;      // grid rows per thread
+    constexpr int CH = NR > 1 ? 2 : 8;              // nodes of a row fetched together
+    constexpr int WS = NR > 1 ? 1 : 2, WC = 2;      // and rows of the wavefront's, nodes per lane
+    __shared__ cx<R> buf[F * PS];
+    __shared__ cx<R> twl[Cfg::TWL ? PY : 1];
+    __shared__ unsigned char keep[PY / 2];
+    const int tid = threadIdx.x, pen = tid / TPP, t = tid % TPP;
+    const cx<R> *gtwx = static_cast<const cx<R> *>(a.twx);
+    const cx<R> *gtwy = static_cast<const cx<R> *>(a.twy);
+    const R *vf = static_cast<const R *>(a.vf);
+    const cx<R> *Xd = static_cast<const cx<R> *>(a.Xd);
     const R *spec = static_cast<const R *>(a.spec);
-    cx<R> acc[O];
+    if constexpr (Cfg::TWL)
+        for (int i = tid; i < PY; i += NT) twl[i] = gtwy[i];
+    // the rows' extents and this lane's spectra
+    int dn[NR], r0[NR], r1[NR];
 #pragma unroll
-    for (int o = 0; o < O; ++o) acc[o] = {R(0), R(0)};
-    static_for<0, T::N>([&](auto tc) {
-        constexpr int term = decltype(tc)::value;
-        constexpr int c = T::c(term), o = T::o(term), f = T::f(term);
-        const cx<R> v = Y[(size_t)(f * a.hx + kx) * a.py + ky];
-        mac<R>(acc[o], v, spec_at<R, KIND>(spec, a, c, kx, ky), comp_imag(KIND, c));
-    });
+    for (int k = 0; k < NR; ++k) {
+        const int y = tid + k * NT;
+        const bool in = y < a.ny;
+        dn[k] = in ? a.row_dense[y] : -1;
+        r0[k] = in ? a.rowptr[y] : 0;
+        r1[k] = in ? a.rowptr[y + 1] : 0;
+    }
+    R sp[NS][E];
+    bool im[NS];
+    if (pen < F) {
 #pragma unroll
-    for (int o = 0; o < O; ++o) Z[(size_t)(o * a.hx + kx) * a.py + ky] = acc[o];
+        for (int n = 0; n < NS; ++n) {
+            const int c = O == 1 ? pen : term_comp2d<KIND>(pen, n);  // O > 1: O = F, pencil = output
+            const int odd = comp_oddmask(KIND, c);
+            im[n] = comp_imag(KIND, c);
+            const R *sc = spec + ((size_t)c * a.hx + kx) * a.hy;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const int ky = t + e * TPP;
+                const R v = sc[ky < a.hy ? ky : PY - ky];
+                sp[n][e] = ky >= a.hy && (odd & 2) ? -v : v;
+            }
+        }
+    }
+    if constexpr (Cfg::TWL) __syncthreads();
+    // x transform at kx of every row's nodes
+    const float inv_px = 1.0f / (float)a.px;
+    // C nodes s, s + stride, ... below s1, with their twiddles, fetched together
+    auto fetch = [&](auto cc, const cx<R> *twt, int s, int stride, int s1, cx<R> *w, R (*v)[F]) {
+        constexpr int C = decltype(cc)::value;
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            const bool in = s + k * stride < s1;
+            const int sk = in ? s + k * stride : 0;
+            w[k] = twt[mod_small(kx, a.gx[sk], a.px, inv_px)];
+            if constexpr (FOLD) {
+                node_fields<R, KIND>(a, sk, v[k]);
+            } else {
+#pragma unroll
+                for (int f = 0; f < F; ++f) v[k][f] = vf[f * a.m + sk];
+            }
+#pragma unroll
+            for (int f = 0; f < F; ++f) v[k][f] = in ? v[k][f] : R(0);
+        }
+    };
+    auto add = [&](auto cc, const cx<R> *w, const R (*v)[F], cx<R> *acc) {
+        constexpr int C = decltype(cc)::value;
+#pragma unroll
+        for (int k = 0; k < C; ++k)
+#pragma unroll
+            for (int f = 0; f < F; ++f) {
+                acc[f].x += v[k][f] * w[k].x;
+                acc[f].y += v[k][f] * w[k].y;
+            }
+    };
+    constexpr std::integral_constant<int, CH> ch;
+    constexpr std::integral_constant<int, WC> wc;
+    auto x_rows = [&](const cx<R> *twt) {
+        // the first CH nodes, or the long row's transform, of all of the thread's
+        // rows together, and the first nodes of the rows that the wavefront sums
+        cx<R> w[NR][CH];
+        R v[NR][CH][F];
+        cx<R> acc[NR][F];
+        bool wide[NR];
+        const int lane = tid & 63;
+        int wsrc[WS], wk[WS], ws0[WS], ws1[WS];
+        cx<R> wx[WS][WC];
+        R wv[WS][WC][F];
+        unsigned long long todo[NR];
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            const bool dense = !FOLD && dn[k] >= 0;
+            if (!FOLD && __any(dense)) {
+#pragma unroll
+                for (int f = 0; f < F; ++f) acc[k][f] = dense ? Xd[((size_t)dn[k] * F + f) * a.hx + kx] : cx<R>{R(0), R(0)};
+                if (dense) r1[k] = r0[k];  // nothing left to sum
+            } else {
+#pragma unroll
+                for (int f = 0; f < F; ++f) acc[k][f] = {R(0), R(0)};
+            }
+            if (FOLD || __any(r1[k] > r0[k])) fetch(ch, twt, r0[k], 1, r1[k], w[k], v[k]);
+            if constexpr (FOLD) {
+                wide[k] = r1[k] - r0[k] > kWaveRow;
+                if (__popcll(__ballot(wide[k])) > 4) wide[k] = dn[k] >= 0;
+                todo[k] = __ballot(wide[k]);
+            }
+        }
+        auto next = [&](int &k, int &src, int &s0, int &s1) {  // next row of the wavefront's: false if none
+            k = 0;
+            if constexpr (NR > 1) k = todo[0] ? 0 : 1;
+            if (!todo[k]) return false;
+            src = __ffsll((long long)todo[k]) - 1;
+            todo[k] &= todo[k] - 1;
+            s0 = __shfl(r0[k], src, 64);
+            s1 = __shfl(r1[k], src, 64);
+            return true;
+        };
+        auto finish = [&](const cx<R> (&part)[F], int k, int src) {
+            cx<R> sum[F];
+#pragma unroll
+            for (int f = 0; f < F; ++f) sum[f] = part[f];
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+                for (int f = 0; f < F; ++f) {
+                    sum[f].x += __shfl_xor(sum[f].x, off, 64);
+                    sum[f].y += __shfl_xor(sum[f].y, off, 64);
+                }
+            if (lane == src)
+#pragma unroll
+                for (int f = 0; f < F; ++f) buf[f * PS + pslot(tid + k * NT)] = sum[f];
+        };
+        auto rest = [&](int s, int s1, cx<R> (&part)[F]) {
+            cx<R> lx[WC];
+            R lv[WC][F];
+            for (; s - lane < s1; s += WC * 64) {
+                fetch(wc, twt, s, 64, s1, lx, lv);
+                add(wc, lx, lv, part);
+            }
+        };
+        if constexpr (FOLD) {
+            bool on[WS];
+#pragma unroll
+            for (int i = 0; i < WS; ++i) {
+                on[i] = next(wk[i], wsrc[i], ws0[i], ws1[i]);
+                if (on[i]) fetch(wc, twt, ws0[i] + lane, 64, ws1[i], wx[i], wv[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < WS; ++i)
+                if (on[i]) {
+                    cx<R> part[F];
+#pragma unroll
+                    for (int f = 0; f < F; ++f) part[f] = {R(0), R(0)};
+                    add(wc, wx[i], wv[i], part);
+                    rest(ws0[i] + lane + WC * 64, ws1[i], part);
+                    finish(part, wk[i], wsrc[i]);
+                }
+            int k, src, s0, s1;
+            while (next(k, src, s0, s1)) {
+                cx<R> part[F];
+#pragma unroll
+                for (int f = 0; f < F; ++f) part[f] = {R(0), R(0)};
+                rest(s0 + lane, s1, part);
+                finish(part, k, src);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            const int y = tid + k * NT, n = r1[k] - r0[k];
+            if (y >= a.ny) continue;
+            keep[y] = all_rows || n > 0 || dn[k] >= 0;
+            if (FOLD && wide[k]) continue;
+            if (n > 0) {
+                add(ch, w[k], v[k], acc[k]);
+                for (int s = r0[k] + CH; s < r1[k]; s += CH) {
+                    fetch(ch, twt, s, 1, r1[k], w[k], v[k]);
+                    add(ch, w[k], v[k], acc[k]);
+                }
+            }
+#pragma unroll
+            for (int f = 0; f < F; ++f) buf[f * PS + pslot(y)] = acc[k][f];
+        }
+    };
+    if constexpr (Cfg::TWL) {
+        if (a.px == PY) x_rows(twl);  // the same table
+        else x_rows(gtwx);
+    } else {
+        x_rows(gtwx);
+    }
+    __syncthreads();
+    cx<R> *pb = buf + pen * PS;
+    const cx<R> *tw;
+    if constexpr (Cfg::TWL) tw = twl;
+    else tw = gtwy;
+    cx<R> x[E];
+    if (pen < F) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int y = t + e * TPP;  // rows y >= PY / 2 lie beyond the grid
+            x[e] = (e < E / 2 && y < a.ny) ? pb[pslot(y)] : cx<R>{R(0), R(0)};
+        }
+        fft_regs_s<R, SH, -1>(x, pb, tw, t);
+        wave_lds_sync();
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            if constexpr (O == 1) x[e] = im[0] ? cx<R>{-sp[0][e] * x[e].y, sp[0][e] * x[e].x} : cx<R>{sp[0][e] * x[e].x, sp[0][e] * x[e].y};
+            pb[pslot(t + e * TPP)] = x[e];
+        }
+    }
+    __syncthreads();
+    if (pen < O) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            cx<R> acc = {R(0), R(0)};
+#pragma unroll
+            for (int f = 0; f < F; ++f) {
+                const cx<R> v = buf[f * PS + pslot(t + e * TPP)];
+                if constexpr (O == 1) acc = {acc.x + v.x, acc.y + v.y};
+                else mac<R>(acc, v, sp[f % NS][e], im[f % NS]);
+            }
+            x[e] = acc;
+        }
+    }
+    if constexpr (O > 1) __syncthreads();  // every pencil's readers
+    if (pen < O) {
+        fft_regs_s<R, SH, 1>(x, pb, tw, t);
+        wave_lds_sync();
+#pragma unroll
+        for (int e = 0; e < E / 2; ++e) {
+            const int y = t + e * TPP;
+            if (y < a.ny) pb[pslot(y)] = x[e];
+        }
+    }
+    __syncthreads();
+    cx<R> *W = static_cast<cx<R> *>(a.Y);
+#pragma unroll
+    for (int o = 0; o < O; ++o)
+        for (int y = tid; y < a.ny; y += NT)
+            if (keep[y]) W[((size_t)o * a.ny + y) * a.hx + kx] = buf[o * PS + pslot(y)];
 }
 
-template <typename R, int KIND>
-__global__ __launch_bounds__(256) void k_mac2d(ApplyArgs a) {
-    mac2d_body<R, KIND>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+// kx in runs per XCD: its L2 joins the columns' 8- or 16-byte parts of W's lines.
+template <typename R, int PY, int KIND, bool FOLD>
+__global__ __launch_bounds__((Mid2dCfg<R, PY, KIND>::NT), (Mid2dCfg<R, PY, KIND>::WPE)) void k_mid2d(ApplyArgs a, int all_rows) {
+    const int kx = xcd_item(blockIdx.x, a.hx);
+    if (kx >= 0) mid2d_body<R, PY, KIND, FOLD>(a, kx, all_rows);
 }
 
-// Batched form: blockIdx.z = member * zdiv + the kernel's own z index.
-template <typename R, int KIND>
-__global__ __launch_bounds__(256) void kb_mac2d(const ApplyArgs *members, const BatchIO *io, int zdiv) {
-    ApplyArgs a = members[blockIdx.z / zdiv];
+template <typename R, int PY, int KIND, bool FOLD>
+__global__ __launch_bounds__((Mid2dCfg<R, PY, KIND>::NT), (Mid2dCfg<R, PY, KIND>::WPE)) void kb_mid2d(const ApplyArgs *members, const BatchIO *io) {
+    ApplyArgs a = members[blockIdx.z];
     if (io->active && !io->active[a.gid]) return;
     a.q = io->q + a.off;
     a.u = io->u + a.off;
-    a.r = io->r + a.off;
-    mac2d_body<R, KIND>(a, blockIdx.x, blockIdx.y, blockIdx.z % zdiv);
+    const int kx = xcd_item(blockIdx.x, a.hx);
+    if (kx >= 0) mid2d_body<R, PY, KIND, FOLD>(a, kx, 0);
 }
 
 // ------------------------------------------------------------------ k_inv_y
@@ -847,10 +1134,10 @@ struct RowInvCfg {
 // length PX holds row a in its real and row b in its imaginary part.  Lane t
 // of the pencil ends with x[e] = value at t + e TPP.  tw: the LDS twiddle
 // table, already synchronised.
-template <typename R, int PX>
-__device__ __forceinline__ void inv_x_pair(const cx<R> *Wa, const cx<R> *Wb, bool va, bool vb, cx<R> *pen,
-                                           const cx<R> *tw, int t, cx<R> (&x)[PX / PencilShape<PX>::TPP]) {
-    constexpr int TPP = PencilShape<PX>::TPP, E = PX / TPP;
+template <typename R, typename SH>
+__device__ __forceinline__ void inv_x_load(const cx<R> *Wa, const cx<R> *Wb, bool va, bool vb, int t,
+                                           cx<R> (&x)[SH::E]) {
+    constexpr int PX = SH::P, TPP = SH::TPP, E = SH::E;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int k = t + e * TPP;
@@ -868,6 +1155,11 @@ __device__ __forceinline__ void inv_x_pair(const cx<R> *Wa, const cx<R> *Wb, boo
         }
         x[e] = {A.x - B.y, A.y + B.x};  // A + iB
     }
+}
+template <typename R, int PX>
+__device__ __forceinline__ void inv_x_pair(const cx<R> *Wa, const cx<R> *Wb, bool va, bool vb, cx<R> *pen,
+                                           const cx<R> *tw, int t, cx<R> (&x)[PX / PencilShape<PX>::TPP]) {
+    inv_x_load<R, PencilShape<PX>>(Wa, Wb, va, vb, t, x);
     fft_regs<R, PX, 1>(x, pen, tw, t);
 }
 
@@ -1018,7 +1310,186 @@ __global__ __launch_bounds__(256) void k_gather(ApplyArgs a) {
     gather_body<R, KIND>(a, blockIdx.x);
 }
 
-// Batched form: blockIdx.z = member.
+// Free term of sorted node s: c u - (exact - grid) self term q, per output.
+template <int O>
+__device__ __forceinline__ void free_term(const ApplyArgs &a, const int s, const int j, double *b) {
+    double u[O], q[O];
+#pragma unroll
+    for (int l = 0; l < O; ++l) {
+        u[l] = a.u[l * a.m + j];
+        q[l] = a.q[l * a.m + j];
+    }
+#pragma unroll
+    for (int o = 0; o < O; ++o) {
+        b[o] = 0.0;
+#pragma unroll
+        for (int l = 0; l < O; ++l) {
+            b[o] += a.C[((size_t)s * O + o) * O + l] * u[l];
+            b[o] -= a.SC[((size_t)s * O + o) * O + l] * q[l];
+        }
+    }
+}
+
+// As k_gather for 2D plans of few nodes, where eight lanes per node leave most
+// of the chip idle and a lane with a long chain: L lanes per node, so that one
+// round of eight coefficients per lane covers the row, the twiddles straight
+// from the table (no staging, no barrier) and the free term's loads ahead of the
+// sum.  2000 nodes of a 500 x 500 square in FP64: 9.2 -> 4.7 us.
+template <typename R, int KIND, int L>
+__device__ __forceinline__ void gather_wide_body(const ApplyArgs &a, const int bx) {
+    constexpr int O = Terms<KIND>::O;
+    const int sub = threadIdx.x % L;
+    const int s = bx * (256 / L) + threadIdx.x / L;
+    if (s >= a.m) return;  // the node's lanes leave together
+    const int y = a.gy[s], xg = a.gx[s], j = a.perm[s];
+    const int dr = a.row_inv ? a.row_dense[y] : -1;
+    double b[O];
+    free_term<O>(a, s, j, b);
+    if (dr >= 0) {  // a long row: its values come from the row FFT
+        const R *Xr = static_cast<const R *>(a.Xd);
+        if (sub == 0)
+#pragma unroll
+            for (int o = 0; o < O; ++o) a.r[o * a.m + j] = (double)Xr[((size_t)dr * O + o) * a.nx + xg] + b[o];
+        return;
+    }
+    const int hx = a.hx, px = a.px;
+    const float inv_px = 1.0f / (float)px;
+    const size_t rstride = (size_t)a.ny * hx;  // between outputs
+    const cx<R> *row = static_cast<const cx<R> *>(a.Y) + (size_t)y * hx;
+    const cx<R> *twx = static_cast<const cx<R> *>(a.twx);
+    cx<R> v0[O], vn[O];
+    double acc[O];
+#pragma unroll
+    for (int o = 0; o < O; ++o) {
+        v0[o] = row[o * rstride];
+        vn[o] = row[o * rstride + hx - 1];
+        acc[o] = 0.0;
+    }
+    for (int kx = 1 + sub; kx < hx - 1; kx += 8 * L) {
+        cx<R> v[8][O], w[8];
+        R mk[8];  // zero past the row's end, where coefficient 1 stands in
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const bool in = kx + k * L < hx - 1;
+            const int kc = in ? kx + k * L : 1;
+            mk[k] = in ? R(1) : R(0);
+            w[k] = twx[mod_small(kc, xg, px, inv_px)];
+#pragma unroll
+            for (int o = 0; o < O; ++o) v[k][o] = row[o * rstride + kc];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+#pragma unroll
+            for (int o = 0; o < O; ++o) acc[o] += (double)((v[k][o].x * w[k].x + v[k][o].y * w[k].y) * mk[k]);
+    }
+#pragma unroll
+    for (int off = L / 2; off > 0; off >>= 1)
+#pragma unroll
+        for (int o = 0; o < O; ++o) acc[o] += __shfl_xor(acc[o], off, 64);
+    if (sub != 0) return;
+    const R wn = (xg & 1) ? R(-1) : R(1);  // exp(i pi x)
+#pragma unroll
+    for (int o = 0; o < O; ++o) a.r[o * a.m + j] = ((double)v0[o].x + (double)(vn[o].x * wn) + 2.0 * acc[o]) + b[o];
+}
+
+template <typename R, int KIND, int L>
+__global__ __launch_bounds__(256) void k_gather_wide(ApplyArgs a) {
+    gather_wide_body<R, KIND, L>(a, blockIdx.x);
+}
+
+template <typename R, int KIND, int L>
+__global__ __launch_bounds__(256) void kb_gather_wide(const ApplyArgs *members, const BatchIO *io) {
+    ApplyArgs a = members[blockIdx.z];
+    if (io->active && !io->active[a.gid]) return;
+    a.q = io->q + a.off;
+    a.u = io->u + a.off;
+    a.r = io->r + a.off;
+    gather_wide_body<R, KIND, L>(a, blockIdx.x);
+}
+
+// 2D plans whose nodes all lie in long rows (a whole loaded surface): inverse x
+// transform of one row's outputs and its nodes' results in one block, without
+// the row's values going through memory.  256^2 half-space
+// surface in FP32: k_rows_inv 6.6 + k_gather 12.6 us -> 10.1 us.
+template <typename R, int PX, int KIND>
+__device__ __forceinline__ void rows_gather_body(const ApplyArgs &a, const int d) {
+    using SH = LineShape<PX, KIND>;
+    constexpr int O = Terms<KIND>::O, TPP = SH::TPP, PS = pstride<PX>(), E = SH::E;
+    constexpr int NP = (O + 1) / 2;  // two outputs per pencil
+    static_assert(NP * TPP <= 256, "a thread for every pencil lane");
+    __shared__ cx<R> buf[NP * PS];
+    __shared__ cx<R> tw[PX];
+    const int tid = threadIdx.x;
+    if (d >= a.nd) return;  // block-uniform: batched members with fewer rows
+    const cx<R> *gtwx = static_cast<const cx<R> *>(a.twx);
+    for (int i = tid; i < PX; i += 256) tw[i] = gtwx[i];
+    const int y = a.dense_rows[d];
+    const int s0 = a.rowptr[y], s1 = a.rowptr[y + 1];
+    const int pen = tid / TPP, t = tid % TPP;
+    cx<R> x[E];
+    if (pen < NP) {
+        const cx<R> *W = static_cast<const cx<R> *>(a.Y) + (size_t)y * a.hx;
+        const size_t ostride = (size_t)a.ny * a.hx;
+        const bool vb = 2 * pen + 1 < O;
+        inv_x_load<R, SH>(W + 2 * pen * ostride, W + (2 * pen + (vb ? 1 : 0)) * ostride, true, vb, t, x);
+    }
+    // items (node, output), outputs fastest: neighbouring lanes read neighbouring
+    // parts of the 72 bytes of a node's blocks.  The first O items of a thread
+    // (all of a row of 256 nodes): their loads run beside the transform's.
+    const int i0 = s0 * O + tid, i1 = s1 * O;
+    double b[O];
+    int j[O], xg[O];
+    auto item = [&](int i, double &bi, int &ji, int &xi) {
+        const int s = i / O, o = i % O;
+        ji = a.perm[s];
+        xi = a.gx[s];
+        bi = 0.0;
+#pragma unroll
+        for (int l = 0; l < O; ++l) {
+            bi += a.C[(size_t)i * O + l] * a.u[l * a.m + ji];
+            bi -= a.SC[(size_t)i * O + l] * a.q[l * a.m + ji];
+        }
+        ji += o * a.m;
+    };
+#pragma unroll
+    for (int k = 0; k < O; ++k)
+        if (i0 + 256 * k < i1) item(i0 + 256 * k, b[k], j[k], xg[k]);
+    __syncthreads();
+    if (pen < NP) {
+        fft_regs_s<R, SH, 1>(x, buf + pen * PS, tw, t);
+        wave_lds_sync();
+#pragma unroll
+        for (int e = 0; e < E / 2; ++e) buf[pen * PS + pslot(t + e * TPP)] = x[e];
+    }
+    __syncthreads();
+    auto value = [&](int i, int xi) {
+        const cx<R> v = buf[i % O / 2 * PS + pslot(xi)];
+        return (double)(i % O % 2 ? v.y : v.x);
+    };
+#pragma unroll
+    for (int k = 0; k < O; ++k)
+        if (i0 + 256 * k < i1) a.r[j[k]] = value(i0 + 256 * k, xg[k]) + b[k];
+    for (int i = i0 + 256 * O; i < i1; i += 256) {
+        item(i, b[0], j[0], xg[0]);
+        a.r[j[0]] = value(i, xg[0]) + b[0];
+    }
+}
+
+template <typename R, int PX, int KIND>
+__global__ __launch_bounds__(256) void k_rows_gather(ApplyArgs a) {
+    rows_gather_body<R, PX, KIND>(a, blockIdx.x);
+}
+
+template <typename R, int PX, int KIND>
+__global__ __launch_bounds__(256) void kb_rows_gather(const ApplyArgs *members, const BatchIO *io) {
+    ApplyArgs a = members[blockIdx.z];
+    if (io->active && !io->active[a.gid]) return;
+    a.q = io->q + a.off;
+    a.u = io->u + a.off;
+    a.r = io->r + a.off;
+    rows_gather_body<R, PX, KIND>(a, blockIdx.x);
+}
+
 template <typename R, int KIND>
 __global__ __launch_bounds__(256) void kb_gather(const ApplyArgs *members, const BatchIO *io) {
     ApplyArgs a = members[blockIdx.z];
@@ -1049,20 +1520,15 @@ int launch_inv_y(const ApplyArgs &a, int all_rows, hipStream_t st) {
 }
 template <typename R, int PZ, int KIND, int SCHED>
 int launch_z(const ApplyArgs &a, hipStream_t st) {
-    if constexpr (PZ == 1) {
-        dim3 grid(a.hx, (a.py + 255) / 256);
-        hipLaunchKernelGGL((k_mac2d<R, KIND>), grid, dim3(256), 0, st, a);
-    } else {
-        using SH = ZSched<R, KIND, PZ, SCHED>;
-        using Cfg = ZCfg<R, SH, KIND>;
-        if (a.py % Cfg::TY != 0 || 2 * a.nzo > PZ + 1) {
-            set_error("z pass: y length or planes do not fit the schedule");
-            return BEMFFT_EUNSUPPORTED;
-        }
-        const int nby = a.py / Cfg::TY;
-        const int per = (a.hx * nby + 7) / 8;  // xcd_item
-        hipLaunchKernelGGL((k_zpass<R, SH, KIND>), dim3(8 * per), dim3(Cfg::NT), 0, st, a, nby);
+    using SH = ZSched<R, KIND, PZ, SCHED>;
+    using Cfg = ZCfg<R, SH, KIND>;
+    if (a.py % Cfg::TY != 0 || 2 * a.nzo > PZ + 1) {
+        set_error("z pass: y length or planes do not fit the schedule");
+        return BEMFFT_EUNSUPPORTED;
     }
+    const int nby = a.py / Cfg::TY;
+    const int per = (a.hx * nby + 7) / 8;  // xcd_item
+    hipLaunchKernelGGL((k_zpass<R, SH, KIND>), dim3(8 * per), dim3(Cfg::NT), 0, st, a, nby);
     BF_HIP(hipGetLastError());
     return 0;
 }
@@ -1091,10 +1557,11 @@ int launch_z(const ApplyArgs &a, hipStream_t st) {
 
 template <typename R, int KIND>
 struct Launch {
+    static constexpr bool FLAT = KIND == 0 || KIND == 3;  // 2D plans
     template <int P> static int fwd(const ApplyArgs &a, hipStream_t st) { return launch_fwd<R, P, KIND>(a, st); }
     template <int P> static int rows(const ApplyArgs &a, hipStream_t st) {
         using Cfg = RowCfg<R, P, KIND>;
-        const int nfb = (a.m + 255) / 256;
+        const int nfb = a.all_long ? 0 : (a.m + 255) / 256;  // long rows take q and u themselves
         const int nrb = a.nd;  // one block per long row
         hipLaunchKernelGGL((k_fields_rows<R, P, KIND>), dim3(nfb + nrb), dim3(256), 0, st, a, nfb);
         BF_HIP(hipGetLastError());
@@ -1129,31 +1596,117 @@ struct Launch {
         return a.zsched == 1 ? launch_z<R, P, KIND, 1>(a, st) : launch_z<R, P, KIND, 0>(a, st);
     }
 
-    // Fields, forward x/y and the z pass: everything up to Z.  ev (optional):
-    // events 0-2 recorded around the two stages.
-    static int front(const ApplyArgs &a, hipStream_t st, hipEvent_t *ev = nullptr) {
+    // Everything up to W.  all_rows: W of every row y < ny (the grid
+    // evaluation), not only of those that hold nodes (the apply).  ev (optional):
+    // events 0-3 recorded around the three stages; 2D plans have one between
+    // the fields and W, counted as the second.
+    static int front(const ApplyArgs &a, int all_rows, hipStream_t st, hipEvent_t *ev = nullptr) {
         if (ev) BF_HIP(hipEventRecord(ev[0], st));
-        if (a.nd > 0) {
-            BF_CHECK(dispatch_rows(a, st));  // fields and long-row transforms, one launch
+        if constexpr (FLAT) {
+            const bool fold = flat_path(a.m, a.nd, a.all_long) & kFlatFold;
+            if (!fold) BF_CHECK(a.nd > 0 ? dispatch_rows(a, st) : fields(a, st));
+            if (ev) BF_HIP(hipEventRecord(ev[1], st));
+            BF_CHECK(dispatch_mid(a, fold, all_rows, st));
+            if (ev) BF_HIP(hipEventRecord(ev[2], st));
         } else {
-            BF_CHECK(fields(a, st));
+            if (a.nd > 0) {
+                BF_CHECK(dispatch_rows(a, st));  // fields and long-row transforms, one launch
+            } else {
+                BF_CHECK(fields(a, st));
+            }
+            BF_CHECK(dispatch_fwd(a, st));
+            if (ev) BF_HIP(hipEventRecord(ev[1], st));
+            BF_CHECK(dispatch_z(a, st));
+            if (ev) BF_HIP(hipEventRecord(ev[2], st));
+            BF_CHECK(dispatch_inv_y(a, all_rows, st));
         }
-        BF_CHECK(dispatch_fwd(a, st));
-        if (ev) BF_HIP(hipEventRecord(ev[1], st));
-        BF_CHECK(dispatch_z(a, st));
-        if (ev) BF_HIP(hipEventRecord(ev[2], st));
+        if (ev) BF_HIP(hipEventRecord(ev[3], st));
         return 0;
     }
 
     // ev (optional): five events recorded around the four stages.
     static int run(const ApplyArgs &a, hipStream_t st, hipEvent_t *ev = nullptr) {
-        BF_CHECK(front(a, st, ev));
-        BF_CHECK(dispatch_inv_y(a, 0, st));
-        if (ev) BF_HIP(hipEventRecord(ev[3], st));
-        if (a.nd > 0 && a.row_inv) BF_CHECK(dispatch_rows_inv(a, st));
-        BF_CHECK(gather(a, st));
+        BF_CHECK(front(a, 0, st, ev));
+        BF_CHECK(back(a, st));
         if (ev) BF_HIP(hipEventRecord(ev[4], st));
         return 0;
+    }
+    // W -> r
+    static int back(const ApplyArgs &a, hipStream_t st) {
+        const int flat = FLAT ? flat_path(a.m, a.nd, a.all_long) : 0;
+        if constexpr (FLAT) {
+            if (flat & kFlatRows) return dispatch_rows_gather(a, st);
+        }
+        if (a.nd > 0 && a.row_inv) BF_CHECK(dispatch_rows_inv(a, st));
+        if constexpr (FLAT) {
+            if (flat & kFlatWide)
+                return a.px >= 1024 ? gather_wide<64>(a, st) : a.px >= 512 ? gather_wide<32>(a, st) : gather_wide<16>(a, st);
+        }
+        return gather(a, st);
+    }
+    template <int L> static int gather_wide(const ApplyArgs &a, hipStream_t st) {
+        constexpr int NPB = 256 / L;  // nodes per block
+        hipLaunchKernelGGL((k_gather_wide<R, KIND, L>), dim3((a.m + NPB - 1) / NPB), dim3(256), 0, st, a);
+        BF_HIP(hipGetLastError());
+        return 0;
+    }
+    template <int P> static int rows_gather(const ApplyArgs &a, hipStream_t st) {
+        hipLaunchKernelGGL((k_rows_gather<R, P, KIND>), dim3(a.nd), dim3(256), 0, st, a);
+        BF_HIP(hipGetLastError());
+        return 0;
+    }
+    static int dispatch_rows_gather(const ApplyArgs &a, hipStream_t st) {
+        BF_SIZE_SWITCH_K(KIND, a.px, rows_gather, a, st);
+        set_error("unsupported x length");
+        return BEMFFT_EUNSUPPORTED;
+    }
+    template <int L>
+    static int bgather_wide(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, hipStream_t st) {
+        constexpr int NPB = 256 / L;
+        hipLaunchKernelGGL((kb_gather_wide<R, KIND, L>), dim3((g.max_m + NPB - 1) / NPB, 1, g.nmem), dim3(256), 0, st, dm,
+                           io);
+        BF_HIP(hipGetLastError());
+        return 0;
+    }
+    template <int P>
+    static int brows_gather(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, hipStream_t st) {
+        hipLaunchKernelGGL((kb_rows_gather<R, P, KIND>), dim3(g.max_nd, 1, g.nmem), dim3(256), 0, st, dm, io);
+        BF_HIP(hipGetLastError());
+        return 0;
+    }
+    static int dispatch_brows_gather(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, hipStream_t st) {
+        BF_SIZE_SWITCH_K(KIND, g.px, brows_gather, dm, io, g, st);
+        set_error("unsupported x length");
+        return BEMFFT_EUNSUPPORTED;
+    }
+    template <int P> static int mid(const ApplyArgs &a, bool fold, int all_rows, hipStream_t st) {
+        const dim3 grid(8 * ((a.hx + 7) / 8)), block(Mid2dCfg<R, P, KIND>::NT);
+        if (fold) hipLaunchKernelGGL((k_mid2d<R, P, KIND, true>), grid, block, 0, st, a, all_rows);
+        else hipLaunchKernelGGL((k_mid2d<R, P, KIND, false>), grid, block, 0, st, a, all_rows);
+        BF_HIP(hipGetLastError());
+        return 0;
+    }
+    static int dispatch_mid(const ApplyArgs &a, bool fold, int all_rows, hipStream_t st) {
+        if (a.pz != 1) {
+            set_error("2D plans need pz == 1");
+            return BEMFFT_EUNSUPPORTED;
+        }
+        BF_SIZE_SWITCH_K(KIND, a.py, mid, a, fold, all_rows, st);
+        set_error("unsupported y length");
+        return BEMFFT_EUNSUPPORTED;
+    }
+    template <int P>
+    static int bmid(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, bool fold, hipStream_t st) {
+        const dim3 grid(8 * ((g.hx + 7) / 8), 1, g.nmem), block(Mid2dCfg<R, P, KIND>::NT);
+        if (fold) hipLaunchKernelGGL((kb_mid2d<R, P, KIND, true>), grid, block, 0, st, dm, io);
+        else hipLaunchKernelGGL((kb_mid2d<R, P, KIND, false>), grid, block, 0, st, dm, io);
+        BF_HIP(hipGetLastError());
+        return 0;
+    }
+    static int dispatch_bmid(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, bool fold, hipStream_t st) {
+        BF_SIZE_SWITCH_K(KIND, g.py, bmid, dm, io, g, fold, st);
+        set_error("unsupported y length");
+        return BEMFFT_EUNSUPPORTED;
     }
     static int fields(const ApplyArgs &a, hipStream_t st) {
         hipLaunchKernelGGL((k_fields<R, KIND>), dim3((a.m + 255) / 256), dim3(256), 0, st, a);
@@ -1167,7 +1720,7 @@ struct Launch {
         return 0;
     }
     static int dispatch_fwd(const ApplyArgs &a, hipStream_t st) {
-        BF_SIZE_SWITCH_K(KIND, a.py, fwd, a, st);
+        BF_SIZE_SWITCH(a.py, fwd, a, st);
         set_error("unsupported y length");
         return BEMFFT_EUNSUPPORTED;
     }
@@ -1195,16 +1748,11 @@ struct Launch {
     }
     template <int PZ, int SCHED>
     static int bz_s(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, hipStream_t st) {
-        if constexpr (PZ == 1) {
-            dim3 grid(g.hx, (g.py + 255) / 256, g.nmem);
-            hipLaunchKernelGGL((kb_mac2d<R, KIND>), grid, dim3(256), 0, st, dm, io, 1);
-        } else {
-            using SH = ZSched<R, KIND, PZ, SCHED>;
-            using Cfg = ZCfg<R, SH, KIND>;
-            const int nby = g.py / Cfg::TY;
-            dim3 grid(8 * ((g.hx * nby + 7) / 8), 1, g.nmem);
-            hipLaunchKernelGGL((kb_zpass<R, SH, KIND>), grid, dim3(Cfg::NT), 0, st, dm, io, nby);
-        }
+        using SH = ZSched<R, KIND, PZ, SCHED>;
+        using Cfg = ZCfg<R, SH, KIND>;
+        const int nby = g.py / Cfg::TY;
+        dim3 grid(8 * ((g.hx * nby + 7) / 8), 1, g.nmem);
+        hipLaunchKernelGGL((kb_zpass<R, SH, KIND>), grid, dim3(Cfg::NT), 0, st, dm, io, nby);
         BF_HIP(hipGetLastError());
         return 0;
     }
@@ -1214,98 +1762,54 @@ struct Launch {
         }
         return g.zsched == 1 ? bz_s<P, 1>(dm, io, g, st) : bz_s<P, 0>(dm, io, g, st);
     }
+    static int dispatch_brows(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, hipStream_t st) {
+        BF_SIZE_SWITCH_K(KIND, g.px, brows, dm, io, g, st);
+        set_error("unsupported x length");
+        return BEMFFT_EUNSUPPORTED;
+    }
+    static int dispatch_bfwd(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, hipStream_t st) {
+        BF_SIZE_SWITCH(g.py, bfwd, dm, io, g, st);
+        set_error("unsupported y length");
+        return BEMFFT_EUNSUPPORTED;
+    }
+    static int dispatch_bz(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, hipStream_t st) {
+        BF_SIZE_SWITCH(g.pz, bz, dm, io, g, st);
+        set_error("unsupported z length");
+        return BEMFFT_EUNSUPPORTED;
+    }
+    static int dispatch_binv(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, hipStream_t st) {
+        BF_SIZE_SWITCH(g.py, binv, dm, io, g, st);
+        set_error("unsupported y length");
+        return BEMFFT_EUNSUPPORTED;
+    }
+    static int dispatch_brows_inv(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, hipStream_t st) {
+        BF_SIZE_SWITCH_K(KIND, g.px, brows_inv, dm, io, g, st);
+        set_error("unsupported x length");
+        return BEMFFT_EUNSUPPORTED;
+    }
     static int run_batch(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, hipStream_t st) {
-        hipLaunchKernelGGL((kb_fields<R, KIND>), dim3((g.max_m + 255) / 256, 1, g.nmem), dim3(256), 0, st, dm, io, 1);
-        BF_HIP(hipGetLastError());
-        if (g.max_nd > 0) {
-            int s2 = BEMFFT_EUNSUPPORTED;
-            if constexpr (KIND == 0 || KIND == 3) {
-                if (g.px == 1024) s2 = brows<1024>(dm, io, g, st);
-            }
-            switch (g.px) {
-                case 32: s2 = brows<32>(dm, io, g, st); break;
-                case 64: s2 = brows<64>(dm, io, g, st); break;
-                case 96: s2 = brows<96>(dm, io, g, st); break;
-                case 128: s2 = brows<128>(dm, io, g, st); break;
-                case 192: s2 = brows<192>(dm, io, g, st); break;
-                case 256: s2 = brows<256>(dm, io, g, st); break;
-                case 320: s2 = brows<320>(dm, io, g, st); break;
-                case 384: s2 = brows<384>(dm, io, g, st); break;
-                case 512: s2 = brows<512>(dm, io, g, st); break;
-                default: break;
-            }
-            BF_CHECK(s2);
+        const bool fold = FLAT && (g.flat & kFlatFold);
+        if (!fold) {
+            hipLaunchKernelGGL((kb_fields<R, KIND>), dim3((g.max_m + 255) / 256, 1, g.nmem), dim3(256), 0, st, dm, io, 1);
+            BF_HIP(hipGetLastError());
+            if (g.max_nd > 0) BF_CHECK(dispatch_brows(dm, io, g, st));
         }
-        int s3 = BEMFFT_EUNSUPPORTED;
-        if constexpr (KIND == 0 || KIND == 3) {
-            if (g.py == 1024) s3 = bfwd<1024>(dm, io, g, st);
-        }
-        switch (g.py) {
-            case 32: s3 = bfwd<32>(dm, io, g, st); break;
-            case 64: s3 = bfwd<64>(dm, io, g, st); break;
-            case 96: s3 = bfwd<96>(dm, io, g, st); break;
-            case 128: s3 = bfwd<128>(dm, io, g, st); break;
-            case 192: s3 = bfwd<192>(dm, io, g, st); break;
-            case 256: s3 = bfwd<256>(dm, io, g, st); break;
-            case 320: s3 = bfwd<320>(dm, io, g, st); break;
-            case 384: s3 = bfwd<384>(dm, io, g, st); break;
-            case 512: s3 = bfwd<512>(dm, io, g, st); break;
-            default: break;
-        }
-        BF_CHECK(s3);
-        int s4 = BEMFFT_EUNSUPPORTED;
-        if constexpr (KIND == 0 || KIND == 3) {
-            if (g.pz == 1) s4 = bz_s<1, 0>(dm, io, g, st);
+        if constexpr (FLAT) {
+            BF_CHECK(dispatch_bmid(dm, io, g, fold, st));
         } else {
-            switch (g.pz) {
-                case 32: s4 = bz<32>(dm, io, g, st); break;
-                case 64: s4 = bz<64>(dm, io, g, st); break;
-                case 96: s4 = bz<96>(dm, io, g, st); break;
-                case 128: s4 = bz<128>(dm, io, g, st); break;
-                case 192: s4 = bz<192>(dm, io, g, st); break;
-                case 256: s4 = bz<256>(dm, io, g, st); break;
-                case 320: s4 = bz<320>(dm, io, g, st); break;
-                case 384: s4 = bz<384>(dm, io, g, st); break;
-                case 512: s4 = bz<512>(dm, io, g, st); break;
-                default: break;
-            }
+            BF_CHECK(dispatch_bfwd(dm, io, g, st));
+            BF_CHECK(dispatch_bz(dm, io, g, st));
+            BF_CHECK(dispatch_binv(dm, io, g, st));
         }
-        BF_CHECK(s4);
-        int s5 = BEMFFT_EUNSUPPORTED;
-        if constexpr (KIND == 0 || KIND == 3) {
-            if (g.py == 1024) s5 = binv<1024>(dm, io, g, st);
+        if constexpr (FLAT) {
+            if (g.flat & kFlatRows) return dispatch_brows_gather(dm, io, g, st);
         }
-        switch (g.py) {
-            case 32: s5 = binv<32>(dm, io, g, st); break;
-            case 64: s5 = binv<64>(dm, io, g, st); break;
-            case 96: s5 = binv<96>(dm, io, g, st); break;
-            case 128: s5 = binv<128>(dm, io, g, st); break;
-            case 192: s5 = binv<192>(dm, io, g, st); break;
-            case 256: s5 = binv<256>(dm, io, g, st); break;
-            case 320: s5 = binv<320>(dm, io, g, st); break;
-            case 384: s5 = binv<384>(dm, io, g, st); break;
-            case 512: s5 = binv<512>(dm, io, g, st); break;
-            default: break;
-        }
-        BF_CHECK(s5);
-        if (g.max_nd > 0 && g.row_inv) {
-            int s6 = BEMFFT_EUNSUPPORTED;
-            if constexpr (KIND == 0 || KIND == 3) {
-                if (g.px == 1024) s6 = brows_inv<1024>(dm, io, g, st);
-            }
-            switch (g.px) {
-                case 32: s6 = brows_inv<32>(dm, io, g, st); break;
-                case 64: s6 = brows_inv<64>(dm, io, g, st); break;
-                case 96: s6 = brows_inv<96>(dm, io, g, st); break;
-                case 128: s6 = brows_inv<128>(dm, io, g, st); break;
-                case 192: s6 = brows_inv<192>(dm, io, g, st); break;
-                case 256: s6 = brows_inv<256>(dm, io, g, st); break;
-                case 320: s6 = brows_inv<320>(dm, io, g, st); break;
-                case 384: s6 = brows_inv<384>(dm, io, g, st); break;
-                case 512: s6 = brows_inv<512>(dm, io, g, st); break;
-                default: break;
-            }
-            BF_CHECK(s6);
+        if (g.max_nd > 0 && g.row_inv) BF_CHECK(dispatch_brows_inv(dm, io, g, st));
+        if constexpr (FLAT) {
+            if (g.flat & kFlatWide)
+                return g.px >= 1024  ? bgather_wide<64>(dm, io, g, st)
+                       : g.px >= 512 ? bgather_wide<32>(dm, io, g, st)
+                                     : bgather_wide<16>(dm, io, g, st);
         }
         constexpr int NPB = 256 / kGatherLanes;  // nodes per block
         hipLaunchKernelGGL((kb_gather<R, KIND>), dim3((g.max_m + NPB - 1) / NPB, 1, g.nmem), dim3(256), 0, st, dm, io);
@@ -1318,23 +1822,15 @@ struct Launch {
         set_error("unsupported x length");
         return BEMFFT_EUNSUPPORTED;
     }
-    // all_rows: store every row y < ny (the grid evaluation), not only those
-    // that hold nodes (the apply)
     static int dispatch_inv_y(const ApplyArgs &a, int all_rows, hipStream_t st) {
-        BF_SIZE_SWITCH_K(KIND, a.py, inv_y, a, all_rows, st);
+        BF_SIZE_SWITCH(a.py, inv_y, a, all_rows, st);
         set_error("unsupported y length");
         return BEMFFT_EUNSUPPORTED;
     }
     static int dispatch_z(const ApplyArgs &a, hipStream_t st) {
-        if constexpr (KIND == 0 || KIND == 3) {
-            if (a.pz == 1) return launch_z<R, 1, KIND, 0>(a, st);
-            set_error("2D plans need pz == 1");
-            return BEMFFT_EUNSUPPORTED;
-        } else {
-            BF_SIZE_SWITCH(a.pz, z, a, st);
-            set_error("unsupported z length");
-            return BEMFFT_EUNSUPPORTED;
-        }
+        BF_SIZE_SWITCH(a.pz, z, a, st);
+        set_error("unsupported z length");
+        return BEMFFT_EUNSUPPORTED;
     }
 };
 

@@ -387,16 +387,17 @@ int bemfft_batch_create(bemfft_batch **out, bemfft_plan *const *plans, int nplan
     for (int k = 0; k < nm && status == 0; ++k)
         status = alloc_intermediates(plans[b->mem_plan[k]], b->precision, &b->ws[k]);
     // groups
-    std::map<std::tuple<int64_t, int64_t, int64_t, int>, int> gidx;
+    std::map<std::tuple<int64_t, int64_t, int64_t, int, int>, int> gidx;
     for (int k = 0; k < nm && status == 0; ++k) {
         bemfft_plan *p = plans[b->mem_plan[k]];
-        auto key = std::make_tuple(p->P[0], p->P[1], p->P[2], p->zsched);
+        const int flat = p->dim == 2 ? flat_path(p->m, p->nd, p->all_long) : 0;
+        auto key = std::make_tuple(p->P[0], p->P[1], p->P[2], p->zsched, flat);
         auto it = gidx.find(key);
         if (it == gidx.end()) {
             Group g;
             g.kernel = b->kernel;
             g.precision = b->precision;
-            g.dims = GroupDims{0, 0, 0, 0, (int)p->H[0], (int)p->P[0], (int)p->P[1], (int)p->P[2], p->zsched, 0};
+            g.dims = GroupDims{0, 0, 0, 0, (int)p->H[0], (int)p->P[0], (int)p->P[1], (int)p->P[2], p->zsched, 0, flat};
             gidx[key] = (int)b->groups.size();
             b->groups.push_back(g);
             it = gidx.find(key);

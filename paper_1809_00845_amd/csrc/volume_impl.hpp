@@ -74,11 +74,11 @@ struct VolumeLaunch {
     // ev (optional): four events recorded around the three stages (front,
     // inverse y, inverse x).
     static int run(const ApplyArgs &a, double *out, hipStream_t st, hipEvent_t *ev) {
-        if (ev) BF_HIP(hipEventRecord(ev[0], st));
-        BF_CHECK((Launch<R, KIND>::front(a, st, nullptr)));
-        if (ev) BF_HIP(hipEventRecord(ev[1], st));
-        BF_CHECK((Launch<R, KIND>::dispatch_inv_y(a, 1, st)));
-        if (ev) BF_HIP(hipEventRecord(ev[2], st));
+        // front()'s first two stages count as one (the second record of ev[1] stands)
+        hipEvent_t fe[4];
+        if (ev)
+            for (int i = 0; i < 4; ++i) fe[i] = ev[i < 2 ? i : i - 1];
+        BF_CHECK((Launch<R, KIND>::front(a, 1, st, ev ? fe : nullptr)));
         BF_CHECK(dispatch_x(a, out, st));
         if (ev) BF_HIP(hipEventRecord(ev[3], st));
         return 0;
