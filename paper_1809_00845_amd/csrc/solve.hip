@@ -406,15 +406,15 @@ int wait_step_flag(const uint64_t *flag, uint64_t seq, hipStream_t st) {
         if ((spins & 0x3fff) == 0) {
             const hipError_t q = hipStreamQuery(st);
             if (q != hipSuccess && q != hipErrorNotReady) {
-                set_error(std::string("GMRES: stream error while waiting: ") + hipGetErrorString(q));
+                set_error(std::string("solve: stream error while waiting: ") + hipGetErrorString(q));
                 return BEMFFT_EDEVICE;
             }
             if (q == hipSuccess && __atomic_load_n(flag, __ATOMIC_ACQUIRE) != seq) {
-                set_error("GMRES: the stream drained without the step's completion flag");
+                set_error("solve: the stream drained without the step's completion flag");
                 return BEMFFT_EDEVICE;
             }
             if (std::chrono::steady_clock::now() - t0 > std::chrono::seconds(120)) {
-                set_error("GMRES: timed out waiting for a step");
+                set_error("solve: timed out waiting for a step");
                 return BEMFFT_EDEVICE;
             }
         }
@@ -466,6 +466,9 @@ int ensure_workspace(bemfft_plan *p, int restart, Ws &ws) {
             set_error("GMRES workspace allocation failed");
             return BEMFFT_ENOMEM;
         }
+        // the allocator may hand out a buffer of an earlier plan, whose completion
+        // flags would hold this plan's first numbers
+        std::fill_n(p->h_pinned, 4 * 512, 0.0);
     }
     ws.V = p->s_V;
     ws.cap = p->s_cap;
@@ -810,6 +813,89 @@ __global__ void k_cg_dir(const double *sc, int cur, double *pv, const double *z,
         pv[i] = z[i] + beta * pv[i];
 }
 
+// Everything of a CG iteration but the apply, for up to kCgNodes unknowns: one
+// block, VPT unknowns per thread, in registers from the first sum to the last.
+// Ap = -W^1/2 (apply's result), p.Ap, the step, the new r.z and r.r, the new
+// direction p and the next apply's input q = W^-1/2 p (u stays zero).  As kernels
+// of their own (two scalings, three sums in two kernels each, the step and the
+// direction) these were seven launches of 2 to 4 us each, all of it launch and
+// load latency: 2000 unknowns, 18.5 -> 6.4 us.  sc[0]: r.z; sc[3]: set once the
+// host will stop (converged, p.Ap not positive, residual not finite), after
+// which a queued iteration changes nothing.  post: r.r, p.Ap and the same mark
+// for the host (pinned), then the iteration's number at flag.
+constexpr int kCgNodes = 8192;
+
+__device__ __forceinline__ double block_sum(double v, double *sm) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if (threadIdx.x % 64 == 0) sm[threadIdx.x / 64] = v;
+    __syncthreads();
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s += sm[i];
+    return s;
+}
+
+template <int VPT>
+__global__ __launch_bounds__(1024) void k_cg_iter(const double *av, const double *sw, const double *dinv, double *x,
+                                                  double *r, double *pv, double *q, int n, double *sc, double tol,
+                                                  double bn, double *post, uint64_t *flag, uint64_t seq) {
+    __shared__ double sm[3][16];
+    double ap[VPT], p[VPT], w[VPT], di[VPT], ri[VPT], xi[VPT];
+    const double rz0 = sc[0], done = sc[3];
+#pragma unroll
+    for (int k = 0; k < VPT; ++k) {
+        const int i = threadIdx.x + 1024 * k;
+        const bool in = i < n;
+        w[k] = in ? sw[i] : 1.0;
+        ap[k] = in ? av[i] : 0.0;
+        p[k] = in ? pv[i] : 0.0;
+        di[k] = in ? dinv[i] : 0.0;
+        ri[k] = in ? r[i] : 0.0;
+        xi[k] = in ? x[i] : 0.0;
+    }
+    if (done != 0.0) return;
+    double pap = 0.0, rz = 0.0, rr = 0.0;
+#pragma unroll
+    for (int k = 0; k < VPT; ++k) {
+        ap[k] = -1.0 * w[k] * ap[k];
+        pap += p[k] * ap[k];
+    }
+    pap = block_sum(pap, sm[0]);
+    const double alpha = rz0 / pap;
+#pragma unroll
+    for (int k = 0; k < VPT; ++k) {
+        xi[k] += alpha * p[k];
+        ri[k] -= alpha * ap[k];
+        ap[k] = di[k] * ri[k];  // z
+        if (threadIdx.x + 1024 * k < n) {
+            rz += ri[k] * ap[k];
+            rr += ri[k] * ri[k];
+        }
+    }
+    rz = block_sum(rz, sm[1]);
+    rr = block_sum(rr, sm[2]);
+    const double beta = rz / rz0;
+#pragma unroll
+    for (int k = 0; k < VPT; ++k) {
+        const int i = threadIdx.x + 1024 * k;
+        if (i >= n) continue;
+        const double d = ap[k] + beta * p[k];
+        x[i] = xi[k];
+        r[i] = ri[k];
+        pv[i] = d;
+        q[i] = d / w[k];
+    }
+    if (threadIdx.x == 0) {
+        const double stop = !(pap > 0.0) || !isfinite(rr) || sqrt(rr) / bn <= tol ? 1.0 : 0.0;
+        sc[0] = rz;
+        sc[3] = stop;
+        post[1] = pap;
+        post[2] = stop;
+        post_step(post, rr, flag, seq);
+    }
+}
+
 // Av = W^1/2 S W^-1/2 v through one apply of the plan's working precision
 int cg_op(bemfft_plan *p, const double *v, const double *sw, Ws &ws, double *av, hipStream_t st) {
     const int64_t n = p->m;
@@ -1109,36 +1195,74 @@ extern "C" int bemfft_solve_cg(bemfft_plan *p, const double *u, double *q, const
                        dinv, r, z, pv, n, ws.red);
     hipLaunchKernelGGL(k_mdot_final, dim3(2), dim3(64), 0, st, ws.red, kRedBlocks, 2, sc, 0);
     BF_HIP(hipGetLastError());
-    int cur = 0;
-    for (;;) {
-        BF_HIP(hipMemcpyAsync(hp, sc, 8 * sizeof(double), hipMemcpyDeviceToHost, st));
-        BF_HIP(hipStreamSynchronize(st));
-        const double rr = hp[4 * cur + 1];
-        if (iters > 0 && !(hp[4 * (cur ^ 1) + 2] > 0.0)) {
+    // r.r and p.Ap after 'iters' iterations: true if the solve ends here
+    auto ends = [&](double rr, double pap) {
+        if (iters > 0 && !(pap > 0.0)) {
             status = BEMFFT_EBREAKDOWN;
             set_error("solve_cg: p.Ap <= 0 (the symmetrised operator is not positive definite)");
-            break;
+            return true;
         }
         if (!std::isfinite(rr)) {
             status = BEMFFT_EBREAKDOWN;
             set_error("solve_cg: non-finite residual");
-            break;
+            return true;
         }
         rel = bn > 0.0 ? std::sqrt(rr) / bn : 0.0;
-        if (rel <= o.tol || bn == 0.0) break;
+        if (rel <= o.tol || bn == 0.0) return true;
         if (iters >= o.maxit) {
             status = BEMFFT_ENOCONV;
-            break;
+            return true;
         }
-        // one iteration: Ap, p.Ap into slot cur, the step into slot cur^1, the new direction
-        BF_CHECK(cg_op(p, pv, sw, ws, ap, st));
-        BF_CHECK(mdot(pv, n, 1, ap, n, ws.red, sc + 4 * cur + 2, 0, st));
-        hipLaunchKernelGGL(k_cg_step, dim3(kRedBlocks), dim3(256), 0, st, sc, cur, x, r, z, pv, ap, dinv, n, ws.red);
-        hipLaunchKernelGGL(k_mdot_final, dim3(2), dim3(64), 0, st, ws.red, kRedBlocks, 2, sc + 4 * (cur ^ 1), 0);
-        hipLaunchKernelGGL(k_cg_dir, dim3(grid_for(n)), dim3(256), 0, st, sc, cur, pv, z, n);
-        BF_HIP(hipGetLastError());
-        cur ^= 1;
-        ++iters;
+        return false;
+    };
+    BF_HIP(hipMemsetAsync(sc + 3, 0, sizeof(double), st));
+    BF_HIP(hipMemcpyAsync(hp, sc, 8 * sizeof(double), hipMemcpyDeviceToHost, st));
+    BF_HIP(hipStreamSynchronize(st));
+    const bool small = n <= kCgNodes;
+    if (ends(hp[1], 0.0)) {
+    } else if (small) {
+        // iteration k + 1 is queued before the host looks at iteration k, so the
+        // device does not wait for the host (it stops itself, k_cg_iter)
+        const uint64_t seq0 = p->s_seq;
+        p->s_seq += (uint64_t)o.maxit + 1;
+        uint64_t *flag = reinterpret_cast<uint64_t *>(hp + 1023);
+        auto queue = [&](int k) -> int {
+            BF_CHECK(launch_apply(p, p->eng, ws.q, ws.u, ap, st));
+            auto go = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(1), dim3(1024), 0, st, ap, sw, dinv, x, r, pv, ws.q, (int)n, sc, o.tol, bn,
+                                   hp + 4 * (k & 1), flag + 1024 * (k & 1), seq0 + (uint64_t)k + 1);
+            };
+            if (n <= 1024) go(k_cg_iter<1>);
+            else if (n <= 2048) go(k_cg_iter<2>);
+            else if (n <= 4096) go(k_cg_iter<4>);
+            else go(k_cg_iter<8>);
+            BF_HIP(hipGetLastError());
+            return 0;
+        };
+        hipLaunchKernelGGL(k_cg_in, dim3(grid_for(n)), dim3(256), 0, st, pv, sw, ws.q, ws.u, n);
+        BF_CHECK(queue(0));
+        for (;;) {
+            if (iters + 1 < o.maxit) BF_CHECK(queue(iters + 1));
+            const int k = iters++;
+            BF_CHECK(wait_step_flag(flag + 1024 * (k & 1), seq0 + (uint64_t)k + 1, st));
+            const double *h = hp + 4 * (k & 1);
+            if (ends(h[0], h[1]) || h[2] != 0.0) break;  // the device's mark decides at the last bit
+        }
+    } else {
+        int cur = 0;
+        do {
+            // one iteration: Ap, p.Ap into slot cur, the step into slot cur^1, the new direction
+            BF_CHECK(cg_op(p, pv, sw, ws, ap, st));
+            BF_CHECK(mdot(pv, n, 1, ap, n, ws.red, sc + 4 * cur + 2, 0, st));
+            hipLaunchKernelGGL(k_cg_step, dim3(kRedBlocks), dim3(256), 0, st, sc, cur, x, r, z, pv, ap, dinv, n, ws.red);
+            hipLaunchKernelGGL(k_mdot_final, dim3(2), dim3(64), 0, st, ws.red, kRedBlocks, 2, sc + 4 * (cur ^ 1), 0);
+            hipLaunchKernelGGL(k_cg_dir, dim3(grid_for(n)), dim3(256), 0, st, sc, cur, pv, z, n);
+            BF_HIP(hipGetLastError());
+            cur ^= 1;
+            ++iters;
+            BF_HIP(hipMemcpyAsync(hp, sc, 8 * sizeof(double), hipMemcpyDeviceToHost, st));
+            BF_HIP(hipStreamSynchronize(st));
+        } while (!ends(hp[4 * cur + 1], hp[4 * (cur ^ 1) + 2]));
     }
     // q = W^-1/2 x; true residual ||b - A x|| / ||b|| with a fresh apply
     if (status >= 0) {
