@@ -445,12 +445,15 @@ __device__ __forceinline__ void fwd_xy_body(const ApplyArgs &a, const int bx, co
 template <typename R, int PY, int KIND, int XG, typename YS>
 __device__ __forceinline__ void fwd_xy_item(const ApplyArgs &a, const int b) {
     constexpr int KXC = FwdCfg<R, PY, KIND>::KXC;
-    const int total = (a.hx + KXC - 1) / KXC * a.nzo;
-    // the 16-bit form writes whole lines: any order will do
-    constexpr bool WHOLE = std::is_same<YS, cbf16>::value;
-    const int lam = WHOLE ? (b < total ? b : -1) : xcd_item(b, total);
-    if (lam < 0) return;
-    fwd_xy_body<R, PY, KIND, XG, YS>(a, lam / a.nzo, lam % a.nzo);
+    const int nkx = (a.hx + KXC - 1) / KXC, total = nkx * a.nzo;
+    if constexpr (std::is_same<YS, cbf16>::value) {
+        // the 16-bit form writes whole lines: kx groups fastest, which share a
+        // plane's nodes
+        if (b < total) fwd_xy_body<R, PY, KIND, XG, YS>(a, b % nkx, b / nkx);
+    } else {
+        const int lam = xcd_item(b, total);
+        if (lam >= 0) fwd_xy_body<R, PY, KIND, XG, YS>(a, lam / a.nzo, lam % a.nzo);
+    }
 }
 
 template <typename R, int PY, int KIND, int XG, typename YS = cx<R>>

@@ -31,9 +31,7 @@
 // Short pencils (N2 < 16) share a tile side by side with block-diagonal
 // second-stage matrices; long ones (N2 > 16) span two column tiles.
 //
-// A block owns PPB pencils of consecutive ky at one kx; the first occupied
-// plane is row 0 of a pencil (a shift of all planes does not change a
-// convolution).  Rows of Y are read
+// A block owns PPB pencils of consecutive ky at one kx.  Rows of Y are read
 // from HBM as 16-byte runs of 4 pencils into an LDS staging tile (one field
 // at a time, the next field's loads in flight meanwhile), and each wavefront
 // reads its pencils' tiles from there; outputs go back through the same kind
@@ -277,7 +275,7 @@ __device__ __forceinline__ void zpass16_body(const ApplyArgs &a, const int kx, c
     for (int i = tid; i < P; i += NT) tw[i] = twz[i];
     for (int i = tid; i < HALF * LS; i += NT) {
         const int z = i / LS;
-        if (z >= a.nzo) stg[i] = 0u;
+        if (z < a.z0 || z >= a.z0 + a.nzo) stg[i] = 0u;
     }
     __syncthreads();
     zop_fill<P, KIND>(ops, tw);
@@ -316,7 +314,7 @@ __device__ __forceinline__ void zpass16_body(const ApplyArgs &a, const int kx, c
             const int it = tid + k * NT;
             if (it < nrun) {
                 const int zz = it / QPR, q = it % QPR;
-                unsigned *row = stg + (size_t)zz * LS + 4 * q;
+                unsigned *row = stg + (size_t)(a.z0 + zz) * LS + 4 * q;
                 row[0] = pre[k][0];
                 row[1] = pre[k][1];
                 row[2] = pre[k][2];
@@ -446,7 +444,7 @@ __device__ __forceinline__ void zpass16_body(const ApplyArgs &a, const int kx, c
         unsigned *Zo = Z + (size_t)o * fstride;
         for (int it = tid; it < nrun; it += NT) {
             const int zz = it / QPR, q = it % QPR;
-            const unsigned *row = stg + (size_t)zz * LS + 4 * q;
+            const unsigned *row = stg + (size_t)(a.z0 + zz) * LS + 4 * q;
             u32x4 v;
             v[0] = row[0];
             v[1] = row[1];
