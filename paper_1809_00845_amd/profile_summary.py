@@ -33,7 +33,8 @@ from collections import defaultdict
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-APPLY_SOURCES = ["apply_impl.hpp", "fft_device.hpp", "kinds.hpp", "internal.hpp", "apply_l3d.hip", "apply_l2d.hip",
+APPLY_SOURCES = ["apply_impl.hpp", "fft_device.hpp", "zsched.hpp", "kinds.hpp", "internal.hpp", "apply_l3d.hip",
+                 "apply_l3d_f32.hip", "apply_l3d_f64.hip", "apply_l2d.hip", "apply_hs.hip", "apply_nav_f32.hip", "apply_nav_f64.hip",
                  "apply_nav.hip", "api.hip"]
 COPY_BYTES = 256 * 1024 * 1024
 
