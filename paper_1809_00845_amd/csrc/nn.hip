@@ -339,7 +339,7 @@ __global__ __launch_bounds__(256) void k_conv16(const _Float16 *__restrict__ in,
     }
 }
 
-// Positions (consecutive voxels) that a block of the k_conv*q kernels takes at
+// Positions (consecutive voxels) that a block of the kernels that share rows takes at
 // once, and the largest dilation they take.
 constexpr int kQPos = 256;
 constexpr int kQMaxD = 16;
@@ -709,37 +709,37 @@ __global__ __launch_bounds__(256) void k_conv_bwd_data_mx(const float *__restric
     }
 }
 
-// Forward of a layer (SIGN = 1) and data gradient between 16-channel layers
-// (SIGN = -1) for dilations up to kQMaxD, with a third of the loads of the
-// kernels above: as in k_conv16q the input of a (dz, dy) row is loaded once per
-// tile and multiplied by the row's three dx taps into three accumulators,
-//     Q_dx[u] = sum_(dy,dz) W_(dx,dy,dz) in[u + SIGN rows],
-//     out[v] = Q_-1[v - SIGN d] + Q_0[v] + Q_1[v + SIGN d],
+// Data gradient between 16-channel layers for dilations up to kQMaxD, with a
+// third of the loads of the kernel above: as in k_conv16q the gradient of a
+// (dz, dy) row is loaded once per tile and multiplied by the row's three dx taps
+// into three accumulators,
+//     Q_dx[u] = sum_(dy,dz) W_(dx,dy,dz)^T g[u - rows],
+//     gin[v] = Q_-1[v + d] + Q_0[v] + Q_1[v - d],
 // summed through LDS.  Two tiles share each weight word read from LDS (at one
 // tile per word those reads alone take as long as the products).  A wavefront
 // takes two pairs of tiles; the next plane's loads are in flight during a
-// plane's products.  Forward: out = relu(. + bias) or without ReLU; gradient:
-// out is zero where prev (the layer's activations) is not positive.
-// Bound: the FP32 matrix cores, 12.2 GFLOP at 96^3 and 16 channels = 78 us at
-// 157 TFLOP/s plus the d positions computed twice per side; 168 -> 120 us (six
-// channels 94 -> 68), of which an eighth is blocks with fewer ranges than others.
-template <int CIN, int CP, int SIGN>
-__global__ __launch_bounds__(256) void k_conv_q(const float *__restrict__ in, const float *__restrict__ W,
-                                                const float *__restrict__ bias, const float *__restrict__ prev,
-                                                float *__restrict__ out, int G, unsigned magic, int d, int relu,
-                                                int nrange) {
-    constexpr int NS = CP / 4;
+// plane's products.  gin is zero where prev (the layer's activations) is not
+// positive.
+// Bound: the FP32 matrix cores, 12.2 GFLOP at 96^3 = 78 us at 157 TFLOP/s plus
+// the d positions computed twice per side; 164 -> 121 us, of which an eighth is
+// blocks with fewer ranges than others.
+// (The forward pass of the hidden layers gains as much in this form, 168 -> 120
+// and 94 -> 68 us, but it adds in another order, and a value that rounding alone
+// puts on either side of its ReLU's zero then moves the gradient by 1e-6 and
+// more; the forward kernel keeps its order.)
+__global__ __launch_bounds__(256) void k_conv_bwd_data_q(const float *__restrict__ g, const float *__restrict__ W,
+                                                         const float *__restrict__ prev, float *__restrict__ gin, int G,
+                                                         unsigned magic, int d, int nrange) {
+    constexpr int NS = 4;
     typedef fvec<NS> VT;
     __shared__ VT sA[27][64];
     __shared__ f4 qm[kQPos * 4], qp[kQPos * 4];
-    stage_weights<NS, (SIGN < 0)>(W, CIN, 16, sA);
+    stage_weights<NS, true>(W, 16, 16, sA);
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int j = lane & 15, kq = lane >> 4;
-    f4 br = f4{0.f, 0.f, 0.f, 0.f};
-    if (SIGN > 0) br = *reinterpret_cast<const f4 *>(bias + 4 * kq);
     const int V = G * G * G, own = kQPos - 2 * d;
-    const auto rs = nn_range(in, V * CP * 4);
+    const auto rs = nn_range(g, V * 64);
     const int nb = gridDim.x, per = (nrange + nb - 1) / nb;
     const int r_lo = xcd_rank(blockIdx.x, nb) * per;
     const int r_hi = r_lo + per < nrange ? r_lo + per : nrange;
@@ -756,15 +756,14 @@ __global__ __launch_bounds__(256) void k_conv_q(const float *__restrict__ in, co
     };
     // the rows of plane dz = q - 1 of tile position p
     auto load = [&](const Pos &p, int q, VT *B) {
-        const int dz = SIGN * (q - 1) * d;
+        const int dz = (1 - q) * d;
         const bool zok = p.valid && p.z + dz >= 0 && p.z + dz < G;
 #pragma unroll
         for (int r = 0; r < 3; ++r) {
-            const int dy = SIGN * (r - 1) * d;
+            const int dy = (1 - r) * d;
             const bool ok = zok && p.y + dy >= 0 && p.y + dy < G;
-            const int off = ok ? (p.v + (dz * G + dy) * G) * (CP * 4) + kq * (NS * 4) : kOutside;
-            if constexpr (NS == 4) B[r] = __builtin_bit_cast(VT, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
-            else B[r] = __builtin_bit_cast(VT, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0));
+            const int off = ok ? (p.v + (dz * G + dy) * G) * 64 + kq * 16 : kOutside;
+            B[r] = __builtin_bit_cast(VT, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
         }
     };
     VT Bc[2][3], Bn[2][3];
@@ -832,23 +831,17 @@ __global__ __launch_bounds__(256) void k_conv_q(const float *__restrict__ in, co
         for (int i = 0; i < 4; ++i) {
             const int pos = (wave * 4 + i) * 16 + j, v = rg * own - d + pos;
             if (pos < d || pos >= kQPos - d || v >= V) continue;
-            // the term of tap dx is in range if x + SIGN dx d is
-            const bool lo = xs[i] >= d, hi = xs[i] + d < G;
-            const f4 m = qm[(pos - SIGN * d) * 4 + kq], p = qp[(pos + SIGN * d) * 4 + kq];
-            const bool okm = SIGN > 0 ? lo : hi, okp = SIGN > 0 ? hi : lo;
+            // the term of tap dx is in range if x - dx d is
+            const bool okm = xs[i] + d < G, okp = xs[i] >= d;
+            const f4 m = qm[(pos + d) * 4 + kq], p = qp[(pos - d) * 4 + kq];
+            const f4 pp = *reinterpret_cast<const f4 *>(prev + (int64_t)v * 16 + 4 * kq);
             f4 o;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) o[r] = ((q0[i][r] + (okm ? m[r] : 0.f)) + (okp ? p[r] : 0.f)) + br[r];
-            f4 *dst = reinterpret_cast<f4 *>(out + (int64_t)v * 16 + 4 * kq);
-            if constexpr (SIGN > 0) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) o[r] = relu ? fmaxf(o[r], 0.f) : o[r];
-            } else {
-                const f4 pp = *reinterpret_cast<const f4 *>(prev + (int64_t)v * 16 + 4 * kq);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) o[r] = pp[r] > 0.f ? o[r] : 0.f;
+            for (int r = 0; r < 4; ++r) {
+                const float sum = (q0[i][r] + (okm ? m[r] : 0.f)) + (okp ? p[r] : 0.f);
+                o[r] = pp[r] > 0.f ? sum : 0.f;
             }
-            *dst = o;
+            *reinterpret_cast<f4 *>(gin + (int64_t)v * 16 + 4 * kq) = o;
         }
         __syncthreads();  // the next range rewrites qm and qp
     }
@@ -1209,9 +1202,9 @@ int mx_blocks(int64_t n, int64_t each, int cap) {
 // The factor of vox_fast.
 unsigned vox_magic(int G) { return (unsigned)((1ull << 32) / (unsigned)G + 1); }
 
-// Ranges and blocks of the k_conv*q kernels: as many blocks as stay resident
+// Ranges and blocks of the kernels that share rows: as many blocks as stay resident
 // (two per CU for the FP32 ones; with one exchange array and three per CU
-// k_conv_q took 126 instead of 120 us), one share of ranges each.
+// k_conv_bwd_data_q took 126 instead of 120 us), one share of ranges each.
 int q_ranges(int64_t V, int d) {
     const int own = kQPos - 2 * d;
     return (int)((V + own - 1) / own);
@@ -1220,15 +1213,11 @@ int q_ranges(int64_t V, int d) {
 template <int CIN, int CP, int COUT>
 int conv_fwd(const float *in, const float *W, const float *b, float *post, int G, int d, int relu, hipStream_t st) {
     const int64_t V = (int64_t)G * G * G;
-    if (d <= kQMaxD) {
+    if (COUT == 1 && d <= kQMaxD) {
         const int nr = q_ranges(V, d);
-        if constexpr (COUT == 16)
-            hipLaunchKernelGGL((k_conv_q<CIN, CP, 1>), dim3(mx_blocks(nr, 1, 512)), dim3(256), 0, st, in, W, b, nullptr,
-                               post, G, vox_magic(G), d, relu, nr);
-        else
-            hipLaunchKernelGGL(k_conv_fwd_q1, dim3(mx_blocks(nr, 1, 1024)), dim3(256), 0, st, in, W, b, post, G,
-                               vox_magic(G), d, nr);
-    } else {  // the halo would be too large a part of a range
+        hipLaunchKernelGGL(k_conv_fwd_q1, dim3(mx_blocks(nr, 1, 1024)), dim3(256), 0, st, in, W, b, post, G, vox_magic(G),
+                           d, nr);
+    } else {  // (one output, d > kQMaxD: the halo would be too large a part of a range)
         const int ntiles = (int)((V + 15) / 16);
         hipLaunchKernelGGL((k_conv_fwd_mx<CIN, CP, COUT>), dim3(mx_blocks(ntiles, 32, 2048)), dim3(256), 0, st, in, W, b,
                            post, G, d, relu, ntiles);
@@ -1286,8 +1275,8 @@ int bwd_d(const float *g, const float *W, const float *prev, float *gin, int cou
         hipLaunchKernelGGL(k_conv_bwd_data1, dim3(mx_blocks(ntiles, 16, 2048)), dim3(256), 0, st, g, W, prev, gin, G,
                            vox_magic(G), d, ntiles);
     else if (d <= kQMaxD)
-        hipLaunchKernelGGL((k_conv_q<16, 16, -1>), dim3(mx_blocks(nr, 1, 512)), dim3(256), 0, st, g, W, nullptr, prev,
-                           gin, G, vox_magic(G), d, 0, nr);
+        hipLaunchKernelGGL(k_conv_bwd_data_q, dim3(mx_blocks(nr, 1, 512)), dim3(256), 0, st, g, W, prev, gin, G,
+                           vox_magic(G), d, nr);
     else
         hipLaunchKernelGGL(k_conv_bwd_data_mx, dim3(mx_blocks(ntiles, 32, 2048)), dim3(256), 0, st, g, W, prev, gin, G,
                            d, ntiles);
