@@ -147,21 +147,35 @@ int upload_twiddles(Engine *e, const bemfft_plan *p) {
     return e->precision == BEMFFT_FP64 ? upload_tw<double>(e, p) : upload_tw<float>(e, p);
 }
 
-// Schedule of the z pass without autotuning, from z-pass times measured on
-// MI355X (us, Navier bodies; schedules 0, 1, 2): P = 192 FP32 68, 73, 68,
-// FP64 170, 150, 170; P = 256 FP32 170, 173, 168, FP64 336, 336, 337; P = 384
-// FP32 612, 571, 571, FP64 1432, 1450, 1387.  Laplace: schedule 0 at every
-// length (P = 256 FP32 43, 49; P = 192 FP32 26, 29).
-static int default_zsched(int kernel, int precision, int64_t pz) {
-    if (kernel != BEMFFT_NAVIER3D) return 0;
+// Schedule of the z pass without autotuning: the fastest at each padded length
+// pz, from z-pass times measured on MI355X (us, every plane of the half pencil
+// occupied; hx x py pencils 129 x 256 unless given; schedules 0, 1, 2).
+//   Laplace FP32: 0 -- 96: 26, 28; 128: 26, 29; 192: 38, 43; 256: 43, 49;
+//     320: 78, 86; 384: 96, 100; 512: 128, 127.
+//   Laplace FP64: 1 at 128, 384 and 512 -- 96: 40, 42; 128: 47, 43; 192: 76, 91;
+//     256: 115, 115; 320: 197, 204; 384: 371, 192; 512: 252, 246.
+//   Navier FP32: 0 below 320 -- 96: 67, 74; 128: 74, 82; 192: 136, 148; 256: 188,
+//     193, 195 -- and 1 from there (129 x 128) -- 320: 218, 166; 384: 166, 159,
+//     158; 512: 237, 201, 201.  Schedule 0 of 128 and 256 points puts eight pencils
+//     in a wavefront, 1 four: with few pencils the chip needs the wavefronts (256
+//     points, 33 x 64: 31, 27; 129 x 64: 62, 52; 129 x 128: 98, 98.  128 points, 33
+//     x 64: 25, 18; 129 x 128: 49, 46).
+//   Navier FP64 -- 96: 177, 190; 128: 651, 180; 192: 327, 302; 256: 386, 384;
+//     384 (129 x 128): 353, 354, 383, but 1467, 1484, 1459 for the 180-plane cube
+//     of 192^3 (193 x 384); 512: 1351, 1348, 402.
+// 32 and 64 points, and Navier FP64 at 320, have one schedule.
+static int default_zsched(int kernel, int precision, int64_t pz, int64_t hx, int64_t py) {
     const bool fp64 = precision == BEMFFT_FP64;
-    if (pz >= 320) return fp64 ? 2 : 1;
-    return fp64 ? 1 : 0;
+    if (kernel != BEMFFT_NAVIER3D) return fp64 && (pz == 128 || pz == 384 || pz == 512) ? 1 : 0;
+    const bool few = hx * py <= 129 * 128;
+    if (!fp64) return pz >= 320 || ((pz == 128 || pz == 256) && few) ? 1 : 0;
+    if (pz == 512 || (pz == 384 && !few)) return 2;
+    return pz == 128 || pz == 192 || pz == 256 ? 1 : 0;
 }
 
 int alloc_workspace(bemfft_plan *p, Engine *e) {
     BF_CHECK(alloc_intermediates(p, e->precision, e));
-    e->zsched = default_zsched(p->kernel, e->precision, p->P[2]);
+    e->zsched = default_zsched(p->kernel, e->precision, p->P[2], p->H[0], p->P[1]);
     // 16-bit spectra: kz rows padded to a multiple of 8 values (16-byte runs)
     e->hzs = e->precision == BEMFFT_BF16_MFMA ? (p->H[2] + 7) / 8 * 8 : spec_row(z_split(p->kernel, e->precision == BEMFFT_FP64, p->P[2]), (int)p->H[2]);
     const size_t spec = (size_t)p->K * p->H[0] * p->H[1] * e->hzs * e->sreal;
@@ -431,9 +445,10 @@ int plan_create_impl(bemfft_plan *p, const bemfft_grid *grid, int64_t m, const d
         // in the grid evaluation alike, so a padded length of 2 nzo - 1 carries
         // the same sums; a body that does not fill its box then takes a shorter
         // transform (a length that the caller asked for is kept, and the 16-bit
-        // form, bound by other loads, keeps the grid's: 33 us against 35).
-        // Navier takes 384 rather than 320, whose half transform has no schedule
-        // of few exchanges (192^3 star-like body, FP32: 569 us against 597).
+        // form, bound by other loads, keeps the grid's: 33 us, 35 at the shorter one).
+        // Navier takes 384 rather than 320, which is slower with every schedule (z
+        // pass of a 160^3 cube with 150 planes, 320 and 384: FP32 470 and 419 us,
+        // FP64 1472 and 1015).
         int64_t pz = auto_pad_len(2 * p->nzo - 1);
         if (pz == 320 && kernel == BEMFFT_NAVIER3D) pz = 384;
         if (pz < p->P[2]) {

@@ -107,3 +107,19 @@ def test_shortened_length_grid_field_and_batch(dev):
         batch.close()
         a.close()
         b.close()
+
+
+# (family, precision, padded lengths, schedule): lengths whose fastest schedule is not
+# the others', both sides of the few-pencils rule, and the length without a third one
+DEFAULTS = [(B.LAPLACE3D, B.FP64, (32, 32, 384), 1), (B.LAPLACE3D, B.FP64, (32, 32, 320), 0),
+            (B.LAPLACE3D, B.FP32, (32, 32, 384), 0), (B.NAVIER3D, B.FP64, (32, 32, 320), 0),
+            (B.NAVIER3D, B.FP64, (32, 32, 512), 2), (B.NAVIER3D, B.FP32, (256, 128, 256), 1),
+            (B.NAVIER3D, B.FP32, (256, 192, 256), 0), (B.NAVIER3D, B.FP32, (32, 32, 320), 1)]
+
+
+@pytest.mark.parametrize("kernel,prec,pad,want", DEFAULTS)
+def test_default_schedule(dev, kernel, prec, pad, want):
+    """The schedule without autotuning: the measured one of the length, one that
+    exists, and the same results as the oracle's."""
+    g = _Nodes((13, 10, pad[2] // 2), 0, pad[2] // 2 - 1, seed=pad[2])
+    assert _check(dev, g, kernel, prec, pad=pad)["zsched"] == want
