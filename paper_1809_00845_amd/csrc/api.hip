@@ -163,7 +163,8 @@ int upload_twiddles(Engine *e, const bemfft_plan *p) {
 //   Navier FP64 -- 96: 177, 190; 128: 651, 180; 192: 327, 302; 256: 386, 384;
 //     384 (129 x 128): 353, 354, 383, but 1467, 1484, 1459 for the 180-plane cube
 //     of 192^3 (193 x 384); 512: 1351, 1348, 402.
-// 32 and 64 points, and Navier FP64 at 320, have one schedule.
+// 64 points, Navier at 32 and Navier FP64 at 320 have one schedule; Laplace at 32
+// has its own for large planes (zsched.hpp).
 static int default_zsched(int kernel, int precision, int64_t pz, int64_t hx, int64_t py) {
     const bool fp64 = precision == BEMFFT_FP64;
     if (kernel != BEMFFT_NAVIER3D) return fp64 && (pz == 128 || pz == 384 || pz == 512) ? 1 : 0;

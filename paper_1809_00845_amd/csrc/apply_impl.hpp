@@ -489,7 +489,7 @@ struct ZCfg {
     static constexpr int KT = 1 << z_tile_log2(KIND, sizeof(R) == 8, PZ);
     static constexpr int CB = (int)sizeof(cx<R>);
     static constexpr int PS = SH::PS;
-        static constexpr int WAVES = 4;
+    static constexpr int WAVES = TPP == 4 ? 2 : 4;  // a block's ky divide every Py (a multiple of 32)
     static constexpr int SETS = WAVES / D;  // groups of PPW pencils per block
     static constexpr int TY = PPW * SETS;
     static constexpr int NT = 64 * WAVES;

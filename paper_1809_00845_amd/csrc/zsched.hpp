@@ -29,11 +29,17 @@ struct ZShape {
     static_assert(PS >= L - 1 + ((L - 1) >> SHIFT) + 1, "pencil slots");
 };
 
+// Laplace at 32 points: a pencil is so short that a block is mostly latency, so
+// four lanes per pencil, half the wavefronts of eight, keep a large plane's blocks
+// resident at once (one plane of 184^2 points on a 192^2 grid, 193 x 384 pencils,
+// FP32 18.0 -> 13.4 us, FP64 23.6 -> 16.8; 8 planes of 120^2: 12.4 -> 10.4).
+//
 // ZSel<NAV, F64, P, S>: schedule S of padded length P (NAV: Navier, else
 // Laplace; F64: FP64).  S = 0 and 1 exist for every family, S = 2 for Navier.
 // D depends on (NAV, F64, P) only, as the stored spectra do.
 template <bool NAV, bool F64, int P, int S> struct ZSel;
 template <bool N, bool F, int S> struct ZSel<N, F, 32, S> { using type = ZShape<1, 32, 8, 3, 40, 4, 4, 2>; };
+template <bool F> struct ZSel<false, F, 32, 0> { using type = ZShape<1, 32, 4, 3, 36, 8, 4>; };
 template <bool N, bool F, int S> struct ZSel<N, F, 64, S> { using type = ZShape<1, 64, 8, 3, 72, 8, 8>; };
 template <bool N, bool F, int S> struct ZSel<N, F, 96, S> { using type = ZShape<1, 96, 8, 3, 120, 4, 4, 6>; };
 template <bool N, bool F> struct ZSel<N, F, 96, 1> { using type = ZShape<1, 96, 8, 4, 104, 6, 4, 4>; };
@@ -81,8 +87,10 @@ __host__ __device__ constexpr int z_split(int kernel, bool f64, int64_t p) {
 // few long runs of one compact tile.  Forward / z pass, 128^3 Laplace cube, us,
 // with rows of 32, 64 and 128 bytes: FP32 44 / 42, 37 / 43, 37 / 47; FP64
 // (64, 128) 60 / 78, 58 / 87.  Narrower rows cost the forward pass partial
-// lines, wider ones the z pass.
+// lines, wider ones the z pass.  Laplace at 32 points takes 16 ky, the pencils of
+// a wavefront with four lanes each.
 __host__ __device__ constexpr int z_tile_log2(int kernel, bool f64, int pz) {
+    if (kernel != 2 && pz == 32) return 4;
     return f64 && pz > 128 && z_split(kernel, f64, pz) == 1 ? 2 : 3;
 }
 

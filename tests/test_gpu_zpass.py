@@ -123,3 +123,14 @@ def test_default_schedule(dev, kernel, prec, pad, want):
     exists, and the same results as the oracle's."""
     g = _Nodes((13, 10, pad[2] // 2), 0, pad[2] // 2 - 1, seed=pad[2])
     assert _check(dev, g, kernel, prec, pad=pad)["zsched"] == want
+
+
+@pytest.mark.parametrize("py", [32, 64, 96, 320])
+@pytest.mark.parametrize("nz", [1, 2, 15, 16])
+def test_short_pencils(dev, py, nz):
+    """Laplace at 32 points, four (schedule 0) or eight lanes per pencil: sixteen ky
+    of a wavefront on both sides of Py / 2, with one, few and all planes occupied."""
+    g = _Nodes((16, py // 2, nz), 0, nz - 1, seed=py + nz)
+    for prec in (B.FP64, B.FP32):
+        for sched in (0, 1):
+            _check(dev, g, B.LAPLACE3D, prec, pad=(32, py, 32), autotune=2 + sched)
