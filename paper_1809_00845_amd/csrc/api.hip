@@ -160,23 +160,26 @@ int upload_twiddles(Engine *e, const bemfft_plan *p) {
 //     in a wavefront, 1 four: with few pencils the chip needs the wavefronts (256
 //     points, 33 x 64: 31, 27; 129 x 64: 62, 52; 129 x 128: 98, 98.  128 points, 33
 //     x 64: 25, 18; 129 x 128: 49, 46).
-//   Navier FP64 -- 96: 177, 190; 128: 651, 180; 192: 327, 302; 256: 386, 384;
+//   Navier FP64 -- 96: 177, 190; 128: 651, 180; 192: 327, 302; 256: schedule 1
+//     (narrower tiles, z_tile_log2) unless the pencils are many and long rows lie
+//     beside short ones;
 //     384 (129 x 128): 353, 354, 383, but 1467, 1484, 1459 for the 180-plane cube
 //     of 192^3 (193 x 384); 512: 1351, 1348, 402.
 // 64 points, Navier at 32 and Navier FP64 at 320 have one schedule; Laplace at 32
 // has its own for large planes (zsched.hpp).
-static int default_zsched(int kernel, int precision, int64_t pz, int64_t hx, int64_t py) {
-    const bool fp64 = precision == BEMFFT_FP64;
+static int default_zsched(const bemfft_plan *p, bool fp64) {
+    const int kernel = p->kernel;
+    const int64_t pz = p->P[2], hx = p->H[0], py = p->P[1];
     if (kernel != BEMFFT_NAVIER3D) return fp64 && (pz == 128 || pz == 384 || pz == 512) ? 1 : 0;
     const bool few = hx * py <= 129 * 128;
     if (!fp64) return pz >= 320 || ((pz == 128 || pz == 256) && few) ? 1 : 0;
     if (pz == 512 || (pz == 384 && !few)) return 2;
-    return pz == 128 || pz == 192 || pz == 256 ? 1 : 0;
+    return pz == 128 || pz == 192 || (pz == 256 && (few || !p->mixed_rows)) ? 1 : 0;
 }
 
 int alloc_workspace(bemfft_plan *p, Engine *e) {
     BF_CHECK(alloc_intermediates(p, e->precision, e));
-    e->zsched = default_zsched(p->kernel, e->precision, p->P[2], p->H[0], p->P[1]);
+    e->zsched = default_zsched(p, e->precision == BEMFFT_FP64);
     // 16-bit spectra: kz rows padded to a multiple of 8 values (16-byte runs)
     e->hzs = e->precision == BEMFFT_BF16_MFMA ? (p->H[2] + 7) / 8 * 8 : spec_row(z_split(p->kernel, e->precision == BEMFFT_FP64, p->P[2]), (int)p->H[2]);
     const size_t spec = (size_t)p->K * p->H[0] * p->H[1] * e->hzs * e->sreal;
@@ -495,6 +498,7 @@ int plan_create_impl(bemfft_plan *p, const bemfft_grid *grid, int64_t m, const d
         int64_t long_nodes = 0;
         for (int r : dense_rows) long_nodes += rowptr[r + 1] - rowptr[r];
         p->all_long = p->dim == 2 && long_nodes == m;
+        p->mixed_rows = p->nd > 0 && long_nodes < m;
         p->row_inv = (double)long_nodes * (double)p->H[0] * p->O > kRowInvWork ? 1 : 0;
     }
     // per-node free term and self correction blocks (sorted order)

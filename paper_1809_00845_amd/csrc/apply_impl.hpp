@@ -429,7 +429,7 @@ __device__ __forceinline__ void fwd_xy_body(const ApplyArgs &a, const int bx, co
 #pragma unroll
             for (int e = 0; e < E; ++e) Y[t + e * TPP] = to_store<YS>(x[e]);
         } else {
-            const int l = z_tile_log2(KIND, sizeof(R) == 8, a.pz);
+            const int l = z_tile_log2(KIND, sizeof(R) == 8, a.pz, a.zsched);
 #pragma unroll
             for (int e = 0; e < E; ++e) {
                 const int ky = t + e * TPP;
@@ -486,7 +486,7 @@ struct ZCfg {
     static_assert(D == z_split(KIND, sizeof(R) == 8, PZ), "the stored spectra's split");
     static constexpr int TPP = SH::TPP;
     static constexpr int PPW = 64 / TPP;
-    static constexpr int KT = 1 << z_tile_log2(KIND, sizeof(R) == 8, PZ);
+    static constexpr int KT = 1 << z_tile_log2(KIND, sizeof(R) == 8, PZ, SH::SCHED);
     static constexpr int CB = (int)sizeof(cx<R>);
     static constexpr int PS = SH::PS;
     static constexpr int WAVES = TPP == 4 ? 2 : 4;  // a block's ky divide every Py (a multiple of 32)
@@ -1548,6 +1548,7 @@ template <typename R, int PZ, int KIND, int SCHED>
 int launch_z(const ApplyArgs &a, hipStream_t st) {
     using SH = ZSched<R, KIND, PZ, SCHED>;
     using Cfg = ZCfg<R, SH, KIND>;
+    static_assert(Cfg::KT == 1 << z_tile_log2(KIND, sizeof(R) == 8, PZ, SCHED), "the forward pass's tiles");
     if (a.py % Cfg::TY != 0 || 2 * a.nzo > PZ + 1) {
         set_error("z pass: y length or planes do not fit the schedule");
         return BEMFFT_EUNSUPPORTED;

@@ -25,6 +25,7 @@ template <int D_, int L_, int TPP_, int SHIFT_, int PS_, int... Rs>
 struct ZShape {
     static constexpr int D = D_, L = L_, TPP = TPP_, SHIFT = SHIFT_, PS = PS_;
     static constexpr int E = L_ / TPP_;
+    static constexpr int SCHED = 0;  // what z_tile_log2 asks for: not 0 where a schedule has its own tiles
     using rad = Radices<Rs...>;
     static_assert(PS >= L - 1 + ((L - 1) >> SHIFT) + 1, "pencil slots");
 };
@@ -60,6 +61,10 @@ template <bool F> struct ZSel<false, F, 512, 1> { using type = ZShape<1, 512, 32
 template <bool F, int S> struct ZSel<true, F, 256, S> { using type = ZShape<2, 128, 16, 4, 135, 8, 8, 2>; };
 template <> struct ZSel<true, false, 256, 0> { using type = ZShape<2, 128, 8, 4, 136, 16, 8>; };
 template <bool F> struct ZSel<true, F, 256, 1> { using type = ZShape<2, 128, 16, 4, 135, 8, 4, 4>; };
+struct ZShapeNav256Few : ZShape<2, 128, 16, 4, 135, 8, 4, 4> {
+    static constexpr int SCHED = 1;
+};
+template <> struct ZSel<true, true, 256, 1> { using type = ZShapeNav256Few; };
 template <bool F, int S> struct ZSel<true, F, 320, S> { using type = ZShape<2, 160, 16, 9, 160, 10, 2, 2, 2, 2>; };
 template <> struct ZSel<true, false, 320, 0> { using type = ZShape<2, 160, 8, 3, 184, 4, 4, 10>; };
 template <int S> struct ZSel<true, false, 384, S> { using type = ZShape<2, 192, 16, 2, 239, 4, 4, 12>; };
@@ -88,9 +93,14 @@ __host__ __device__ constexpr int z_split(int kernel, bool f64, int64_t p) {
 // with rows of 32, 64 and 128 bytes: FP32 44 / 42, 37 / 43, 37 / 47; FP64
 // (64, 128) 60 / 78, 58 / 87.  Narrower rows cost the forward pass partial
 // lines, wider ones the z pass.  Laplace at 32 points takes 16 ky, the pencils of
-// a wavefront with four lanes each.
-__host__ __device__ constexpr int z_tile_log2(int kernel, bool f64, int pz) {
+// a wavefront with four lanes each.  Navier FP64 at 256 points: rows of 64 bytes
+// in schedule 1, 128 in the others (z pass with 128 and 64 bytes: 33 x 64 pencils
+// 44.0, 38.3 us; 129 x 128 202, 189; two far plates, 129 x 256, 369, 354; but the
+// forward pass of a body with long and short rows pays: the 100-point cube on
+// 128^3 347, 336 and 148, 164).
+__host__ __device__ constexpr int z_tile_log2(int kernel, bool f64, int pz, int sched) {
     if (kernel != 2 && pz == 32) return 4;
+    if (kernel == 2 && f64 && pz == 256 && sched == 1) return 2;
     return f64 && pz > 128 && z_split(kernel, f64, pz) == 1 ? 2 : 3;
 }
 

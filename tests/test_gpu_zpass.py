@@ -113,7 +113,8 @@ def test_shortened_length_grid_field_and_batch(dev):
 # the others', both sides of the few-pencils rule, and the length without a third one
 DEFAULTS = [(B.LAPLACE3D, B.FP64, (32, 32, 384), 1), (B.LAPLACE3D, B.FP64, (32, 32, 320), 0),
             (B.LAPLACE3D, B.FP32, (32, 32, 384), 0), (B.NAVIER3D, B.FP64, (32, 32, 320), 0),
-            (B.NAVIER3D, B.FP64, (32, 32, 512), 2), (B.NAVIER3D, B.FP32, (256, 128, 256), 1),
+            (B.NAVIER3D, B.FP64, (32, 32, 512), 2), (B.NAVIER3D, B.FP64, (96, 64, 256), 1),
+            (B.NAVIER3D, B.FP32, (256, 128, 256), 1),
             (B.NAVIER3D, B.FP32, (256, 192, 256), 0), (B.NAVIER3D, B.FP32, (32, 32, 320), 1)]
 
 
