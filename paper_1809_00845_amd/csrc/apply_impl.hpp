@@ -67,14 +67,23 @@ struct ApplyArgs {
     void *Y, *Z;
 };
 
-// Launch extents of one group of batch members (same family, precision,
-// padded sizes and schedule): the largest per-member extents.
+// Consecutive members of a group with one z length and schedule.
+struct ZRange {
+    int first, nmem, pz, zsched;
+};
+
+// Launch extents of one group of batch members (same family, precision and padded
+// x and y sizes): the largest per-member extents.  Members whose bodies occupy
+// different numbers of planes differ in their z length; only the z pass is
+// launched by length, so that many small bodies still fill the chip.
 struct GroupDims {
     int nmem;
     int max_m, max_nd, max_nzo;
-    int hx, px, py, pz, zsched;
+    int hx, px, py;
     int row_inv;  // some member takes the row FFT for its long rows
     int flat;     // 2D: flat_path of every member
+    const ZRange *z;  // 3D: host array of nz ranges
+    int nz;
 };
 
 // The 2D kernels that a plan takes, a rule on its nodes (m, nd long rows) so
@@ -1774,20 +1783,21 @@ struct Launch {
         return 0;
     }
     template <int PZ, int SCHED>
-    static int bz_s(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, hipStream_t st) {
+    static int bz_s(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, const ZRange &r, hipStream_t st) {
         using SH = ZSched<R, KIND, PZ, SCHED>;
         using Cfg = ZCfg<R, SH, KIND>;
         const int nby = g.py / Cfg::TY;
-        dim3 grid(8 * ((g.hx * nby + 7) / 8), 1, g.nmem);
-        hipLaunchKernelGGL((kb_zpass<R, SH, KIND>), grid, dim3(Cfg::NT), 0, st, dm, io, nby);
+        dim3 grid(8 * ((g.hx * nby + 7) / 8), 1, r.nmem);
+        hipLaunchKernelGGL((kb_zpass<R, SH, KIND>), grid, dim3(Cfg::NT), 0, st, dm + r.first, io, nby);
         BF_HIP(hipGetLastError());
         return 0;
     }
-    template <int P> static int bz(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, hipStream_t st) {
+    template <int P>
+    static int bz(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, const ZRange &r, hipStream_t st) {
         if constexpr (KIND == 2) {
-            if (g.zsched == 2) return bz_s<P, 2>(dm, io, g, st);
+            if (r.zsched == 2) return bz_s<P, 2>(dm, io, g, r, st);
         }
-        return g.zsched == 1 ? bz_s<P, 1>(dm, io, g, st) : bz_s<P, 0>(dm, io, g, st);
+        return r.zsched == 1 ? bz_s<P, 1>(dm, io, g, r, st) : bz_s<P, 0>(dm, io, g, r, st);
     }
     static int dispatch_brows(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, hipStream_t st) {
         BF_SIZE_SWITCH_K(KIND, g.px, brows, dm, io, g, st);
@@ -1799,8 +1809,8 @@ struct Launch {
         set_error("unsupported y length");
         return BEMFFT_EUNSUPPORTED;
     }
-    static int dispatch_bz(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, hipStream_t st) {
-        BF_SIZE_SWITCH(g.pz, bz, dm, io, g, st);
+    static int dispatch_bz(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, const ZRange &r, hipStream_t st) {
+        BF_SIZE_SWITCH(r.pz, bz, dm, io, g, r, st);
         set_error("unsupported z length");
         return BEMFFT_EUNSUPPORTED;
     }
@@ -1825,7 +1835,7 @@ struct Launch {
             BF_CHECK(dispatch_bmid(dm, io, g, fold, st));
         } else {
             BF_CHECK(dispatch_bfwd(dm, io, g, st));
-            BF_CHECK(dispatch_bz(dm, io, g, st));
+            for (int i = 0; i < g.nz; ++i) BF_CHECK(dispatch_bz(dm, io, g, g.z[i], st));
             BF_CHECK(dispatch_binv(dm, io, g, st));
         }
         if constexpr (FLAT) {

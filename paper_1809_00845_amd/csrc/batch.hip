@@ -36,7 +36,8 @@ constexpr size_t kForkBytes = 256u << 20;
 struct Group {
     int kernel, precision;
     GroupDims dims;
-    std::vector<int> members;
+    std::vector<int> members;  // by z length and schedule
+    std::vector<ZRange> z;
     ApplyArgs *d_args = nullptr;
 };
 
@@ -73,10 +74,13 @@ void bfree(void *p) {
 }
 
 int launch_group(const bemfft_batch *b, const Group &g, hipStream_t st) {
-    if (g.kernel == 0) return apply_batch_kind<0>(g.precision, g.d_args, b->d_io, g.dims, st);
-    if (g.kernel == 1) return apply_batch_kind<1>(g.precision, g.d_args, b->d_io, g.dims, st);
-    if (g.kernel == 3) return apply_batch_kind<3>(g.precision, g.d_args, b->d_io, g.dims, st);
-    return apply_batch_kind<2>(g.precision, g.d_args, b->d_io, g.dims, st);
+    GroupDims d = g.dims;
+    d.z = g.z.data();
+    d.nz = (int)g.z.size();
+    if (g.kernel == 0) return apply_batch_kind<0>(g.precision, g.d_args, b->d_io, d, st);
+    if (g.kernel == 1) return apply_batch_kind<1>(g.precision, g.d_args, b->d_io, d, st);
+    if (g.kernel == 3) return apply_batch_kind<3>(g.precision, g.d_args, b->d_io, d, st);
+    return apply_batch_kind<2>(g.precision, g.d_args, b->d_io, d, st);
 }
 
 int launch_groups(bemfft_batch *b, hipStream_t st) {
@@ -387,17 +391,17 @@ int bemfft_batch_create(bemfft_batch **out, bemfft_plan *const *plans, int nplan
     for (int k = 0; k < nm && status == 0; ++k)
         status = alloc_intermediates(plans[b->mem_plan[k]], b->precision, &b->ws[k]);
     // groups
-    std::map<std::tuple<int64_t, int64_t, int64_t, int, int>, int> gidx;
+    std::map<std::tuple<int64_t, int64_t, int>, int> gidx;
     for (int k = 0; k < nm && status == 0; ++k) {
         bemfft_plan *p = plans[b->mem_plan[k]];
         const int flat = p->dim == 2 ? flat_path(p->m, p->nd, p->all_long) : 0;
-        auto key = std::make_tuple(p->P[0], p->P[1], p->P[2], p->zsched, flat);
+        auto key = std::make_tuple(p->P[0], p->P[1], flat);
         auto it = gidx.find(key);
         if (it == gidx.end()) {
             Group g;
             g.kernel = b->kernel;
             g.precision = b->precision;
-            g.dims = GroupDims{0, 0, 0, 0, (int)p->H[0], (int)p->P[0], (int)p->P[1], (int)p->P[2], p->zsched, 0, flat};
+            g.dims = GroupDims{0, 0, 0, 0, (int)p->H[0], (int)p->P[0], (int)p->P[1], 0, flat, nullptr, 0};
             gidx[key] = (int)b->groups.size();
             b->groups.push_back(g);
             it = gidx.find(key);
@@ -412,6 +416,17 @@ int bemfft_batch_create(bemfft_batch **out, bemfft_plan *const *plans, int nplan
     }
     for (auto &g : b->groups) {
         if (status) break;
+        auto zkey = [&](int k) {
+            const bemfft_plan *p = plans[b->mem_plan[k]];
+            return std::make_tuple(p->P[2], p->zsched);
+        };
+        std::stable_sort(g.members.begin(), g.members.end(), [&](int i, int j) { return zkey(i) < zkey(j); });
+        for (size_t i = 0; i < g.members.size(); ++i) {
+            const bemfft_plan *p = plans[b->mem_plan[g.members[i]]];
+            if (i == 0 || zkey(g.members[i]) != zkey(g.members[i - 1]))
+                g.z.push_back(ZRange{(int)i, 0, (int)p->P[2], p->zsched});
+            g.z.back().nmem += 1;
+        }
         std::vector<ApplyArgs> args(g.members.size());
         for (size_t i = 0; i < g.members.size(); ++i) {
             const int k = g.members[i];

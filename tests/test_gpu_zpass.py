@@ -135,3 +135,31 @@ def test_short_pencils(dev, py, nz):
     for prec in (B.FP64, B.FP32):
         for sched in (0, 1):
             _check(dev, g, B.LAPLACE3D, prec, pad=(32, py, 32), autotune=2 + sched)
+
+
+@pytest.mark.parametrize("use_graph", [True, False])
+@pytest.mark.parametrize("kernel", [B.LAPLACE3D, B.NAVIER3D])
+def test_batch_of_lengths(dev, kernel, use_graph):
+    """Members of one grid whose bodies occupy different numbers of planes (their z
+    passes differ in length and schedule, everything else runs as one group), in an
+    order that is not that of the lengths: every member has its plan's bits."""
+    spans = [(3, 40), (10, 10), (0, 63), (20, 45), (5, 20), (1, 40)]
+    geoms = [_Nodes((24, 20, 64), lo, hi, m=50 + 7 * i, seed=i) for i, (lo, hi) in enumerate(spans)]
+    nc = 3 if kernel == B.NAVIER3D else 1
+    rng = np.random.default_rng(3)
+    for prec in (B.FP64, B.FP32):
+        plans = [B.Plan(g, kernel, precision=prec, autotune=2 + i % 2) for i, g in enumerate(geoms)]
+        batch = B.Batch(plans, nrhs=2, use_graph=use_graph)
+        n = sum(batch.lengths)
+        q, u = (torch.tensor(rng.uniform(-1, 1, n), device=dev) for _ in range(2))
+        cut = lambda t, k: t[batch.offsets[k]:batch.offsets[k] + batch.lengths[k]].contiguous()
+        ref = torch.cat([plans[k // 2].apply(cut(q, k), cut(u, k)) for k in range(len(batch.offsets))])
+        assert n == sum(2 * nc * len(g.weights) for g in geoms)
+        for _ in range(3):
+            r = torch.full_like(q, float("nan"))
+            batch.apply(q, u, r)
+            assert torch.equal(r, ref)
+            _ = (q * 2.0).sum().item()  # eager work between replays
+        batch.close()
+        for p in plans:
+            p.close()
