@@ -472,7 +472,7 @@ __global__ __launch_bounds__((FwdCfg<R, PY, KIND>::NT)) void k_fwd_xy(ApplyArgs 
 // Batched form: blockIdx.z = member.
 template <typename R, int PY, int KIND>
 __global__ __launch_bounds__((FwdCfg<R, PY, KIND>::NT)) void kb_fwd_xy(const ApplyArgs *members, const BatchIO *io) {
-    const ApplyArgs &a = members[blockIdx.z];
+    const ApplyArgs a = members[blockIdx.z];
     if (io->active && !io->active[a.gid]) return;
     fwd_xy_item<R, PY, KIND, 1, cx<R>>(a, blockIdx.x);
 }
@@ -742,11 +742,13 @@ __global__ __launch_bounds__((ZCfg<R, SH, KIND>::NT), 2) void k_zpass(ApplyArgs 
     zpass_item<R, SH, KIND>(a, blockIdx.x, nby);
 }
 
-// Batched form: blockIdx.z = member.
+// Batched form: blockIdx.z = member.  The member's arguments are copied first: read
+// through the pointer they are fetched again after every scheduling barrier (two
+// Navier bodies of 64^3 in FP64 at 64 points: 119 -> 50 us).
 template <typename R, typename SH, int KIND>
 __global__ __launch_bounds__((ZCfg<R, SH, KIND>::NT), 2) void kb_zpass(const ApplyArgs *members, const BatchIO *io,
                                                                      int nby) {
-    const ApplyArgs &a = members[blockIdx.z];
+    const ApplyArgs a = members[blockIdx.z];
     if (io->active && !io->active[a.gid]) return;
     zpass_item<R, SH, KIND>(a, blockIdx.x, nby);
 }
@@ -1123,7 +1125,7 @@ __global__ __launch_bounds__((InvYCfg<R, PY, KIND>::NT)) void k_inv_y(ApplyArgs 
 // Batched form: blockIdx.z = member * zdiv + the kernel's own z index.
 template <typename R, int PY, int KIND>
 __global__ __launch_bounds__((InvYCfg<R, PY, KIND>::NT)) void kb_inv_y(const ApplyArgs *members, const BatchIO *io, int zdiv) {
-    const ApplyArgs &a = members[blockIdx.z / zdiv];
+    const ApplyArgs a = members[blockIdx.z / zdiv];
     if (io->active && !io->active[a.gid]) return;
     inv_y_body<R, PY, KIND>(a, blockIdx.x, blockIdx.y, 0);
 }
@@ -1219,7 +1221,7 @@ __global__ __launch_bounds__((RowInvCfg<R, PX>::NT)) void k_rows_inv(ApplyArgs a
 // Batched form: blockIdx.z = member.
 template <typename R, int PX, int KIND>
 __global__ __launch_bounds__((RowInvCfg<R, PX>::NT)) void kb_rows_inv(const ApplyArgs *members, const BatchIO *io) {
-    const ApplyArgs &a = members[blockIdx.z];
+    const ApplyArgs a = members[blockIdx.z];
     if (io->active && !io->active[a.gid]) return;
     rows_inv_body<R, PX, KIND>(a, blockIdx.x);
 }
