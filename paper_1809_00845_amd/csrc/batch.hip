@@ -28,10 +28,14 @@ namespace {
 
 constexpr int kBpm = 64;       // reduction blocks per member
 constexpr int kHs = 1024;      // per-member slots of the Hessenberg column buffer
-// Groups run side by side when their intermediates fit the 256 MB memory-side
-// cache together; larger ones would evict each other's (8 bodies of 64 to 160
-// points x 4 right-hand sides: 2421 us one after the other, 2529 side by side).
-constexpr size_t kForkBytes = 256u << 20;
+// Groups run side by side while their intermediates take between these sizes
+// together.  Each join in a graph costs some 25 us, so small batches lose by it
+// (replayed side by side and one after the other, us: two sizes of half-space
+// surfaces, 1 MB, 85 and 40; four squares, 3 MB, 110 and 64; five bodies of 20 to
+// 58 points, 32 MB, 88 and 75; but seven of 28 to 54, 92 MB, 122 and 141; eight of
+// 36 to 52 x 4, 171 MB, 145 and 160); above the memory-side cache's 256 MB the
+// groups evict each other's (8 bodies of 64 to 160 points x 4: 2529 and 2421).
+constexpr size_t kForkMin = 64u << 20, kForkMax = 256u << 20;
 
 struct Group {
     int kernel, precision;
@@ -89,15 +93,14 @@ int launch_groups(bemfft_batch *b, hipStream_t st) {
 }
 
 // For the captured graph: the groups do not depend on each other (every member
-// has its own intermediates and results), so they are captured as up to four
-// parallel branches, joined at the end.  A group of few small members then
-// does not leave the chip to its own launches (4 bodies of 29 to 69 points x 3
-// right-hand sides: 239 -> 170 us; 4 of 33 to 81 x 4: 329 -> 265).
+// has its own intermediates and results), so batches of the sizes above are
+// captured as up to four parallel branches, joined at the end: a group of few
+// small members then does not leave the chip to its own launches.
 int capture_groups(bemfft_batch *b, hipStream_t st) {
     constexpr int kMaxBranches = 4;  // hardware queues
     size_t bytes = 0;
     for (const Engine &e : b->ws) bytes += e.bytes;
-    const int nb = bytes <= kForkBytes ? std::min<int>(kMaxBranches, (int)b->groups.size()) : 1;
+    const int nb = bytes >= kForkMin && bytes <= kForkMax ? std::min<int>(kMaxBranches, (int)b->groups.size()) : 1;
     hipStream_t s[kMaxBranches] = {st};
     hipEvent_t ev[kMaxBranches] = {};
     int status = 0;

@@ -163,3 +163,22 @@ def test_batch_of_lengths(dev, kernel, use_graph):
         batch.close()
         for p in plans:
             p.close()
+
+
+def test_batch_in_branches(dev):
+    """Two grids whose intermediates together take 64 to 256 MB (the graph then holds
+    the groups as parallel branches): every replay gives the plans' bits."""
+    geoms = [_Nodes((48, 48, 48), 2, 40, m=300), _Nodes((64, 64, 64), 5, 50, m=400), _Nodes((48, 40, 48), 0, 47, m=200)]
+    plans = [B.Plan(g, B.LAPLACE3D, precision=B.FP64) for g in geoms]
+    batch = B.Batch(plans, nrhs=2, use_graph=True)
+    rng = np.random.default_rng(8)
+    n = sum(batch.lengths)
+    cut = lambda t, k: t[batch.offsets[k]:batch.offsets[k] + batch.lengths[k]].contiguous()
+    for _ in range(4):  # replays on new inputs, with eager work between them
+        q, u = (torch.tensor(rng.uniform(-1, 1, n), device=dev) for _ in range(2))
+        r = torch.full_like(q, float("nan"))
+        batch.apply(q, u, r)
+        assert torch.equal(r, torch.cat([plans[k // 2].apply(cut(q, k), cut(u, k)) for k in range(6)]))
+    batch.close()
+    for p in plans:
+        p.close()
