@@ -25,6 +25,18 @@ constexpr double kPi = 3.141592653589793238462643383279502884;
 const int64_t kSizes[] = {32, 64, 96, 128, 192, 256, 320, 384, 512, 1024};  // 1024: 2D only
 // A grid row holding this many nodes is x-transformed by FFT.
 constexpr int kDenseRow = 24;
+// 2D plans whose fields are not folded (fold_rule) transform shorter rows so: the
+// sums of k_mid2d take each row in one thread and grow with the busiest, the row FFTs
+// of k_fields_rows do not.  512^2 grids with 10, 16 and 23 nodes in each row, us an
+// apply with the limit at 24 and 8: Laplace FP64 53, 92, 126 and 41, FP32 33, 53, 87
+// and 28, half-space FP32 45, 67, 102 and 35; 256^2, 10 and 23 nodes, 22, 36 and 18 in
+// FP64.  Rows of 6 are faster summed: 34.3 and, with the limit at 6, 40.8.
+constexpr int kDenseRow2d = 8;
+// Where eight lanes per node leave a 2D plan's chip idle, k_gather_wide sums a row
+// in one round (one output up to this many nodes, three up to twice as many): rows of
+// 0 to 23 nodes, us with it and without, Laplace 2997 nodes 20.1 and 20.3, 3967
+// 35.9 and 35.8, 6008 49.1 and 47.0; half-space 3967 55.7 and 63.7, 6008 74.8 and 83.0.
+constexpr int kWideNodes = 4096;
 // When no other row holds more than this many nodes, the forward direct DFT
 // takes two kx per thread (each node load serves both; measured on the
 // 128^3 cube: 42 -> 38 us).  Plans with busier short rows keep one kx per
@@ -227,7 +239,7 @@ void fill_apply_args(const bemfft_plan *p, const Engine &e, const Engine &ws, Ap
     a.dense_rows = p->d_dense_rows;
     a.nd = (int)p->nd;
     a.row_inv = p->row_inv;
-    a.all_long = p->all_long;
+    a.flat = p->flat;
     a.fwd_xg = p->fwd_xg;
     a.zsched = e.zsched;
     a.off = 0;
@@ -339,6 +351,37 @@ int implicit_free_term(bemfft_plan *p, const Engine &e64, hipStream_t st, std::v
 
 int autotune_zsched(bemfft_plan *p, hipStream_t st);
 int num_zsched(const bemfft_plan *p);
+
+// 2D: the fields are folded into k_mid2d (which saves the launch before it, 3 us,
+// but has every block fetch every node from q and u) where that is faster: few long
+// rows, which a wavefront sums one after the other, and either a short transform, whose
+// blocks leave CUs idle, or few nodes, in rows that are fetched in one round.
+// Measured (us an apply, folded and not): long rows beside two nodes per row on 128^2,
+// 1, 3, 5, 8 of them: 11.5, 13.0, 14.8, 17.3 and 14.3; on 512^2 23.8, 26.0, 28.0, 31.4
+// and 27.0.  128^2, 13 and 16 nodes in each row (1,728, 2,112 nodes): 13.5, 15.6 and
+// 14.3, 14.0.  190^2, 6 and 8 per row 15.9, 17.7 and 17.0, 20.5.  256^2, 4 and 6 per row: 15.4, 17.3 and 15.6, 16.6; 512^2, 2 and 2 to 3
+// per row: 21.8, 26.3 and 22.0, 24.7, the square's sides (1,020 nodes beside two long
+// rows) 24.7 and 27.2.  A circle, whose top and bottom rows hold 8 to 40 nodes:
+// 128^2 12.3 and 14.2, 256^2 20.4 and 17.7, 512^2 32.6 and 29.0.
+constexpr int kFoldRows = 3, kFoldNodes = 1792, kFoldLight = 1152, kFoldAll = 4096;
+
+bool fold_rule(const bemfft_plan *p, const std::vector<int> &rowptr) {
+    int64_t long_rows = 0, heavy = 0, light = 0, busiest = 0;  // light: nodes of the rows that are not heavy
+    for (size_t r = 0; r + 1 < rowptr.size(); ++r) {
+        const int64_t c = rowptr[r + 1] - rowptr[r];
+        long_rows += c >= kDenseRow;
+        if (c >= kDenseRow2d) {
+            ++heavy;
+        } else {
+            light += c;
+            busiest = std::max(busiest, c);
+        }
+    }
+    if (long_rows > kFoldRows || p->m > kFoldAll) return false;
+    if (p->H[0] < 256 && p->m <= kFoldNodes) return true;
+    // with 1024 points along y a thread has two rows and fetches two nodes of each at once
+    return heavy <= kFoldRows && light <= kFoldLight && busiest <= (p->P[1] > 512 ? 2 : kDenseRow2d - 1);
+}
 
 int plan_create_impl(bemfft_plan *p, const bemfft_grid *grid, int64_t m, const double *nodes,
                      const double *normals, const double *weights, int kernel, double nu, double mu,
@@ -475,11 +518,13 @@ int plan_create_impl(bemfft_plan *p, const bemfft_grid *grid, int64_t m, const d
     }
     for (size_t i = 1; i < rowptr.size(); ++i) rowptr[i] += rowptr[i - 1];
     // long rows get their x-transform from a row FFT
+    const bool fold = p->dim == 2 && fold_rule(p, rowptr);
+    const int dense = p->dim == 2 && !fold ? kDenseRow2d : kDenseRow;
     std::vector<int> row_dense((size_t)p->nzo * ny, -1), dense_rows;
     for (int64_t z = 0; z < p->nzo; ++z) {
         for (int64_t y = 0; y < ny; ++y) {
             const int64_t row = z * ny + y;
-            if (rowptr[row + 1] - rowptr[row] >= kDenseRow) {
+            if (rowptr[row + 1] - rowptr[row] >= dense) {
                 row_dense[row] = (int)dense_rows.size();
                 dense_rows.push_back((int)row);
             }
@@ -490,14 +535,16 @@ int plan_create_impl(bemfft_plan *p, const bemfft_grid *grid, int64_t m, const d
         int64_t busiest = 0;  // nodes of the busiest row that is not a long row
         for (size_t row = 0; row + 1 < rowptr.size(); ++row) {
             const int64_t c = rowptr[row + 1] - rowptr[row];
-            if (c < kDenseRow) busiest = std::max(busiest, c);
+            if (c < dense) busiest = std::max(busiest, c);
         }
         p->fwd_xg = busiest <= kFewNodesRow ? 2 : 1;
     }
     {
         int64_t long_nodes = 0;
         for (int r : dense_rows) long_nodes += rowptr[r + 1] - rowptr[r];
-        p->all_long = p->dim == 2 && long_nodes == m;
+        if (p->dim == 2)
+            p->flat = (fold ? kFlatFold : 0) |
+                      (long_nodes == m ? kFlatRows : m <= (p->O == 1 ? kWideNodes : 2 * kWideNodes) ? kFlatWide : 0);
         p->mixed_rows = p->nd > 0 && long_nodes < m;
         p->row_inv = (double)long_nodes * (double)p->H[0] * p->O > kRowInvWork ? 1 : 0;
     }

@@ -21,7 +21,7 @@
 //
 // 2D plans: k_mid2d takes the place of the first three (one kx per block, no Y
 // and Z), with the fields folded in for few nodes; k_gather_wide or
-// k_rows_gather that of the last where flat_path says so.
+// k_rows_gather that of the last where the plan's kFlat bits say so.
 //
 // Layout: complex intermediates are interleaved (re, im) in the working
 // precision R.  Y is tiled for the z pass, [f][kx][ky / KT][z][KT] (the 16-bit
@@ -61,7 +61,7 @@ struct ApplyArgs {
     const int *row_dense;   // [nzo * ny]: index into dense_rows, or -1
     const int *dense_rows;  // [nd]: row index (zz * ny + y) of each long row
     int nd;
-    int all_long;           // 2D: every node lies in a long row
+    int flat;               // 2D: the kernels of the plan, kFlat bits
     int row_inv;            // 1: the long rows' inverse x transform is an FFT (k_rows_inv)
     int fwd_xg;             // kx per thread in the forward direct DFT (1 or 2)
     void *Y, *Z;
@@ -81,20 +81,15 @@ struct GroupDims {
     int max_m, max_nd, max_nzo;
     int hx, px, py;
     int row_inv;  // some member takes the row FFT for its long rows
-    int flat;     // 2D: flat_path of every member
+    int flat;     // 2D: kFlat bits of every member
     const ZRange *z;  // 3D: host array of nz ranges
     int nz;
 };
 
-// The 2D kernels that a plan takes, a rule on its nodes (m, nd long rows) so
-// that a batch's members take their own plan's (bit 0: k_mid2d with the fields
-// folded in, bit 1: k_gather_wide, bit 2: k_rows_gather).
-constexpr int kFoldNodes = 4096, kFoldRows = 8, kWideNodes = 8192, kWaveRow = 8;
+// The 2D kernels that a plan takes (flat_rule in api.hip; a batch's members take
+// their own plan's): k_mid2d with the fields folded in, k_gather_wide, k_rows_gather.
 constexpr int kFlatFold = 1, kFlatWide = 2, kFlatRows = 4;
-
-inline int flat_path(int64_t m, int64_t nd, int all_long) {
-    return (m <= kFoldNodes && nd <= kFoldRows ? kFlatFold : 0) | (all_long ? kFlatRows : m <= kWideNodes ? kFlatWide : 0);
-}
+constexpr int kWaveRow = 8;  // longer rows are summed by a wavefront in the folded form
 
 // Base pointers of a batched apply (device memory, so that a captured graph
 // of the launches serves any call) and the members still iterating.
@@ -770,7 +765,7 @@ __global__ __launch_bounds__((ZCfg<R, SH, KIND>::NT), 2) void kb_zpass(const App
 // nodes are summed by their wavefront (one round of loads instead of a chain of
 // them; long rows always, others unless a wavefront has many), which saves the launch before (fields and long-row
 // transforms, 7.9 us on the square).  Each block then reads every node's data,
-// so this is for few nodes and few long rows (flat_path).
+// so this is for few nodes and few long rows.
 template <typename R, int PY, int KIND>
 struct Mid2dCfg {
     static constexpr int F = Terms<KIND>::F, O = Terms<KIND>::O;
@@ -1599,7 +1594,7 @@ struct Launch {
     template <int P> static int fwd(const ApplyArgs &a, hipStream_t st) { return launch_fwd<R, P, KIND>(a, st); }
     template <int P> static int rows(const ApplyArgs &a, hipStream_t st) {
         using Cfg = RowCfg<R, P, KIND>;
-        const int nfb = a.all_long ? 0 : (a.m + 255) / 256;  // long rows take q and u themselves
+        const int nfb = a.flat & kFlatRows ? 0 : (a.m + 255) / 256;  // long rows take q and u themselves
         const int nrb = a.nd;  // one block per long row
         hipLaunchKernelGGL((k_fields_rows<R, P, KIND>), dim3(nfb + nrb), dim3(256), 0, st, a, nfb);
         BF_HIP(hipGetLastError());
@@ -1641,7 +1636,7 @@ struct Launch {
     static int front(const ApplyArgs &a, int all_rows, hipStream_t st, hipEvent_t *ev = nullptr) {
         if (ev) BF_HIP(hipEventRecord(ev[0], st));
         if constexpr (FLAT) {
-            const bool fold = flat_path(a.m, a.nd, a.all_long) & kFlatFold;
+            const bool fold = a.flat & kFlatFold;
             if (!fold) BF_CHECK(a.nd > 0 ? dispatch_rows(a, st) : fields(a, st));
             if (ev) BF_HIP(hipEventRecord(ev[1], st));
             BF_CHECK(dispatch_mid(a, fold, all_rows, st));
@@ -1671,13 +1666,12 @@ struct Launch {
     }
     // W -> r
     static int back(const ApplyArgs &a, hipStream_t st) {
-        const int flat = FLAT ? flat_path(a.m, a.nd, a.all_long) : 0;
         if constexpr (FLAT) {
-            if (flat & kFlatRows) return dispatch_rows_gather(a, st);
+            if (a.flat & kFlatRows) return dispatch_rows_gather(a, st);
         }
         if (a.nd > 0 && a.row_inv) BF_CHECK(dispatch_rows_inv(a, st));
         if constexpr (FLAT) {
-            if (flat & kFlatWide)
+            if (a.flat & kFlatWide)
                 return a.px >= 1024 ? gather_wide<64>(a, st) : a.px >= 512 ? gather_wide<32>(a, st) : gather_wide<16>(a, st);
         }
         return gather(a, st);

@@ -397,14 +397,13 @@ int bemfft_batch_create(bemfft_batch **out, bemfft_plan *const *plans, int nplan
     std::map<std::tuple<int64_t, int64_t, int>, int> gidx;
     for (int k = 0; k < nm && status == 0; ++k) {
         bemfft_plan *p = plans[b->mem_plan[k]];
-        const int flat = p->dim == 2 ? flat_path(p->m, p->nd, p->all_long) : 0;
-        auto key = std::make_tuple(p->P[0], p->P[1], flat);
+        auto key = std::make_tuple(p->P[0], p->P[1], p->flat);
         auto it = gidx.find(key);
         if (it == gidx.end()) {
             Group g;
             g.kernel = b->kernel;
             g.precision = b->precision;
-            g.dims = GroupDims{0, 0, 0, 0, (int)p->H[0], (int)p->P[0], (int)p->P[1], 0, flat, nullptr, 0};
+            g.dims = GroupDims{0, 0, 0, 0, (int)p->H[0], (int)p->P[0], (int)p->P[1], 0, p->flat, nullptr, 0};
             gidx[key] = (int)b->groups.size();
             b->groups.push_back(g);
             it = gidx.find(key);

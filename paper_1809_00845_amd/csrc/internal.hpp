@@ -81,7 +81,7 @@ struct bemfft_plan {
     int *d_row_dense = nullptr;   // [nzo * ny] long-row index or -1
     int *d_dense_rows = nullptr;  // [nd]
     int64_t nd = 0;               // rows whose x-transform is an FFT
-    int all_long = 0;             // 2D: every node lies in a long row
+    int flat = 0;                 // 2D: kernels of the plan (kFlat bits)
     int mixed_rows = 0;           // some nodes lie in long rows and some do not
     int row_inv = 0;              // their inverse x transform is an FFT too
     int fwd_xg = 1;               // kx per thread in the forward direct DFT

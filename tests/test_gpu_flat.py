@@ -1,8 +1,10 @@
-"""2D plans at the limits of their kernels' rules: node counts and long rows on
-both sides of where the fields are folded into the transform kernel (4096 nodes,
-8 long rows), where the node sums go wide (8192 nodes) and where every node lies
-in a long row; rows of 1 to nx nodes around the sizes where a thread, a wavefront
-or an FFT sums them (8, 24, and several rounds of a wavefront); every padded
+"""2D plans at the limits of their kernels' rules: node counts and rows on both
+sides of where the fields are folded into the transform kernel (three rows of 24 or
+more; 1792 nodes below 512 points along x; three rows of 8 or more beside 1152 other
+nodes, in rows of at most two where Py = 1024), where the node sums go wide (4096
+nodes, 8192 with three outputs) and where every node lies in a long row (8 or
+more, 24 in the folded form); rows of 1 to nx nodes around the sizes where a thread,
+a wavefront or an FFT sums them (and several rounds of a wavefront); every padded
 length on either axis.  Bars: normwise against the direct sums, 1e-12 in FP64,
 2e-5 in FP32, as for ordinary geometries: they grow with log P only."""
 
@@ -47,7 +49,29 @@ def spread(total, rows, ny, most):
 
 MIXED = [1, 0, 8, 9, 23, 24, 2, 64, 65, 0, 16, 3]
 CASES = {
-    # fold limits: 8 and 9 long rows; 4096 and 4097 nodes
+    # the folded form's limits: long rows, nodes of a short transform
+    "long3": (100, 40, [30] * 3 + [2] * 37),
+    "long4": (100, 40, [30] * 4 + [2] * 36),
+    "m1792": (128, 128, [14] * 128),
+    "m1793": (128, 128, [15] + [14] * 127),
+    "m4100": (128, 400, [120] + [10] * 398 + [0]),
+    # of a longer one: heavy rows, other nodes, rows of two at 1024 points
+    "heavy3": (200, 200, [23, 8, 100] + [5] * 197),
+    "heavy4": (200, 200, [23, 8, 100, 8] + [5] * 196),
+    "heavy4x256": (256, 200, [23, 8, 100, 8] + [5] * 196),
+    "m1792x384": (192, 128, [14] * 128),
+    "m1793x384": (192, 128, [15] + [14] * 127),
+    "light1152": (256, 256, [5] * 128 + [4] * 128),
+    "light1153": (256, 256, [5] * 129 + [4] * 127),
+    "two1024": (300, 512, [2] * 500 + [0] * 11 + [300]),
+    "three1024": (300, 512, [2] * 500 + [3] + [0] * 10 + [300]),
+    # rows of 7 and 8 nodes side by side, every row of 8
+    "rows78": (512, 256, [7, 8] * 128),
+    "rows8": (512, 256, [8] * 256),
+    # wide sums: 4096 and 4097 nodes
+    "wide4096": (512, 512, [7] * 448 + [15] * 64),
+    "wide4097": (512, 512, [7] * 448 + [15] * 63 + [16]),
+    # long rows and node counts of several rounds
     "long8": (100, 40, [30] * 8 + [2] * 32),
     "long9": (100, 40, [30] * 9 + [2] * 31),
     "m4096": (250, 250, spread(4096, 250, 250, 23)),
