@@ -766,6 +766,13 @@ __global__ __launch_bounds__((ZCfg<R, SH, KIND>::NT), 2) void kb_zpass(const App
 // them; long rows always, others unless a wavefront has many), which saves the launch before (fields and long-row
 // transforms, 7.9 us on the square).  Each block then reads every node's data,
 // so this is for few nodes and few long rows.
+//
+// LEAN, for batches: the fields come from k_fields' buffer and fewer nodes are
+// fetched at a time (the sums keep their order, so a member has its plan's bits).  Many
+// members fill the chip, and then wavefronts count, not latency: 63 registers
+// against 224 for the folded form at 256 points in FP32.  32 circles on 128^2, us:
+// folded from q and u 72 (FP32) and 87 (FP64), lean 37 and 56; 32 discs of 0.15 on
+// 256^2 FP64, not folded, 183 and 141.
 template <typename R, int PY, int KIND>
 struct Mid2dCfg {
     static constexpr int F = Terms<KIND>::F, O = Terms<KIND>::O;
@@ -792,15 +799,15 @@ __device__ __forceinline__ int term_comp2d(int o, int f) {
     }
 }
 
-template <typename R, int PY, int KIND, bool FOLD>
+template <typename R, int PY, int KIND, bool FOLD, bool LEAN = false>
 __device__ __forceinline__ void mid2d_body(const ApplyArgs &a, const int kx, const int all_rows) {
     using Cfg = Mid2dCfg<R, PY, KIND>;
     constexpr int F = Cfg::F, O = Cfg::O, TPP = Cfg::TPP, E = Cfg::E, PS = Cfg::PS, NT = Cfg::NT;
     using SH = typename Cfg::SH;
     constexpr int NS = O == 1 ? 1 : F;              // spectra per thread
     constexpr int NR = (PY / 2 + NT - 1) / NT;      // grid rows per thread
-    constexpr int CH = NR > 1 ? 2 : 8;              // nodes of a row fetched together
-    constexpr int WS = NR > 1 ? 1 : 2, WC = 2;      // and rows of the wavefront's, nodes per lane
+    constexpr int CH = LEAN || NR > 1 ? 2 : 8;      // nodes of a row fetched together
+    constexpr int WS = LEAN || NR > 1 ? 1 : 2, WC = 2;  // and rows of the wavefront's, nodes per lane
     __shared__ cx<R> buf[F * PS];
     __shared__ cx<R> twl[Cfg::TWL ? PY : 1];
     __shared__ unsigned char keep[PY / 2];
@@ -850,7 +857,7 @@ __device__ __forceinline__ void mid2d_body(const ApplyArgs &a, const int kx, con
             const bool in = s + k * stride < s1;
             const int sk = in ? s + k * stride : 0;
             w[k] = twt[mod_small(kx, a.gx[sk], a.px, inv_px)];
-            if constexpr (FOLD) {
+            if constexpr (FOLD && !LEAN) {
                 node_fields<R, KIND>(a, sk, v[k]);
             } else {
 #pragma unroll
@@ -1043,14 +1050,14 @@ __global__ __launch_bounds__((Mid2dCfg<R, PY, KIND>::NT), (Mid2dCfg<R, PY, KIND>
     if (kx >= 0) mid2d_body<R, PY, KIND, FOLD>(a, kx, all_rows);
 }
 
-template <typename R, int PY, int KIND, bool FOLD>
+template <typename R, int PY, int KIND, bool FOLD, bool LEAN>
 __global__ __launch_bounds__((Mid2dCfg<R, PY, KIND>::NT), (Mid2dCfg<R, PY, KIND>::WPE)) void kb_mid2d(const ApplyArgs *members, const BatchIO *io) {
     ApplyArgs a = members[blockIdx.z];
     if (io->active && !io->active[a.gid]) return;
     a.q = io->q + a.off;
     a.u = io->u + a.off;
     const int kx = xcd_item(blockIdx.x, a.hx);
-    if (kx >= 0) mid2d_body<R, PY, KIND, FOLD>(a, kx, 0);
+    if (kx >= 0) mid2d_body<R, PY, KIND, FOLD, LEAN>(a, kx, 0);
 }
 
 // ------------------------------------------------------------------ k_inv_y
@@ -1728,15 +1735,26 @@ struct Launch {
         return BEMFFT_EUNSUPPORTED;
     }
     template <int P>
-    static int bmid(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, bool fold, hipStream_t st) {
+    static int bmid(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, bool fold, bool lean, hipStream_t st) {
         const dim3 grid(8 * ((g.hx + 7) / 8), 1, g.nmem), block(Mid2dCfg<R, P, KIND>::NT);
-        if (fold) hipLaunchKernelGGL((kb_mid2d<R, P, KIND, true>), grid, block, 0, st, dm, io);
-        else hipLaunchKernelGGL((kb_mid2d<R, P, KIND, false>), grid, block, 0, st, dm, io);
+        if (fold && lean) hipLaunchKernelGGL((kb_mid2d<R, P, KIND, true, true>), grid, block, 0, st, dm, io);
+        else if (fold) hipLaunchKernelGGL((kb_mid2d<R, P, KIND, true, false>), grid, block, 0, st, dm, io);
+        else hipLaunchKernelGGL((kb_mid2d<R, P, KIND, false, true>), grid, block, 0, st, dm, io);
         BF_HIP(hipGetLastError());
         return 0;
     }
-    static int dispatch_bmid(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, bool fold, hipStream_t st) {
-        BF_SIZE_SWITCH_K(KIND, g.py, bmid, dm, io, g, fold, st);
+    // Blocks of the folded form that stay resident, at its two wavefronts per SIMD:
+    // beyond, the lean form is faster although it takes the fields in a launch of
+    // their own (circles on 128^2 FP32, 387, 516 and 1032 blocks of 512: 15.4, 20.7 and
+    // 28.0 us, lean 16.3, 16.9 and 18.7).
+    template <int P> static int fold_resident() { return 256 * (8 / (Mid2dCfg<R, P, KIND>::NT / 64)); }
+    static int dispatch_fold_resident(int py) {
+        BF_SIZE_SWITCH_K(KIND, py, fold_resident);
+        return 0;
+    }
+    static int dispatch_bmid(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, bool fold, bool lean,
+                             hipStream_t st) {
+        BF_SIZE_SWITCH_K(KIND, g.py, bmid, dm, io, g, fold, lean, st);
         set_error("unsupported y length");
         return BEMFFT_EUNSUPPORTED;
     }
@@ -1821,14 +1839,18 @@ struct Launch {
         return BEMFFT_EUNSUPPORTED;
     }
     static int run_batch(const ApplyArgs *dm, const BatchIO *io, const GroupDims &g, hipStream_t st) {
-        const bool fold = FLAT && (g.flat & kFlatFold);
-        if (!fold) {
+        bool fold = false, lean = true;
+        if constexpr (FLAT) {
+            fold = g.flat & kFlatFold;
+            lean = !fold || g.nmem * g.hx > dispatch_fold_resident(g.py);
+        }
+        if (lean) {
             hipLaunchKernelGGL((kb_fields<R, KIND>), dim3((g.max_m + 255) / 256, 1, g.nmem), dim3(256), 0, st, dm, io, 1);
             BF_HIP(hipGetLastError());
-            if (g.max_nd > 0) BF_CHECK(dispatch_brows(dm, io, g, st));
+            if (!fold && g.max_nd > 0) BF_CHECK(dispatch_brows(dm, io, g, st));
         }
         if constexpr (FLAT) {
-            BF_CHECK(dispatch_bmid(dm, io, g, fold, st));
+            BF_CHECK(dispatch_bmid(dm, io, g, fold, lean, st));
         } else {
             BF_CHECK(dispatch_bfwd(dm, io, g, st));
             for (int i = 0; i < g.nz; ++i) BF_CHECK(dispatch_bz(dm, io, g, g.z[i], st));

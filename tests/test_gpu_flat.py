@@ -117,3 +117,32 @@ def test_flat_rules(dev, name, kernel):
         assert torch.equal(r.reshape(-1), rb.reshape(-1))
         batch.close()
         plan.close()
+
+
+# right-hand sides on both sides of the blocks that the folded form keeps resident
+# (256 CUs of two wavefronts per SIMD: 512 blocks of three or four wavefronts, 2048 of one)
+MANY = [("m1792", 3), ("m1792", 4), ("heavy3", 1), ("heavy3", 2), ("two1024", 2), ("light1152", 2), ("long3", 15),
+        ("long3", 16), ("mixed64", 33), ("rows78", 3), ("heavy", 5)]
+
+
+@pytest.mark.parametrize("name,nrhs", MANY)
+@pytest.mark.parametrize("kernel", [B.LAPLACE2D, B.HALFSPACE])
+def test_batches_of_many_members(dev, name, nrhs, kernel):
+    """Batches that fill the chip take the lean form of the transform kernel: every
+    member has its plan's bits."""
+    nx, ny, counts = CASES[name]
+    g = rows_geometry(nx, ny, counts, seed=len(name))
+    n = (3 if kernel == B.HALFSPACE else 1) * g.m
+    rng = np.random.default_rng(6)
+    q, u = (torch.tensor(rng.uniform(-1, 1, (nrhs, n)), device=dev) for _ in range(2))
+    for prec in (B.FP64, B.FP32):
+        plan = B.Plan(g, kernel, precision=prec, nu=0.3, mu=1.0)
+        batch = B.Batch([plan], nrhs=nrhs, use_graph=True)
+        ref = torch.stack([plan.apply(q[i], u[i]) for i in range(nrhs)])
+        for _ in range(3):
+            r = torch.full_like(q, float("nan"))
+            batch.apply(q.reshape(-1), u.reshape(-1), r)
+            assert torch.equal(r, ref)
+            _ = (q * 2.0).sum().item()  # eager work between replays
+        batch.close()
+        plan.close()
