@@ -665,6 +665,36 @@ int num_zsched(const bemfft_plan *p) {
     return (p->kernel == BEMFFT_NAVIER3D && (pad == 256 || pad == 384 || pad == 512)) ? 3 : 2;
 }
 
+// First schedule that is the same as s at the plan's z length: some lengths have
+// fewer different ones than numbers.
+template <bool N, bool F, int P>
+int z_first_of(int s) {
+    if constexpr (N) {
+        if (s == 2) return z_first<N, F, P, 2>();
+    }
+    return s == 1 ? z_first<N, F, P, 1>() : 0;
+}
+template <bool N, bool F>
+int z_first_at(int64_t pz, int s) {
+    switch (pz) {
+        case 32: return z_first_of<N, F, 32>(s);
+        case 64: return z_first_of<N, F, 64>(s);
+        case 96: return z_first_of<N, F, 96>(s);
+        case 128: return z_first_of<N, F, 128>(s);
+        case 192: return z_first_of<N, F, 192>(s);
+        case 256: return z_first_of<N, F, 256>(s);
+        case 320: return z_first_of<N, F, 320>(s);
+        case 384: return z_first_of<N, F, 384>(s);
+        case 512: return z_first_of<N, F, 512>(s);
+        default: return s;
+    }
+}
+int first_zsched(const bemfft_plan *p, int s) {
+    const bool fp64 = p->eng.precision == BEMFFT_FP64;
+    if (p->kernel == BEMFFT_NAVIER3D) return fp64 ? z_first_at<true, true>(p->P[2], s) : z_first_at<true, false>(p->P[2], s);
+    return fp64 ? z_first_at<false, true>(p->P[2], s) : z_first_at<false, false>(p->P[2], s);
+}
+
 int tune_cache_lookup(const std::string &key) {
     const char *path = std::getenv("BEMFFT_TUNE_CACHE");
     if (!path || !*path) return -1;
@@ -687,8 +717,8 @@ void tune_cache_store(const std::string &key, int v) {
     std::fclose(f);
 }
 
-// Time the working-precision apply with each compiled z schedule and keep
-// the fastest, then, with that schedule, the other number of kx per thread
+// Time the working-precision apply with each different z schedule (numbers of the
+// same one get its time) and keep the fastest, then, with that schedule, the other number of kx per thread
 // in the forward direct DFT (1 or 2) and keep the faster.
 int autotune_zsched(bemfft_plan *p, hipStream_t st) {
     const std::string key = tune_key(p);
@@ -729,8 +759,10 @@ int autotune_zsched(bemfft_plan *p, hipStream_t st) {
         *us = 1e3 * ms / reps;
     };
     for (int sched = 0; sched < nsched && status == 0; ++sched) {
+        const int first = first_zsched(p, sched);
         p->eng.zsched = sched;
-        time_apply(&p->tune_us[sched]);
+        if (first < sched) p->tune_us[sched] = p->tune_us[first];
+        else time_apply(&p->tune_us[sched]);
     }
     if (status == 0) {
         p->zsched = 0;

@@ -228,7 +228,6 @@ template <int DIR, typename R> struct DFT<8, DIR, R> : DFTSplit<8, 2, 4, DIR, R>
 template <int DIR, typename R> struct DFT<10, DIR, R> : DFTSplit<10, 2, 5, DIR, R> {};
 template <int DIR, typename R> struct DFT<12, DIR, R> : DFTSplit<12, 3, 4, DIR, R> {};
 template <int DIR, typename R> struct DFT<16, DIR, R> : DFTSplit<16, 4, 4, DIR, R> {};
-template <int DIR, typename R> struct DFT<24, DIR, R> : DFTSplit<24, 4, 6, DIR, R> {};
 template <int DIR, typename R> struct DFT<20, DIR, R> : DFTSplit<20, 4, 5, DIR, R> {};
 
 // ------------------------------------------------------------ pencil plans

@@ -75,10 +75,15 @@ template <int S> struct ZSel<true, false, 512, S> { using type = ZShape<2, 256, 
 template <> struct ZSel<true, false, 512, 0> { using type = ZShape<2, 256, 32, 4, 271, 8, 8, 4>; };
 template <int S> struct ZSel<true, true, 512, S> { using type = ZShape<1, 512, 32, 4, 543, 8, 8, 8>; };
 template <> struct ZSel<true, true, 512, 2> { using type = ZShape<1, 512, 64, 4, 543, 8, 8, 8>; };
-// 1024 points: the y transforms of 2D plans only
-template <bool F> struct ZSel<false, F, 1024, 0> { using type = ZShape<1, 1024, 64, 4, 1087, 16, 16, 4>; };
 template <typename R, int KIND, int P, int S>
 using ZSched = typename ZSel<KIND == 2, sizeof(R) == 8, P, S>::type;
+
+// First schedule that is the same as schedule S of a length (S itself if none is).
+template <bool N, bool F, int P, int S, int T = 0>
+constexpr int z_first() {
+    if constexpr (T >= S) return S;
+    else return std::is_same<typename ZSel<N, F, P, T>::type, typename ZSel<N, F, P, S>::type>::value ? T : z_first<N, F, P, S, T + 1>();
+}
 
 // Parts D of the frequencies in the z pass and the stored spectra of a family,
 // precision and length.

@@ -182,3 +182,19 @@ def test_batch_in_branches(dev):
     batch.close()
     for p in plans:
         p.close()
+
+
+def test_autotune_times_each_schedule_once(dev):
+    """Numbers of one schedule share its time (and the first of them is kept): at 64
+    points there is one, at 96 there are two, Navier FP64 at 320 has one."""
+    for kernel, prec, pz, same in ((B.LAPLACE3D, B.FP32, 64, True), (B.LAPLACE3D, B.FP32, 96, False),
+                                   (B.NAVIER3D, B.FP64, 320, True), (B.NAVIER3D, B.FP64, 256, False)):
+        g = _Nodes((13, 10, pz // 2), 0, pz // 2 - 1)
+        plan = B.Plan(g, kernel, precision=prec, pad=(32, 32, pz), autotune=1)
+        info = plan.info()
+        plan.close()
+        t = info["tune_us"]
+        assert (t[0] == t[1]) == same and t[info["zsched"]] == min(x for x in t if x > 0)
+        assert not same or info["zsched"] == 0
+        if kernel == B.NAVIER3D and pz == 256:
+            assert t[2] > 0 and t[2] == t[0]  # 8, 8, 2 in wide tiles: schedule 0's
