@@ -651,10 +651,10 @@ int plan_create_impl(bemfft_plan *p, const bemfft_grid *grid, int64_t m, const d
     return 0;
 }
 
-// Cache entries hold zsched + 4 (fwd_xg - 1); the "3:" prefix keeps entries
+// Cache entries hold zsched + 4 (fwd_xg - 1); the "4:" prefix keeps entries
 // written for other sets of schedules from being read.
 std::string tune_key(const bemfft_plan *p) {
-    return "3:" + std::to_string(p->kernel) + ":" + std::to_string(p->eng.precision) + ":" + std::to_string(p->P[0]) +
+    return "4:" + std::to_string(p->kernel) + ":" + std::to_string(p->eng.precision) + ":" + std::to_string(p->P[0]) +
            "x" + std::to_string(p->P[1]) + "x" + std::to_string(p->P[2]) + "/" + std::to_string(num_zsched(p));
 }
 
@@ -705,7 +705,7 @@ int tune_cache_lookup(const std::string &key) {
     while (std::fscanf(f, "%127s %d", k, &v) == 2)
         if (key == k) found = v;
     std::fclose(f);
-    return (found >= 0 && found <= 2) ? found : -1;
+    return found;  // checked against the plan's schedules by the caller
 }
 
 void tune_cache_store(const std::string &key, int v) {

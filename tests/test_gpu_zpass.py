@@ -198,3 +198,22 @@ def test_autotune_times_each_schedule_once(dev):
         assert not same or info["zsched"] == 0
         if kernel == B.NAVIER3D and pz == 256:
             assert t[2] > 0 and t[2] == t[0]  # 8, 8, 2 in wide tiles: schedule 0's
+
+
+def test_autotune_cache(dev, tmp_path, monkeypatch):
+    """A second plan reads what the first one stored, for either forward width."""
+    path = tmp_path / "tune"
+    monkeypatch.setenv("BEMFFT_TUNE_CACHE", str(path))
+    g = _Nodes((20, 16, 24), 2, 20)
+    first = B.Plan(g, B.LAPLACE3D, precision=B.FP32, autotune=1)
+    a = first.info()
+    first.close()
+    key, value = path.read_text().split()
+    for stored in range(2):
+        for width in (1, 2):
+            path.write_text(f"{key} {stored + 4 * (width - 1)}\n")
+            plan = B.Plan(g, B.LAPLACE3D, precision=B.FP32, autotune=1)
+            b = plan.info()
+            plan.close()
+            assert (b["zsched"], b["fwd_xg"]) == (stored, width) and not any(b["tune_us"])
+    assert int(value) == a["zsched"] + 4 * (a["fwd_xg"] - 1)
