@@ -1844,11 +1844,11 @@ struct Launch {
             fold = g.flat & kFlatFold;
             lean = !fold || g.nmem * g.hx > dispatch_fold_resident(g.py);
         }
-        if (lean) {
+        if (lean && (fold || !(g.flat & kFlatRows))) {  // all in long rows: those take q and u themselves
             hipLaunchKernelGGL((kb_fields<R, KIND>), dim3((g.max_m + 255) / 256, 1, g.nmem), dim3(256), 0, st, dm, io, 1);
             BF_HIP(hipGetLastError());
-            if (!fold && g.max_nd > 0) BF_CHECK(dispatch_brows(dm, io, g, st));
         }
+        if (!fold && g.max_nd > 0) BF_CHECK(dispatch_brows(dm, io, g, st));
         if constexpr (FLAT) {
             BF_CHECK(dispatch_bmid(dm, io, g, fold, lean, st));
         } else {
