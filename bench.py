@@ -30,14 +30,20 @@ METRIC = "BEM matvecs/s + GMRES time-to-solve @1e-6 rel. residual; HBM roofline 
 HBM_PEAK_GBS = 8000.0
 
 
+def plan_info(plan):
+    """The plan's facts with the transform lengths in use."""
+    return dict(plan.info(), lengths=plan.lengths())
+
+
 def model_bytes(info, b):
     """The byte model of one apply (b = bytes per stored real): per field
     f = Hx Ny Nz 2b (the x-pass half spectrum), g = Hx Py Nz 2b (after the
     y pass); forward x, y: F (2f + g); fused z pass with the products:
     F g + K Hx Hy Hz b + O g; inverse y, x: O (g + 2f).  It credits the
-    zero padding, the half spectrum, the octant spectra and the fused scatter
-    and gather, not the occupancy of the boundary."""
-    px, py, pz = info["pad"]
+    zero padding (of the transform lengths in use), the half spectrum, the
+    octant spectra and the fused scatter and gather, not the occupancy of the
+    boundary."""
+    px, py, pz = info["lengths"]
     hx, hy, hz = px // 2 + 1, py // 2 + 1, pz // 2 + 1
     ny, nz = info["n"][1], info["n"][2]
     F, K, O = info["nfields"], info["nspectra"], info["noutputs"]
@@ -65,8 +71,8 @@ def stage_bytes(info, prec_bytes, arith_bytes=None):
     included).  prec_bytes: stored real (Y, Z, spectra); arith_bytes: real
     of the inverse-y rows and the node fields (default prec_bytes)."""
     ab = arith_bytes or prec_bytes
-    px, py, pz = info["pad"]
-    hx, hy, hz = px // 2 + 1, py // 2 + 1, pz // 2 + 1
+    px, py, _ = info["lengths"]
+    hx = px // 2 + 1
     nzo = info["z_count"]
     F, K, O, m = info["nfields"], info["nspectra"], info["noutputs"], info["m"]
     cb = 2 * prec_bytes
@@ -106,8 +112,8 @@ def zpass_alu_view(info, ms):
     transform (4 forward, 1 inverse per pencil for Laplace 3D) plus 4 flops
     per spectral product, over Hx * Py pencils.  Packed FP32 instructions are
     not used, so the peak is half the chip's 157.3 TFLOP/s."""
-    P = info["pad"][2]
-    hx, py = info["pad"][0] // 2 + 1, info["pad"][1]
+    px, py, P = info["lengths"]
+    hx = px // 2 + 1
     per_pencil = 5 * 5 * P * math.log2(P) + 4 * info["nspectra"] * P
     flops = per_pencil * hx * py
     tf = flops / (ms * 1e-3) / 1e12
@@ -361,12 +367,16 @@ def bench_batched(B, I, dev, steps=20, count=64, nrhs=4):
         p_.close()
     os.unlink(tune.name)
     sizes = sorted(set(n for n, _ in items))
+    mb = nrhs * sum(sum(stage_bytes(plan_info(p), 4).values()) for p in plans)
     out = {
         "workload": "64 star surfaces (seed 2), grids {64,96,128,160}^3 padded 2N, 4 Dirichlet RHS each",
         "members": nm, "nodes_total": int(sum(g.m for g in geoms)),
         "grid_counts": {str(n): sum(1 for m_, _ in items if m_ == n) for n in sizes},
-        "groups_by_pad_and_schedule": len(set((p.info()["pad"][0], p.info()["zsched"]) for p in plans)),
+        "groups_by_xy_lengths": len(set(tuple(p.lengths()[:2]) for p in plans)),
+        "z_passes": len(set((*p.lengths(), p.info()["zsched"]) for p in plans)),
         "batched_apply_ms": dt_b * 1e3, "batched_rhs_matvec_s": nm / dt_b,
+        # bytes that the stages must move (occupied planes, lengths in use)
+        "batched_apply_bytes": mb, "batched_apply_gbs": mb / dt_b / 1e9,
         "per_plan_apply_ms": dt_s * 1e3, "per_plan_rhs_matvec_s": nm / dt_s,
         "batched_solve_fp32_s": t_bsolve, "batched_solve_status": st,
         "batched_solve_iters_max": int(max(its)), "batched_solve_iters_mean": float(np.mean(its)),
@@ -408,7 +418,7 @@ def bench_navier_star(B, I, dev, steps, mixed=True):
         pl = B.Plan(g, B.NAVIER3D, precision=prec, nu=0.3, mu=1.0, keep_fp64=prec != B.FP64,
                     autotune=1 if prec != B.BF16_MFMA else 0)
         plans[tag] = pl
-        inf = pl.info()
+        inf = plan_info(pl)
         n = max(10, steps // (10 if prec == B.FP64 else 4))
         st = B.bemfft_apply_profile(pl.handle, q, u, r, reps=20)
         kern = "k_zpass16" if prec == B.BF16_MFMA else "k_zpass"
@@ -484,7 +494,7 @@ def bench_cube_bf16(B, I, dev, cube, q, u, steps):
 
     r = torch.empty_like(u)
     pl = B.Plan(cube, B.LAPLACE3D, precision=B.BF16_MFMA, keep_fp64=True)
-    inf = pl.info()
+    inf = plan_info(pl)
     names = ["fwd_xy", "zpass", "inv_y", "gather"]
     st = B.bemfft_apply_profile(pl.handle, q, u, r, reps=max(20, steps // 4))
     out = {"matvec_s": steps / timed_applies(pl, q, u, r, steps, 5),
@@ -689,7 +699,7 @@ def main():
         print(json.dumps({"workload": "laplace3d cube 128^3 16-bit applies", "matvec_s": args.steps / dt}), flush=True)
         return
     plan = B.Plan(cube, B.LAPLACE3D, precision=B.FP32, keep_fp64=True, autotune=1)
-    info = plan.info()
+    info = plan_info(plan)
     if args.grid_eval_only:
         print(json.dumps({"workload": "laplace3d cube 128^3 grid-box evaluation, fp32",
                           **bench_grid_eval(plan, q, u, info, args.steps)}), flush=True)

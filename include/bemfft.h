@@ -108,7 +108,11 @@ typedef enum { BEMFFT_C_HALF = 0, BEMFFT_C_USER = 1, BEMFFT_C_IMPLICIT = 2 } bem
  * axis; 0 picks the smallest supported even length >= 2 n[a] (Sec. 4 pads the
  * space for the FFT without fixing the size).  Supported lengths: 32, 64,
  * 96, 128, 192, 256, 320, 384, 512, and 1024 on 2D grids; so n[a] <= 512 in
- * 2D and <= 256 in 3D (EINVAL beyond, EUNSUPPORTED for other pad values). */
+ * 2D and <= 256 in 3D (EINVAL beyond, EUNSUPPORTED for other pad values).
+ * With pad[2] = 0 an FP64 or FP32 plan transforms only the planes that hold
+ * nodes along z: at the smallest supported length >= 2 z_count - 1 (Navier:
+ * 384 in place of 320) where that is shorter.  bemfft_plan_get_lengths gives
+ * the lengths in use. */
 typedef struct {
     int dim;
     int64_t n[3];
@@ -136,9 +140,11 @@ typedef struct {
                                    the file named by BEMFFT_TUNE_CACHE, if
                                    set),
                                    2 + s schedule s: 0 and 1 always exist; 2
-                                   only for Navier plans with padded z length
-                                   256, 384 or 512 (else the default is
-                                   kept).  Other values: EINVAL.            */
+                                   only for Navier plans with pad[2] 256, 384
+                                   or 512, asked for or picked for the grid
+                                   (else the default is kept); at some
+                                   lengths several are the same.  Other
+                                   values: EINVAL.                          */
     int cell_quad;              /* kernel values at grid offsets m != 0
                                    (Sec. 4 / Fig. 5 discretises the kernels
                                    as constants per element): 0 or 1 the
@@ -186,10 +192,12 @@ int bemfft_apply(bemfft_plan *p, const double *q, const double *u, double *r, vo
 
 /*
  * Same as bemfft_apply, repeated 'reps' times with HIP events recorded on
- * 'stream' between the four stages (scatter + x/y transforms, z transform +
- * spectral products, inverse y transform, gather at the nodes); stage_ms[4]
- * receives the mean duration of each stage in milliseconds.  Synchronises
- * the stream.  For measurement only.  Errors: EINVAL, EDEVICE.
+ * 'stream' between the four stages; stage_ms[4] receives the mean duration of
+ * each in milliseconds.  3D plans: scatter + x/y transforms, z transform +
+ * spectral products, inverse y transform, gather at the nodes.  2D plans:
+ * fields + long rows' x transforms (nothing where they are folded into the
+ * next), x sums + y transforms both ways + products, nothing, gather.
+ * Synchronises the stream.  For measurement only.  Errors: EINVAL, EDEVICE.
  */
 int bemfft_apply_profile(bemfft_plan *p, const double *q, const double *u, double *r, int reps,
                          double *stage_ms, void *stream);
@@ -322,9 +330,10 @@ int bemfft_solve_cg(bemfft_plan *p, const double *u, double *q, const bemfft_sol
 typedef struct bemfft_batch bemfft_batch;
 
 /* Build a batch of nplans plans x nrhs right-hand sides.  Members of plans
- * with equal padded sizes and z schedule share one launch per stage.  With
- * use_graph = 1 the launch sequence is captured once into a HIP graph that
- * every batched apply replays.  Errors: EINVAL (mixed families/precisions),
+ * with equal x and y lengths (2D: whose plans also take the same kernels)
+ * share one launch per stage; the z pass is one launch per z length in use and
+ * schedule.  With use_graph = 1 the launch sequence is captured once into a
+ * HIP graph that every batched apply replays.  Errors: EINVAL (mixed families/precisions),
  * ENOMEM, EDEVICE. */
 int bemfft_batch_create(bemfft_batch **out, bemfft_plan *const *plans, int nplans, int nrhs, int use_graph,
                         void *stream);
@@ -374,7 +383,7 @@ int bemfft_eval_grid(bemfft_plan *p, const double *q, const double *u, double *o
 typedef struct {
     int dim, kernel, precision, c_mode;
     int64_t m, ncomp;
-    int64_t n[3], pad[3];
+    int64_t n[3], pad[3];        /* pad: as asked for or picked for the grid   */
     int64_t z_lo, z_count;       /* occupied grid planes along the last axis   */
     int64_t nfields, nspectra, noutputs;
     int64_t workspace_bytes, spectra_bytes;
@@ -384,7 +393,8 @@ typedef struct {
     int zsched;                  /* radix schedule in use for the z transform
                                     (0, 1 or 2)                               */
     double tune_us[3];           /* autotune: mean apply time per schedule, us
-                                    (0 for schedules not timed)               */
+                                    (numbers of the same schedule share its
+                                    time, 0 for those that were not timed)    */
     int fwd_xg;                  /* kx per thread in the forward direct DFT
                                     (1 or 2): from the row lengths, or timed
                                     by autotune = 1                           */
@@ -393,6 +403,10 @@ typedef struct {
 } bemfft_plan_info;
 
 int bemfft_plan_get_info(const bemfft_plan *p, bemfft_plan_info *info);
+
+/* Transform lengths in use per axis (1 along z in 2D): those of the plan info's
+ * pad, or a shorter one along z (see bemfft_grid).  Errors: EINVAL. */
+int bemfft_plan_get_lengths(const bemfft_plan *p, int64_t lengths[3]);
 
 /* Copy the free-term values c_j in use (host; m or m*9 doubles). */
 int bemfft_plan_get_c(const bemfft_plan *p, double *c_host);
@@ -417,8 +431,9 @@ int bemfft_plan_destroy(bemfft_plan *p);
  * Parameters are FP32, laid out per layer as W[cout][cin][27] (tap index
  * (dz+1)*9 + (dy+1)*3 + (dx+1)) followed by b[cout].  Arithmetic and
  * activations are FP32.  Training minimises sum_i wt_i (y(vox_i) - t_i)^2
- * with Adam (beta 0.9 / 0.999, eps 1e-8).  A network owns its activations
- * (2 * layers * 16 * n^3 floats) and is used by one stream at a time.
+ * with Adam (beta 0.9 / 0.999, eps 1e-8).  A network owns its activations and
+ * their gradients ((16 * layers + 56) * n^3 floats) and is used by one stream at
+ * a time.
  */
 typedef struct bemfft_net bemfft_net;
 

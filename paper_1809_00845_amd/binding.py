@@ -62,7 +62,7 @@ EXPORTS = [
     "bemfft_batch_members", "bemfft_batch_destroy", "bemfft_net_create", "bemfft_net_destroy",
     "bemfft_net_num_params", "bemfft_net_get_params", "bemfft_net_set_params", "bemfft_net_input",
     "bemfft_net_forward", "bemfft_net_infer", "bemfft_net_gradients", "bemfft_net_train_step", "bemfft_net_guess",
-    "bemfft_plan_node_voxels", "bemfft_eval_grid", "bemfft_solve_cg", "bemfft_solve_noalloc",
+    "bemfft_plan_get_lengths", "bemfft_plan_node_voxels", "bemfft_eval_grid", "bemfft_solve_cg", "bemfft_solve_noalloc",
 ]
 
 NOALLOC_SCRATCH_BYTES = 32 << 20  # BEMFFT_NOALLOC_SCRATCH_BYTES
@@ -98,6 +98,7 @@ def load():
     L.bemfft_solve_cg.argtypes = [vp, vp, vp, ctypes.POINTER(bemfft_solve_opts), ctypes.POINTER(bemfft_solve_info),
                                   vp]
     L.bemfft_plan_get_info.argtypes = [vp, ctypes.POINTER(bemfft_plan_info)]
+    L.bemfft_plan_get_lengths.argtypes = [vp, ctypes.POINTER(i64)]
     L.bemfft_plan_get_c.argtypes = [vp, dp]
     L.bemfft_plan_destroy.argtypes = [vp]
     L.bemfft_fft3d_c2c_f64.argtypes = [vp, i64, i64, i64, ctypes.c_int, vp]
@@ -256,7 +257,8 @@ def bemfft_eval_grid(plan, q, u, out, stream=None, n=None):
 
 
 def bemfft_apply_profile(plan, q, u, r, reps=10, stream=None, n=None):
-    """Mean per-stage milliseconds (fwd_xy, zpass, inv_y, gather)."""
+    """Mean per-stage milliseconds (3D: fwd_xy, zpass, inv_y, gather; 2D: fields, all
+    transforms, nothing, gather)."""
     n = _plan_len(plan, n)
     ms = (ctypes.c_double * 4)()
     _check(load().bemfft_apply_profile(plan, _f64(q, n, "q"), _f64(u, n, "u"), _f64(r, n, "r"), int(reps), ms,
@@ -310,6 +312,13 @@ def bemfft_plan_get_info(plan):
         v = getattr(info, name)
         out[name] = list(v) if not isinstance(v, (int, float)) else v
     return out
+
+
+def bemfft_plan_get_lengths(plan):
+    """Transform lengths in use per axis (along z possibly shorter than the pad)."""
+    buf = (ctypes.c_int64 * 3)()
+    _check(load().bemfft_plan_get_lengths(plan, buf), "bemfft_plan_get_lengths")
+    return list(buf)
 
 
 def bemfft_plan_get_c(plan, m, ncomp):
@@ -392,6 +401,9 @@ class Plan:
 
     def info(self):
         return bemfft_plan_get_info(self.handle)
+
+    def lengths(self):
+        return bemfft_plan_get_lengths(self.handle)
 
     def c(self):
         return bemfft_plan_get_c(self.handle, self.m, self.ncomp)

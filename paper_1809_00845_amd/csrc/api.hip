@@ -907,6 +907,15 @@ int bemfft_plan_get_info(const bemfft_plan *p, bemfft_plan_info *info) {
     return 0;
 }
 
+int bemfft_plan_get_lengths(const bemfft_plan *p, int64_t lengths[3]) {
+    if (!p || !lengths) {
+        set_error("null argument");
+        return BEMFFT_EINVAL;
+    }
+    for (int a = 0; a < 3; ++a) lengths[a] = p->P[a];
+    return 0;
+}
+
 int bemfft_plan_get_c(const bemfft_plan *p, double *c_host) {
     if (!p || !c_host) {
         set_error("null argument");

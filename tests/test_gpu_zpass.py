@@ -52,7 +52,7 @@ def _check(dev, g, kernel, prec, **kw):
     # a first apply on other data: nothing of it may reach the second one
     plan.apply(t(1e3 * u), t(1e3 * q))
     r = plan.apply(t(q), t(u)).cpu().numpy().reshape(nc, m)
-    info = plan.info()
+    info = dict(plan.info(), lengths=plan.lengths())
     plan.close()
     p = O.problem(g, KIND[kernel], 0.3, 1.0)
     ref, sc = O.apply(p, q if nc > 1 else q[0], u if nc > 1 else u[0], with_scale=True)
@@ -71,21 +71,43 @@ def test_every_length_with_full_pencils(dev, pz, kernel):
     for prec in (B.FP64, B.FP32):
         for sched in (0, 1, 2) if kernel == B.NAVIER3D and pz in (256, 384, 512) else (0, 1):
             info = _check(dev, g, kernel, prec, pad=(32, 32, pz), autotune=2 + sched)
-            assert info["pad"] == [32, 32, pz] and info["zsched"] == sched
+            assert info["pad"] == info["lengths"] == [32, 32, pz] and info["zsched"] == sched
 
 
-@pytest.mark.parametrize("lo,hi,nz", [(0, 0, 40), (39, 39, 40), (7, 7, 128), (3, 18, 100), (99, 115, 128),
+@pytest.mark.parametrize("lo,hi,nz", [(0, 0, 40), (39, 39, 40), (7, 7, 128), (3, 18, 100), (99, 115, 128), (20, 160, 192), (0, 128, 180),
                                       (10, 57, 128), (1, 96, 128), (60, 200, 256), (0, 127, 256)])
 def test_shortened_length(dev, lo, hi, nz):
     """Planes lo..hi of nz: one plane, 2 nzo - 1 just below, at and just above
     a supported length, at either end of the grid; the reported pad stays the
-    grid's."""
+    grid's, the length in use is the smallest for the planes (Navier: not 320)."""
     g = _Nodes((20, 9, nz), lo, hi, seed=lo + hi)
     for kernel in (B.LAPLACE3D, B.NAVIER3D):
         for prec in (B.FP64, B.FP32):
             info = _check(dev, g, kernel, prec)
             want = min(s for s in B.supported_sizes() if s >= 2 * nz)
             assert info["pad"][2] == want and info["z_lo"] == lo and info["z_count"] == hi - lo + 1
+            use = min(s for s in B.supported_sizes() if s >= 2 * (hi - lo) + 1)
+            use = 384 if use == 320 and kernel == B.NAVIER3D else use
+            assert info["lengths"] == info["pad"][:2] + [min(use, want)]
+
+
+def test_kept_length(dev):
+    """A length that the caller asked for is kept, the 16-bit form keeps the grid's,
+    2D plans have none along z, Navier's 160-point grid its 320."""
+    g = _Nodes((20, 9, 160), 5, 30)
+    for prec, kernel, pad, want in ((B.FP64, B.LAPLACE3D, (0, 0, 320), 320), (B.BF16_MFMA, B.LAPLACE3D, (0, 0, 0), 320),
+                                    (B.FP32, B.NAVIER3D, (0, 0, 0), 64), (B.FP32, B.LAPLACE3D, (0, 0, 0), 64)):
+        plan = B.Plan(g, kernel, precision=prec, pad=pad)
+        assert plan.lengths() == [64, 32, want] and plan.info()["pad"] == [64, 32, 320]
+        plan.close()
+    full = B.Plan(_Nodes((20, 9, 160), 0, 159), B.NAVIER3D, precision=B.FP32)
+    assert full.lengths()[2] == 320
+    full.close()
+    from paper_1809_00845_amd import inputs as I
+
+    flat = B.Plan(I.circle2d(40, 0.4), B.LAPLACE2D)
+    assert flat.lengths() == flat.info()["pad"] == [96, 96, 1]
+    flat.close()
 
 
 def test_shortened_length_grid_field_and_batch(dev):

@@ -67,6 +67,22 @@ def test_traffic_lookup_needs_matching_workload_and_sources():
         assert t is None
 
 
+def test_byte_models_use_the_lengths_in_use():
+    """A body that does not fill its grid is credited with the transforms and spectra of
+    its own z length, not the grid's."""
+    import bench
+
+    info = {"pad": [256, 256, 256], "lengths": [256, 256, 96], "n": [128, 128, 128], "nfields": 4, "nspectra": 4,
+            "noutputs": 1, "m": 1000, "ncomp": 1, "z_count": 40, "spectra_bytes": 129 * 129 * 49 * 4 * 4}
+    full = dict(info, lengths=[256, 256, 256])
+    short, whole = bench.model_bytes(info, 4), bench.model_bytes(full, 4)
+    assert whole["zpass"] - short["zpass"] == 4 * 129 * 129 * (129 - 49) * 4
+    assert short["forward_xy"] == whole["forward_xy"]
+    a, b = bench.zpass_alu_view(info, 0.04), bench.zpass_alu_view(full, 0.04)
+    assert a["flops"] < 96 / 256 * b["flops"]
+    assert bench.stage_bytes(info, 4) == bench.stage_bytes(full, 4)
+
+
 def test_learned_summary():
     rows = [
         {"m": 10, "iters0": 30, "iters1": 28, "t0": 0.005, "t1": 0.006, "relres0": 9e-7, "relres1": 8e-7,

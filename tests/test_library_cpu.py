@@ -112,6 +112,7 @@ def test_null_arguments(lib):
     assert lib.bemfft_solve(None, None, None, None, None, None, None) == B.EINVAL
     assert lib.bemfft_plan_destroy(None) == 0
     assert lib.bemfft_plan_get_info(None, None) == B.EINVAL
+    assert lib.bemfft_plan_get_lengths(None, None) == B.EINVAL
 
 
 def test_net_validation_rejects_before_device_work(lib):
