@@ -462,7 +462,7 @@ __global__ __launch_bounds__(256) void k_conv16q(const _Float16 *__restrict__ in
                 *reinterpret_cast<h4 *>(out + (int64_t)v * 16 + 4 * kq) = o;
             }
         }
-        __syncthreads();  // the next range rewrites qx
+        __syncthreads();  // the next range rewrites qm and qp
     }
 }
 

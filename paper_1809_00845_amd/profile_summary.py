@@ -106,9 +106,9 @@ def _stats(d):
         for row in csv.DictReader(f):
             name = _norm(row["Name"])
             # rocprofv3 -T leaves some template kernels mangled; keep the readable core
-            for tag in ("k_conv16ILb0", "k_conv16ILb1"):
+            for tag in ("k_conv16ILb0", "k_conv16ILb1", "k_conv16qILb0", "k_conv16qILb1"):
                 if tag in name:
-                    name = "k_conv16<" + ("false" if tag.endswith("0") else "true") + ">"
+                    name = tag[:-4] + "<" + ("false" if tag.endswith("0") else "true") + ">"
             stats.append((name, int(row["Calls"]), float(row["AverageNs"]) / 1e3, float(row["MinNs"]) / 1e3,
                           float(row["MaxNs"]) / 1e3, float(row["TotalDurationNs"]) / 1e3))
     return sorted(stats, key=lambda r: -r[5])
